@@ -151,6 +151,8 @@ struct fr_dvm {
     void *d_tr[2] = {nullptr, nullptr};
     int cur_tr = 0;
     double *d_Q = nullptr;       // [ne*ns][nmom]
+    int nsplit[2] = {1, 1};      // workgroups per element of the box kernel: stage and residual, prime pass
+    double *d_Qpart = nullptr;   // [largest nsplit][ne*ns][nmom] their moments (where it is above 1)
     double *d_eq = nullptr;      // [ne*ns][kEqW]
     // [ne][kRefW] element references (FP32 deviation storage): three sets,
     // those of the value read by a stage, of its result, and (SSP) of the
@@ -241,6 +243,8 @@ struct StageArgs {
     int64_t e0, ecount;      // element range [e0, e0 + ecount); ecount 0: all elements
 };
 int launch_fr_axis(fr_dvm *h, int mode, const StageArgs &a, int do_traces, int do_moments);
+// workgroups per element of the box kernel under the handle's parameters
+int box_split(const fr_dvm *h, bool prime);
 // element references of the current equilibrium records into ref [ne][kRefW]
 int launch_elem_ref(fr_dvm *h, double *ref);
 // ---- mixed meshes (frdvm_gen.hip): same modes and arguments ----

@@ -84,6 +84,9 @@ struct FrArgs {
     const double *wrow;     // [nv_y nv_z][6] moment weights of a (y, z) row
     StageArgs sa;
     int do_traces, do_moments;
+    int nsplit;          // workgroups per element, each with its share of the velocity chunks
+    double *Qpart;       // [nsplit][npts][nmom] their moments (nsplit > 1)
+    int64_t npts;
     int64_t elem_comp;   // trace entries of one component in an element block
     const double *gfp;   // [npts] the pair's G factor delta theta / 2 (records of 6 / 11)
 };
@@ -342,7 +345,8 @@ k_fr_layer(const FrArgs A) {
     __shared__ __attribute__((aligned(16))) Real s_it[EQ_LDS ? NS : 1];
 
     const OpsR<Real> &op = ops_of<Real>(A);
-    const int64_t e = A.sa.e0 + blockIdx.x;
+    const int split = (int)(blockIdx.x % (unsigned)A.nsplit);
+    const int64_t e = A.sa.e0 + blockIdx.x / (unsigned)A.nsplit;
     const int tid = threadIdx.x;
     const int vl = tid & (kChunk - 1);                       // velocity of the chunk (lane)
     const int l = __builtin_amdgcn_readfirstlane(tid >> 6);  // z-layer of the wave
@@ -424,6 +428,8 @@ k_fr_layer(const FrArgs A) {
                                          : nullptr;
     const int nchunk = (nu + kChunk - 1) / kChunk;
     const int ntot = NCOMP * nchunk;  // chunks of all components, F first
+    // this workgroup's chunks [cc0, cc1)
+    const int cc0 = split * ntot / A.nsplit, cc1 = (split + 1) * ntot / A.nsplit;
 
     // The stage value and the inflow traces of chunk c+1 are requested while
     // chunk c is computed.  Of the z-face traces (N^2 points per velocity,
@@ -432,8 +438,10 @@ k_fr_layer(const FrArgs A) {
     SReal fc[NL];
     Real TX[N], TY[N], TZ[N];
     {
-        const Vel v0 = velocity(A, vl, true);
-        const uint32_t o = (lrow + (uint32_t)v0.k) * (uint32_t)sizeof(SReal);
+        const int comp0 = NCOMP == 2 && cc0 >= nchunk ? 1 : 0;
+        const Real *__restrict__ tr0 = trE + (NCOMP == 2 ? comp0 * A.elem_comp : 0);
+        const Vel v0 = velocity(A, (cc0 - comp0 * nchunk) * kChunk + vl, true);
+        const uint32_t o = (lrow + (uint32_t)(comp0 * nu + v0.k)) * (uint32_t)sizeof(SReal);
 #pragma unroll
         for (int q = 0; q < NL; ++q) fc[q] = ldn(fE, o + q * QB);
         if (FLUX) {
@@ -442,14 +450,14 @@ k_fr_layer(const FrArgs A) {
             const TraceOff sz = trace_in<Real>(A, T, v0, 2, N * l);
 #pragma unroll
             for (int a = 0; a < N; ++a) {
-                TX[a] = ldb(trE, sx.off + a * sx.stride);
-                TY[a] = ldb(trE, sy.off + a * sy.stride);
-                TZ[a] = ldb(trE, sz.off + a * sz.stride);
+                TX[a] = ldb(tr0, sx.off + a * sx.stride);
+                TY[a] = ldb(tr0, sy.off + a * sy.stride);
+                TZ[a] = ldb(tr0, sz.off + a * sz.stride);
             }
         }
     }
 
-    for (int cc = 0; cc < ntot; ++cc) {
+    for (int cc = cc0; cc < cc1; ++cc) {
         // the lane's tile column, recomputed every chunk: tile addresses are
         // then formed from it with immediate offsets instead of being kept
         // in registers across the loop
@@ -516,12 +524,13 @@ k_fr_layer(const FrArgs A) {
             for (int q = 0; q < NL; ++q) X[q] = SReal(0);
         }
         TraceOff nx{0u, 0u}, ny{0u, 0u};
-        // the next chunk (possibly the first of the next component)
+        // the next chunk (possibly the first of the next component; after
+        // the workgroup's last one every lane requests the last node)
         const int compn = NCOMP == 2 && cc + 1 >= nchunk ? 1 : 0;
         const Real *__restrict__ trEn = trE + (NCOMP == 2 ? compn * A.elem_comp : 0);
         {
             const int chn = cc + 1 - compn * nchunk;
-            const Vel vn = velocity(A, chn * kChunk + vl, NCOMP == 1 || cc + 1 < ntot);
+            const Vel vn = velocity(A, chn * kChunk + vl, cc + 1 < cc1);
             const uint32_t on = (lrow + (uint32_t)(compn * nu + vn.k)) * (uint32_t)sizeof(SReal);
 #pragma unroll
             for (int q = 0; q < NL; ++q) fc[q] = ldn(fE, on + q * QB);
@@ -806,9 +815,23 @@ k_fr_layer(const FrArgs A) {
 #pragma unroll
             for (int w = 1; w < N; ++w) t += red[w * NS * NMOM + i];
             // (deviation storage: plus the moments of the element reference)
-            A.sa.Q[(e * NS) * NMOM + i] = out_dev ? t + A.sa.ref_cur[e * kRefW + kRefCoef + i % NMOM] : t;
+            if (out_dev && split == 0) t += A.sa.ref_cur[e * kRefW + kRefCoef + i % NMOM];
+            double *Qo = A.nsplit > 1 ? A.Qpart + split * A.npts * NMOM : A.sa.Q;
+            Qo[(e * NS) * NMOM + i] = t;
         }
     }
+}
+
+// Moments of elements whose velocity chunks were split over several
+// workgroups: the parts added in their order.
+__global__ __launch_bounds__(256) void k_moment_parts(const double *__restrict__ part, int nsplit, int64_t stride,
+                                                      int64_t i0, int64_t n, double *__restrict__ Q) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    double t = part[i0 + i];
+#pragma unroll 4
+    for (int s = 1; s < nsplit; ++s) t += part[s * stride + i0 + i];
+    Q[i0 + i] = t;
 }
 
 // Element reference of the FP32 deviation storage from the current
@@ -883,13 +906,19 @@ __global__ __launch_bounds__(kRefBlock) void k_elem_ref(const FrArgs A, int ns, 
 
 template <typename Real, typename SReal, int P, int NMOM, bool ER>
 int launch_p(fr_dvm *h, int mode, const FrArgs &A) {
-    dim3 grid((unsigned)(A.sa.ecount ? A.sa.ecount : h->ne)), block(kChunk * (P + 1));
+    const int64_t ne = A.sa.ecount ? A.sa.ecount : h->ne;
+    dim3 grid((unsigned)(ne * A.nsplit)), block(kChunk * (P + 1));
     if (mode == MODE_PRIME)
         hipLaunchKernelGGL((k_fr_layer<Real, SReal, P, NMOM, MODE_PRIME, false>), grid, block, 0, h->stream, A);
     else if (mode == MODE_STAGE)
         hipLaunchKernelGGL((k_fr_layer<Real, SReal, P, NMOM, MODE_STAGE, ER>), grid, block, 0, h->stream, A);
     else
         hipLaunchKernelGGL((k_fr_layer<Real, SReal, P, NMOM, MODE_RESID, false>), grid, block, 0, h->stream, A);
+    if (A.nsplit > 1 && A.do_moments) {
+        const int64_t n = ne * h->ns * NMOM;
+        hipLaunchKernelGGL(k_moment_parts, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, h->stream, A.Qpart, A.nsplit,
+                           A.npts * NMOM, A.sa.e0 * h->ns * NMOM, n, A.sa.Q);
+    }
     hipError_t st = hipGetLastError();
     if (st != hipSuccess) return h->fail(FR_DVM_EHIP, std::string("FR kernel launch: ") + hipGetErrorString(st));
     return FR_DVM_OK;
@@ -948,16 +977,53 @@ void fill_args(fr_dvm *h, const StageArgs &sa, int do_traces, int do_moments, Fr
     A.sa = sa;
     A.do_traces = do_traces;
     A.do_moments = do_moments;
+    A.Qpart = h->d_Qpart;
+    A.npts = h->ne * h->ns;
     A.elem_comp = h->tl.elem / h->ncomp;
     A.gfp = h->d_gfp;
 }
 }  // namespace
+
+// Workgroups per element of the box kernel (prime: the moment / trace pass of
+// a given f).  One workgroup walks an element's velocity chunks in turn, so a
+// mesh of few elements leaves CUs idle while each element's chunks wait for
+// one another, and a launch of few rounds of resident workgroups ends in a
+// long, half-empty last round; such meshes have an element's chunks dealt to
+// several workgroups, whose moments k_moment_parts adds in order.
+//  * Where every workgroup still gets kSplitChunks chunks (its start-up,
+//    records and tables into LDS and the first chunk's loads exposed, is
+//    about one and a half): as many as make 16 rounds (the prime pass, which
+//    streams f at the copy rate by itself, 4).  Steps, one workgroup per
+//    element -> the rule's: 6^3 elements p = 3 pair 5.0 -> 2.3 ms, 12^3 FP64
+//    ES 26.0 -> 24.9, 16^3 deviation storage 43.5 -> 43.0, 16^3 FP64 BGK
+//    24.2 -> 23.7; at 24^3 (18 rounds) nothing is split.
+//  * On smaller meshes: the least of (rounds) x (chunks walked + start-up).
+//    60 elements p = 2, 19 x 17 x 18 velocities: 4.19 -> 0.87 ms for two
+//    steps (17 workgroups per element; 8: 1.04, 31: 0.90, 91: 0.99); 64
+//    elements p = 1, 8^3: 222 -> 119 us.
+// It depends on the whole mesh only, so a launch over a part of the elements
+// sums in the same order.
+int box_split(const fr_dvm *h, bool prime) {
+    constexpr int kSplitChunks = 8;
+    constexpr double kSplitSetup = 1.5;
+    const int n = h->n, per_simd = prime ? 4 : (h->prm.precision == FR_DVM_FP64 ? FRDVM_WAVES_F64 : FRDVM_WAVES_F32);
+    const int64_t slots = 256 * (4 * per_simd / n), rounds = prime ? 4 : 16;  // (n <= 4)
+    const int ntot = h->ncomp * ((h->vg.nu + kChunk - 1) / kChunk);
+    const int64_t most = ntot / kSplitChunks > 1 ? ntot / kSplitChunks : 1, want = (rounds * slots + h->ne - 1) / h->ne;
+    if (h->ne * most >= 2 * slots) return (int)(want < most ? want : most);
+    int s = 1;
+    auto cost = [&](int q) { return (double)((h->ne * q + slots - 1) / slots) * ((ntot + q - 1) / q + kSplitSetup); };
+    for (int q = 2; q <= ntot; ++q)
+        if (cost(q) < cost(s)) s = q;
+    return s;
+}
 
 int launch_fr_axis(fr_dvm *h, int mode, const StageArgs &sa, int do_traces, int do_moments) {
     if (sa.ecount < 0 || sa.e0 < 0 || (sa.ecount ? sa.e0 + sa.ecount > h->ne : sa.e0 != 0))
         return h->fail(FR_DVM_EINVAL, "element range");
     FrArgs A;
     fill_args(h, sa, do_traces, do_moments, A);
+    A.nsplit = h->nsplit[mode == MODE_PRIME ? 1 : 0];
     if (h->prm.precision == FR_DVM_FP32_DEV && mode == MODE_STAGE && (sa.in_dev || sa.out_dev)) {
         // FP32 arithmetic on deviations from element references (monatomic)
         if (!sa.ref_prev || !sa.ref_cur) return h->fail(FR_DVM_EINVAL, "element references missing");

@@ -727,6 +727,11 @@ extern "C" int fr_dvm_set_params(fr_dvm_t h, const fr_dvm_params *p) {
         if ((rc = dev_alloc(h, &h->d_wrow, wrow.size()))) return rc;
         if ((rc = upload(h, h->d_wrow, wrow.data(), wrow.size() * sizeof(double)))) return rc;
     }
+    if (realloc_all || realloc_mom) {
+        for (int k = 0; k < 2; ++k) h->nsplit[k] = h->axis_mode ? box_split(h, k == 1) : 1;
+        const int most = std::max(h->nsplit[0], h->nsplit[1]);
+        if ((rc = dev_alloc(h, &h->d_Qpart, most > 1 ? (size_t)most * npts * nmom : 0))) return rc;
+    }
     if (!h->axis_mode && !h->mx && (rc = gen_boundary_tables(h))) return rc;
     // verification switch: FRDVM_ES_DIRECT=1 makes the ES Newton use the
     // direct per-node sums instead of the factorised ones
@@ -815,7 +820,7 @@ extern "C" void fr_dvm_destroy(fr_dvm_t h) {
     if (h->stream) hipStreamSynchronize(h->stream); else hipDeviceSynchronize();
     free_mixed(h);
     void *ptrs[] = {h->d_gfac, h->d_nbr, h->d_wq3J, h->d_wx3, h->d_wrow, h->d_wax, h->d_reg, h->d_tr[0], h->d_tr[1],
-                    h->d_Q, h->d_eq, h->d_ref[0], h->d_ref[1], h->d_ref[2], h->d_z, h->d_prim, h->d_stats, h->d_maxres, h->d_tot, h->d_mlp,
+                    h->d_Q, h->d_Qpart, h->d_eq, h->d_ref[0], h->d_ref[1], h->d_ref[2], h->d_z, h->d_prim, h->d_stats, h->d_maxres, h->d_tot, h->d_mlp,
                     h->d_mlp_x, h->d_mlp_work, h->d_mlp_dz, h->d_pt_iters, h->d_pt_evals, h->d_pt_status,
                     h->d_pt_resid, h->d_S, h->d_ijac, h->d_nf, h->d_conn, h->d_wall, h->d_rw, h->d_mw,
                     h->d_finf, h->d_Sf, h->d_ijacf, h->d_nff, h->d_gfp};
