@@ -20,6 +20,7 @@ constexpr int kEqW = 12;   // per-point equilibrium record (see EqRec below)
 // its exponent polynomial, then its moments (5 or 10)
 constexpr int kRefW = 20;
 constexpr int kHist = 64;  // Newton iteration histogram bins
+constexpr int kTotBlocks = 256;  // workgroups of the domain totals
 
 // Per-point equilibrium record written by the Newton kernels and read by the
 // collision (fused or stand-alone):
@@ -170,7 +171,7 @@ struct fr_dvm {
     double *d_pt_resid = nullptr;
     int64_t *d_stats = nullptr;  // [kHist + 4]: histogram, fallback, ES guard, evaluations
     double *d_maxres = nullptr;  // [1] (as ordered bits)
-    double *d_tot = nullptr;     // [5]
+    double *d_tot = nullptr;     // [5], then the parts of the totals pass [kTotBlocks][5]
     float *d_mlp = nullptr;      // learned-guess network weights
     size_t mlp_n = 0;
     int mlp_hidden = 0;

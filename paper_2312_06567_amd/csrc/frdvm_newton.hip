@@ -605,35 +605,70 @@ __device__ void record_stats(const NewtonArgs &A, int64_t pt, int iters, int eva
 
 // Histogram of iterations, fallback / ES-guard counts, total evaluations and
 // the largest final residual, aggregated per workgroup in LDS and then added
-// to the handle's counters with one atomic per non-empty bin.
+// to the handle's counters with one atomic per non-empty bin.  Nearly every
+// point takes the same number of iterations, so one LDS atomic per point
+// would queue a whole wave on one bin (50 us for 262,144 points): each wave
+// counts its points of one iteration number with a ballot and adds that
+// once (7 us), four points per thread with their loads together.
+constexpr int kStatPts = 4;
 __global__ __launch_bounds__(256) void k_stats_reduce(int64_t npts, const int32_t *__restrict__ iters,
                                                       const int32_t *__restrict__ evals,
                                                       const int32_t *__restrict__ status,
                                                       const double *__restrict__ resid, unsigned long long *stats,
                                                       unsigned long long *maxres) {
     __shared__ unsigned int hist[kHist + 3];
-    __shared__ double rmax[256];
+    __shared__ double rmax[4];
     for (int i = threadIdx.x; i < kHist + 3; i += 256) hist[i] = 0u;
     __syncthreads();
+    const int lane = threadIdx.x & 63;
+    const int64_t step = (int64_t)gridDim.x * 256;
     double m = 0.0;
-    for (int64_t pt = (int64_t)blockIdx.x * 256 + threadIdx.x; pt < npts; pt += (int64_t)gridDim.x * 256) {
-        const int it = iters[pt];
-        atomicAdd(&hist[it < kHist ? (it < 0 ? 0 : it) : kHist - 1], 1u);
-        if (status[pt] == FR_DVM_NEWTON_FALLBACK) atomicAdd(&hist[kHist], 1u);
-        if (status[pt] == FR_DVM_NEWTON_ESGUARD) atomicAdd(&hist[kHist + 1], 1u);
-        atomicAdd(&hist[kHist + 2], (unsigned int)evals[pt]);
-        const double r = resid[pt];
-        if (r >= 0.0 && isfinite(r)) m = fmax(m, r);
+    unsigned int ev = 0u;
+    int64_t pt = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    for (int64_t base = 0; base < npts; base += kStatPts * step) {
+        int it[kStatPts], st[kStatPts];
+#pragma unroll
+        for (int a = 0; a < kStatPts; ++a) {
+            const int64_t q = pt + base + a * step;
+            const bool in = q < npts;
+            it[a] = in ? iters[q] : -1;
+            st[a] = in ? status[q] : -1;
+            ev += in ? (unsigned int)evals[q] : 0u;
+            const double r = in ? resid[q] : 0.0;
+            if (in) it[a] = it[a] < kHist ? (it[a] < 0 ? 0 : it[a]) : kHist - 1;
+            if (r >= 0.0 && isfinite(r)) m = fmax(m, r);
+        }
+#pragma unroll
+        for (int a = 0; a < kStatPts; ++a) {
+            unsigned long long todo = __ballot(it[a] >= 0);
+            while (todo) {
+                const int v = __shfl(it[a], __ffsll(todo) - 1);
+                const unsigned long long same = __ballot(it[a] == v);
+                if (lane == 0) atomicAdd(&hist[v], (unsigned int)__popcll(same));
+                todo &= ~same;
+            }
+            const unsigned long long fb = __ballot(st[a] == FR_DVM_NEWTON_FALLBACK);
+            const unsigned long long eg = __ballot(st[a] == FR_DVM_NEWTON_ESGUARD);
+            if (lane == 0 && fb) atomicAdd(&hist[kHist], (unsigned int)__popcll(fb));
+            if (lane == 0 && eg) atomicAdd(&hist[kHist + 1], (unsigned int)__popcll(eg));
+        }
     }
-    rmax[threadIdx.x] = m;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        ev += __shfl_xor(ev, o);
+        m = fmax(m, __shfl_xor(m, o));
+    }
+    if (lane == 0) {
+        if (ev) atomicAdd(&hist[kHist + 2], ev);
+        rmax[threadIdx.x >> 6] = m;
+    }
     __syncthreads();
-    for (int o = 128; o >= 1; o >>= 1) {
-        if ((int)threadIdx.x < o) rmax[threadIdx.x] = fmax(rmax[threadIdx.x], rmax[threadIdx.x + o]);
-        __syncthreads();
-    }
     for (int i = threadIdx.x; i < kHist + 3; i += 256)
         if (hist[i]) atomicAdd(&stats[i], (unsigned long long)hist[i]);
-    if (threadIdx.x == 0 && rmax[0] > 0.0) atomicMax(maxres, (unsigned long long)__double_as_longlong(rmax[0]));
+    if (threadIdx.x == 0) {
+        m = fmax(fmax(rmax[0], rmax[1]), fmax(rmax[2], rmax[3]));
+        if (m > 0.0) atomicMax(maxres, (unsigned long long)__double_as_longlong(m));
+    }
 }
 
 // Second starting point besides the cold one (warm or learned), if any.
@@ -1162,27 +1197,40 @@ __global__ __launch_bounds__(64 * kKnElems) void k_kn_gll(NewtonArgs A, Ops1D op
     kn[pt] = out;
 }
 
-// Domain totals: one workgroup, fixed-order strided sums and tree reduction.
-__global__ __launch_bounds__(1024) void k_totals(int64_t npts, int nmom, const double *__restrict__ Q,
-                                                 const double *__restrict__ wJ, double *__restrict__ out) {
-    __shared__ double red[5][1024];
-    double a[5] = {0, 0, 0, 0, 0};
-    for (int64_t pt = threadIdx.x; pt < npts; pt += 1024) {
-        const double *q = Q + pt * nmom;
-        const double w = wJ[pt];
-        a[0] += w * q[0]; a[1] += w * q[1]; a[2] += w * q[2]; a[3] += w * q[3];
-        a[4] += w * record_energy(q, nmom);
-    }
+// Domain totals in two passes of fixed order: each workgroup sums a strided
+// share of the points, the last pass adds the workgroups.  (One workgroup over
+// all points waits on its own loads: 179 us at 262,144 points, now 11.)
+__device__ __forceinline__ void block_totals(const double a[5], double *__restrict__ out) {
+    __shared__ double red[5][256];
 #pragma unroll
     for (int c = 0; c < 5; ++c) red[c][threadIdx.x] = a[c];
     __syncthreads();
-    for (int o = 512; o >= 1; o >>= 1) {
+    for (int o = 128; o >= 1; o >>= 1) {
         if ((int)threadIdx.x < o)
 #pragma unroll
             for (int c = 0; c < 5; ++c) red[c][threadIdx.x] += red[c][threadIdx.x + o];
         __syncthreads();
     }
     if (threadIdx.x < 5) out[threadIdx.x] = red[threadIdx.x][0];
+}
+__global__ __launch_bounds__(256) void k_totals(int64_t npts, int nmom, const double *__restrict__ Q,
+                                                const double *__restrict__ wJ, double *__restrict__ part) {
+    double a[5] = {0, 0, 0, 0, 0};
+#pragma unroll 4
+    for (int64_t pt = (int64_t)blockIdx.x * 256 + threadIdx.x; pt < npts; pt += (int64_t)gridDim.x * 256) {
+        const double *q = Q + pt * nmom;
+        const double w = wJ[pt];
+        a[0] += w * q[0]; a[1] += w * q[1]; a[2] += w * q[2]; a[3] += w * q[3];
+        a[4] += w * record_energy(q, nmom);
+    }
+    block_totals(a, part + 5 * blockIdx.x);
+}
+__global__ __launch_bounds__(256) void k_totals_sum(int n, const double *__restrict__ part, double *__restrict__ out) {
+    double a[5] = {0, 0, 0, 0, 0};
+    if ((int)threadIdx.x < n)  // (n <= kTotBlocks = 256)
+#pragma unroll
+        for (int c = 0; c < 5; ++c) a[c] = part[5 * threadIdx.x + c];
+    block_totals(a, out);
 }
 
 int check(fr_dvm *h, const char *what) {
@@ -1295,7 +1343,7 @@ int newton_run(fr_dvm *h, NewtonArgs A, int64_t p0, int64_t np, hipStream_t s) {
     } else {
         hipLaunchKernelGGL(k_newton_bgk, dim3((unsigned)((A.npts + 255) / 256)), dim3(256), 0, s, A);
     }
-    int64_t nb = (A.npts + 256 * 16 - 1) / (256 * 16);
+    int64_t nb = (A.npts + 256 * kStatPts - 1) / (256 * kStatPts);
     if (nb > 1024) nb = 1024;
     hipLaunchKernelGGL(k_stats_reduce, dim3((unsigned)nb), dim3(256), 0, s, A.npts, A.pt_iters, A.pt_evals,
                        A.pt_status, A.pt_resid, A.stats, A.maxres);
@@ -1409,7 +1457,10 @@ int launch_kn_gll(fr_dvm *h, double *kn) {
 
 int launch_totals(fr_dvm *h, double *host_tot) {
     const int64_t npts = h->ne * h->ns;
-    hipLaunchKernelGGL(k_totals, dim3(1), dim3(1024), 0, h->stream, npts, h->nmom, h->d_Q, h->d_wq3J, h->d_tot);
+    const int64_t nb = (npts + 255) / 256;
+    const int n = (int)(nb < kTotBlocks ? nb : kTotBlocks);
+    hipLaunchKernelGGL(k_totals, dim3(n), dim3(256), 0, h->stream, npts, h->nmom, h->d_Q, h->d_wq3J, h->d_tot + 5);
+    hipLaunchKernelGGL(k_totals_sum, dim3(1), dim3(256), 0, h->stream, n, h->d_tot + 5, h->d_tot);
     int rc = check(h, "totals kernel");
     if (rc) return rc;
     if (hipMemcpyAsync(host_tot, h->d_tot, 5 * sizeof(double), hipMemcpyDeviceToHost, h->stream) != hipSuccess)

@@ -516,7 +516,7 @@ int finish_create(fr_dvm *h, const std::vector<double> &wq3J) {
     if ((rc = upload(h, h->d_wax, wax.data(), wax.size() * sizeof(double)))) return rc;
     if ((rc = dev_alloc(h, &h->d_stats, kHist + 4))) return rc;
     if ((rc = dev_alloc(h, &h->d_maxres, 1))) return rc;
-    if ((rc = dev_alloc(h, &h->d_tot, 8))) return rc;
+    if ((rc = dev_alloc(h, &h->d_tot, 5 + 5 * kTotBlocks))) return rc;
     hipMemset(h->d_stats, 0, (kHist + 4) * sizeof(int64_t));
     hipMemset(h->d_maxres, 0, sizeof(double));
     return FR_DVM_OK;
