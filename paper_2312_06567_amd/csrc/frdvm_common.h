@@ -176,9 +176,8 @@ struct fr_dvm {
     size_t mlp_n = 0;
     int mlp_hidden = 0;
     float *d_mlp_x = nullptr;    // feature batch
-    float *d_mlp_work = nullptr; // forward workspace
     float *d_mlp_dz = nullptr;   // [npts][5] predicted Newton corrections
-    size_t mlp_x_n = 0, mlp_work_n = 0, dz_n = 0;
+    size_t mlp_x_n = 0, dz_n = 0;
     size_t owned_bytes = 0;
 
     // HIP-event kernel timing (fr_dvm_profile)
@@ -274,6 +273,9 @@ int launch_newton(fr_dvm *h, int guess);
 // newton_part_ok tells whether the handle's start allows it).
 int newton_part_ok(fr_dvm *h, int guess);
 int launch_newton_part(fr_dvm *h, int guess, int64_t p0, int64_t np, hipStream_t s);
+// ---- learned start (frdvm_mlp.hip) ----
+// Prediction of B rows times env[row], for networks a handle may hold (H <= 64).
+int mlp_forward_scaled(int H, const float *w, const float *X, int64_t B, const float *env, float *dz, hipStream_t s);
 int launch_newton_points(fr_dvm *h, const double *Q, int64_t n, int guess, double *z, int32_t *iters, int32_t *evals,
                          int32_t *status, double *resid);
 int launch_collide(fr_dvm *h, const void *f, void *S, int accumulate);

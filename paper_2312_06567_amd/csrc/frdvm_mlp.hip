@@ -241,7 +241,8 @@ __device__ __forceinline__ floatx4 tile_product(const float *A, int ld, int r, i
 }
 
 // GRAD: the gradient pass (partial gradient rows of `out`, or the gradient
-// itself when the grid is one workgroup); else the prediction dz in `out`.
+// itself when the grid is one workgroup); else the prediction dz in `out`,
+// times T[row] if T is given.
 template <int HT, bool GRAD>
 __global__ __launch_bounds__(64 * HT) void k_mlp_rows(const float *__restrict__ w, const float *__restrict__ X,
                                                       const float *__restrict__ T, int64_t B, int H, Layout L,
@@ -316,7 +317,10 @@ __global__ __launch_bounds__(64 * HT) void k_mlp_rows(const float *__restrict__ 
                 const floatx4 y = tile_product<HT>(sA[0], S, r, q, f3);
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    if (r < 5 && m0 + 4 * q + i < B) out[(m0 + 4 * q + i) * 5 + r] = (y[i] + b3) * sc + of;
+                    if (r < 5 && m0 + 4 * q + i < B) {
+                        const float v = (y[i] + b3) * sc + of;
+                        out[(m0 + 4 * q + i) * 5 + r] = T ? v * T[m0 + 4 * q + i] : v;
+                    }
             }
             continue;
         }
@@ -451,9 +455,10 @@ void launch_rows(hipStream_t s, int H, unsigned nwg, const float *w, const float
 
 // Prediction of a batch: up to four workgroups per CU, each looping over its
 // row blocks with the weights in registers.
-void forward_rows(hipStream_t s, int H, const float *w, const float *X, int64_t B, float *dz) {
+void forward_rows(hipStream_t s, int H, const float *w, const float *X, int64_t B, float *dz,
+                  const float *env = nullptr) {
     const int64_t nblk = (B + 15) / 16;
-    launch_rows<false>(s, H, (unsigned)(nblk < 1024 ? nblk : 1024), w, X, nullptr, B, dz, nullptr, 0);
+    launch_rows<false>(s, H, (unsigned)(nblk < 1024 ? nblk : 1024), w, X, env, B, dz, nullptr, 0);
 }
 
 // Forward pass into the workspace; Y holds the normalised output.
@@ -501,6 +506,13 @@ int hip_ok(const char *what) {
 }
 
 }  // namespace
+
+int mlp_forward_scaled(int H, const float *w, const float *X, int64_t B, const float *env, float *dz, hipStream_t s) {
+    if (H < 1 || H > kRowsMaxH) return FR_DVM_EUNSUPPORTED;
+    forward_rows(s, H, w, X, B, dz, env);
+    return hip_ok("mlp forward");
+}
+
 }  // namespace frdvm
 
 using namespace frdvm;

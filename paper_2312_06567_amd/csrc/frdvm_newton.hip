@@ -27,6 +27,7 @@
 // learned start never costs more than one extra evaluation).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 
@@ -174,14 +175,17 @@ __device__ __forceinline__ void assemble(const Sums &s, double r[5], double J[5]
 }
 
 // BGK sums by axis factorisation: e = exp(z0) prod_d exp(z_d c_d - z4 c_d^2 / 2).
-__device__ void sums_bgk(const NewtonArgs &A, const double U[3], double ist, const double z[5], Sums &s) {
+// LPP lanes of a point take every LPP-th node of each axis and add their
+// sums in a butterfly (every lane gets the same bits).
+template <int LPP>
+__device__ void sums_bgk(const NewtonArgs &A, int lane, const double U[3], double ist, const double z[5], Sums &s) {
     double m[3][5];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         double a0 = 0, a1 = 0, a2 = 0, a3 = 0, a4 = 0;
         const int nv = A.vg.nv[d];
         const double zd = z[1 + d], hz = 0.5 * z[4];
-        for (int i = 0; i < nv; ++i) {
+        for (int i = lane; i < nv; i += LPP) {
             const double c = (gridu(A.vg, d, i) - U[d]) * ist;
             const double ev = A.wax[64 * d + i] * ist * exp(c * (zd - hz * c));
             double t = ev;
@@ -193,6 +197,12 @@ __device__ void sums_bgk(const NewtonArgs &A, const double U[3], double ist, con
         }
         m[d][0] = a0; m[d][1] = a1; m[d][2] = a2; m[d][3] = a3; m[d][4] = a4;
     }
+#pragma unroll
+    for (int o = LPP / 2; o >= 1; o >>= 1)
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+#pragma unroll
+            for (int a = 0; a < 5; ++a) m[d][a] += __shfl_xor(m[d][a], o, LPP);
     const double K = exp(z[0]) * m[0][0] * m[1][0] * m[2][0];
     double Pn[3][5];
 #pragma unroll
@@ -568,6 +578,10 @@ __device__ void write_point(const NewtonArgs &A, int64_t pt, double rho, const d
     for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int j = 0; j < 3; ++j) mAm += m[i] * Am[i][j] * m[j];
+#pragma unroll
+    for (int a = 0; a < 5; ++a)
+        if (A.z) A.z[pt * 5 + a] = z[a];
+    if (!A.eq) return;  // moment vectors of the caller: no record
     const double st = sqrt(th);
     double *eq = A.eq + pt * kEqW;
     eq[EQ_C0] = log(rho) - 1.5 * log(th) + z[0] + 0.5 * z[4] * mAm;
@@ -583,15 +597,16 @@ __device__ void write_point(const NewtonArgs &A, int64_t pt, double rho, const d
 #pragma unroll
     for (int d = 0; d < 3; ++d) pp[1 + d] = eq[EQ_V + d];
     pp[4] = th / z[4];
-#pragma unroll
-    for (int a = 0; a < 5; ++a) A.z[pt * 5 + a] = z[a];
 }
 
 __device__ void write_nonreal(const NewtonArgs &A, int64_t pt) {
+    for (int a = 0; a < 5; ++a)
+        if (A.z) A.z[pt * 5 + a] = 0.0;
+    if (!A.eq) return;
     double *eq = A.eq + pt * kEqW;
     eq[EQ_C0] = -INFINITY;
     for (int a = 1; a < kEqW; ++a) eq[a] = 0.0;
-    for (int a = 0; a < 5; ++a) { A.prim[pt * 5 + a] = 0.0; A.z[pt * 5 + a] = 0.0; }
+    for (int a = 0; a < 5; ++a) A.prim[pt * 5 + a] = 0.0;
 }
 
 // Per-point outcome; the counters are aggregated afterwards by k_stats_reduce
@@ -912,9 +927,15 @@ __device__ int newton_solve_es(const NewtonArgs &A, SumsFn sums, int64_t pt, con
     return conv;
 }
 
-__global__ __launch_bounds__(256) void k_newton_bgk(const NewtonArgs A) {
-    const int64_t pt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (pt >= A.npts) return;
+constexpr int kBgkBlock = 64;
+// One solution point per LPP lanes; the iteration runs alike in all of them
+// and the first writes the point (launch_bgk chooses LPP).
+template <int LPP>
+__global__ __launch_bounds__(kBgkBlock) void k_newton_bgk(const NewtonArgs A) {
+    const int64_t pt = ((int64_t)blockIdx.x * kBgkBlock + threadIdx.x) / LPP;
+    const int lane = threadIdx.x % LPP;
+    if (pt >= A.npts) return;  // a point's lanes leave together
+    const bool first = lane == 0;
     const double *Q = A.Q + pt * A.nmom;
     const double rho = Q[0];
     const double irho = 1.0 / rho;
@@ -923,20 +944,23 @@ __global__ __launch_bounds__(256) void k_newton_bgk(const NewtonArgs A) {
     const double E = record_energy(Q, A.nmom);
     const double th = (2.0 / (3.0 + A.delta)) * (E * irho - 0.5 * (U[0] * U[0] + U[1] * U[1] + U[2] * U[2]));
     if (!(rho > 0.0) || !(th > 0.0) || !isfinite(rho) || !isfinite(th)) {
-        write_nonreal(A, pt);
-        if (A.gfp) A.gfp[pt] = 0.0;
-        record_stats(A, pt, 0, 0, FR_DVM_NEWTON_NONREAL, -1.0);
+        if (first) {
+            write_nonreal(A, pt);
+            if (A.gfp) A.gfp[pt] = 0.0;
+            record_stats(A, pt, 0, 0, FR_DVM_NEWTON_NONREAL, -1.0);
+        }
         return;
     }
-    if (A.gfp) A.gfp[pt] = 0.5 * A.delta * th;
+    if (A.gfp && first) A.gfp[pt] = 0.5 * A.delta * th;
     const double inv_tau = rho * th / viscosity(A, th);
     const double ist = 1.0 / sqrt(th);
     const double zc[5] = {-1.5 * log(kTwoPi), 0.0, 0.0, 0.0, 1.0};
     double z[5];
-    auto fn = [&](const double zz[5], Sums &s, bool) { sums_bgk(A, U, ist, zz, s); };
+    auto fn = [&](const double zz[5], Sums &s, bool) { sums_bgk<LPP>(A, lane, U, ist, zz, s); };
     double res;
     int iters, evals;
     const int conv = newton_solve(A, fn, pt, zc, z, res, iters, evals);
+    if (!first) return;
     const double Am[3][3] = {{1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
     write_point(A, pt, rho, U, th, Am, z, inv_tau, res);
     record_stats(A, pt, iters, evals, conv ? FR_DVM_NEWTON_OK : FR_DVM_NEWTON_FALLBACK, res);
@@ -1050,11 +1074,6 @@ __device__ __forceinline__ double guess_envelope(const double U[3], double th, d
     }
     const double s = exp(-0.5 * kTwoPi * kTwoPi * th / (du * du)) + tr;
     return fmin(fmax(s, 1e-10), 1.0);  // below 1e-10 the correction is Newton round-off
-}
-
-__global__ void k_mlp_scale(int64_t n, const float *__restrict__ env, float *__restrict__ dz) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n * 5) dz[i] *= env[i / 5];
 }
 
 // Features of the learned guess from the moments: [ln rho, U/u_max, ln theta,
@@ -1280,17 +1299,16 @@ double grid_umax(const VGrid &vg) {
 int mlp_predict(fr_dvm *h, const double *Q, int64_t n, int nmom, float *dz) {
     const int64_t batch = 65536;
     const int64_t nb = n < batch ? n : batch;
-    const size_t need_x = (size_t)nb * (FR_MLP_INPUTS + 1), need_w = fr_mlp_workspace_floats(h->mlp_hidden, nb);
-    if (h->mlp_x_n < need_x || h->mlp_work_n < need_w) {
+    const size_t need_x = (size_t)nb * (FR_MLP_INPUTS + 1);
+    if (h->mlp_x_n < need_x) {
         if (h->d_mlp_x) (void)hipFree(h->d_mlp_x);
-        if (h->d_mlp_work) (void)hipFree(h->d_mlp_work);
         h->d_mlp_x = nullptr;
-        h->d_mlp_work = nullptr;
-        if (hipMalloc(&h->d_mlp_x, need_x * sizeof(float)) != hipSuccess ||
-            hipMalloc(&h->d_mlp_work, need_w * sizeof(float)) != hipSuccess)
-            return h->fail(FR_DVM_ENOMEM, "MLP workspace");
+        h->mlp_x_n = 0;
+        if (hipMalloc(&h->d_mlp_x, need_x * sizeof(float)) != hipSuccess) {
+            h->d_mlp_x = nullptr;
+            return h->fail(FR_DVM_ENOMEM, "MLP features");
+        }
         h->mlp_x_n = need_x;
-        h->mlp_work_n = need_w;
     }
     const double umax = grid_umax(h->vg);
     const double du = std::fmax(h->vg.du[0], std::fmax(h->vg.du[1], h->vg.du[2]));
@@ -1299,10 +1317,8 @@ int mlp_predict(fr_dvm *h, const double *Q, int64_t n, int nmom, float *dz) {
         const int64_t m = (n - b0) < batch ? (n - b0) : batch;
         hipLaunchKernelGGL(k_mlp_features, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, h->stream, m, nmom,
                            Q + b0 * nmom, h->vg, umax, du, h->d_mlp_x, env);
-        int rc = fr_mlp_forward(h->mlp_hidden, h->d_mlp, h->d_mlp_x, m, dz + b0 * 5, h->d_mlp_work, h->stream);
+        int rc = mlp_forward_scaled(h->mlp_hidden, h->d_mlp, h->d_mlp_x, m, env, dz + b0 * 5, h->stream);
         if (rc) return h->fail(rc, "MLP forward");
-        hipLaunchKernelGGL(k_mlp_scale, dim3((unsigned)((m * 5 + 255) / 256)), dim3(256), 0, h->stream, m, env,
-                           dz + b0 * 5);
     }
     return check(h, "MLP features");
 }
@@ -1311,7 +1327,11 @@ int ensure_dz(fr_dvm *h, int64_t n) {
     if (h->dz_n >= (size_t)n) return FR_DVM_OK;
     if (h->d_mlp_dz) (void)hipFree(h->d_mlp_dz);
     h->d_mlp_dz = nullptr;
-    if (hipMalloc(&h->d_mlp_dz, sizeof(float) * 5 * n) != hipSuccess) return h->fail(FR_DVM_ENOMEM, "MLP output");
+    h->dz_n = 0;
+    if (hipMalloc(&h->d_mlp_dz, sizeof(float) * 5 * n) != hipSuccess) {
+        h->d_mlp_dz = nullptr;
+        return h->fail(FR_DVM_ENOMEM, "MLP output");
+    }
     h->dz_n = n;
     return FR_DVM_OK;
 }
@@ -1319,6 +1339,28 @@ int ensure_dz(fr_dvm *h, int64_t n) {
 }  // namespace
 
 namespace {
+
+template <int LPP>
+void launch_bgk_lanes(const NewtonArgs &A, hipStream_t s) {
+    constexpr int per = kBgkBlock / LPP;
+    hipLaunchKernelGGL(k_newton_bgk<LPP>, dim3((unsigned)((A.npts + per - 1) / per)), dim3(kBgkBlock), 0, s, A);
+}
+// Lanes per point: one where the points alone fill the chip (the sums are a
+// part of the work, the 5 x 5 solves are repeated by every lane: at 262,144
+// points of a 32^3 grid 1, 2, 4, 8 lanes take 356, 370, 439, 596 us), more
+// on small batches, where one lane's chain over the nodes is the time (4096
+// points: 99, 71, 52, 47 us; 512 points of an 8^3 grid 57, 51, 46, 44 us, of
+// which 30 are the call).  The lines lie where the measured times cross:
+// with the axis length, since the shared part grows with it.  `all` counts
+// the points of the whole solve, of which A may be a part: the order of a
+// point's sums does not depend on the part it is solved in.
+void launch_bgk(const NewtonArgs &A, int64_t all, hipStream_t s) {
+    const int64_t nv = std::max(A.vg.nv[0], std::max(A.vg.nv[1], A.vg.nv[2]));
+    if (all <= 128 * nv) launch_bgk_lanes<8>(A, s);
+    else if (all <= 512 * nv) launch_bgk_lanes<4>(A, s);
+    else if (all <= 2048 * nv) launch_bgk_lanes<2>(A, s);
+    else launch_bgk_lanes<1>(A, s);
+}
 
 // The Newton kernel and its statistics over the points [p0, p0 + np) on
 // stream s: every per-point array of A is offset to p0, so the kernels see a
@@ -1341,7 +1383,7 @@ int newton_run(fr_dvm *h, NewtonArgs A, int64_t p0, int64_t np, hipStream_t s) {
         const size_t shm = kEsPts * sizeof(double) * (size_t)es_slot_doubles(h->vg, A.use_fact);
         hipLaunchKernelGGL(k_newton_es, dim3((unsigned)((A.npts + kEsPts - 1) / kEsPts)), dim3(kEsBlock), shm, s, A);
     } else {
-        hipLaunchKernelGGL(k_newton_bgk, dim3((unsigned)((A.npts + 255) / 256)), dim3(256), 0, s, A);
+        launch_bgk(A, h->ne * h->ns, s);
     }
     int64_t nb = (A.npts + 256 * kStatPts - 1) / (256 * kStatPts);
     if (nb > 1024) nb = 1024;
@@ -1384,19 +1426,12 @@ int launch_newton_part(fr_dvm *h, int guess, int64_t p0, int64_t np, hipStream_t
 }
 
 // Newton on caller-supplied moment vectors (BGK form), for training targets
-// and guess evaluation.  Scratch records are allocated per call.
+// and guess evaluation: the per-point outputs only, no equilibrium records.
 int launch_newton_points(fr_dvm *h, const double *Q, int64_t n, int guess, double *z, int32_t *iters,
                          int32_t *evals, int32_t *status, double *resid) {
     if (n <= 0) return FR_DVM_OK;
     if (guess == FR_DVM_GUESS_MLP && !h->d_mlp) return h->fail(FR_DVM_EINVAL, "no MLP weights set");
     NewtonArgs A = newton_args(h, guess == FR_DVM_GUESS_MLP ? FR_DVM_GUESS_MLP : FR_DVM_GUESS_COLD);
-    double *eq = nullptr, *prim = nullptr, *zz = nullptr;
-    if (hipMalloc(&eq, sizeof(double) * kEqW * n) != hipSuccess || hipMalloc(&prim, sizeof(double) * 5 * n) != hipSuccess ||
-        (!z && hipMalloc(&zz, sizeof(double) * 5 * n) != hipSuccess)) {
-        if (eq) (void)hipFree(eq);
-        if (prim) (void)hipFree(prim);
-        return h->fail(FR_DVM_ENOMEM, "equilibrium scratch");
-    }
     int rc = FR_DVM_OK;
     if (A.guess == FR_DVM_GUESS_MLP) {
         rc = ensure_dz(h, n);
@@ -1407,9 +1442,9 @@ int launch_newton_points(fr_dvm *h, const double *Q, int64_t n, int guess, doubl
         A.npts = n;
         A.nmom = 5;
         A.Q = Q;
-        A.eq = eq;
-        A.prim = prim;
-        A.z = z ? z : zz;
+        A.eq = nullptr;
+        A.prim = nullptr;
+        A.z = z;
         A.pt_iters = iters;
         A.pt_evals = evals;
         A.pt_status = status;
@@ -1417,13 +1452,10 @@ int launch_newton_points(fr_dvm *h, const double *Q, int64_t n, int guess, doubl
         A.delta = 0.0;  // monatomic moment vectors
         A.gfp = nullptr;
         if (!(A.mu_ref > 0)) A.mu_ref = 1.0;  // tau is not an output here
-        hipLaunchKernelGGL(k_newton_bgk, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, h->stream, A);
+        launch_bgk(A, n, h->stream);
         rc = check(h, "newton kernel");
     }
     (void)hipStreamSynchronize(h->stream);
-    (void)hipFree(eq);
-    (void)hipFree(prim);
-    if (zz) (void)hipFree(zz);
     return rc;
 }
 
