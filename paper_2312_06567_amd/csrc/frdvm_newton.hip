@@ -18,9 +18,8 @@
 // BGK kernel: one thread per point.  On a tensor velocity grid the BGK
 // exponential factorises per axis, so each Newton iteration costs 3 n_v
 // exponentials and 1-D power sums instead of n_v^3 terms.
-// ES kernel: 32 lanes per point (two points per wave), lanes over velocity
-// nodes or node pairs, butterfly reduction of the 18 sums (lane-symmetric:
-// every lane gets the same bits); the iteration state lives in LDS.
+// ES kernel: a wave per point for the sums, one thread per point for the
+// iteration around them; the state the two share lives in LDS.
 // Starting points: cold (continuous equilibrium of the moments), warm (the
 // previous solution at the point) or learned (cold + a correction predicted
 // by the MLP kernels; the start with the smaller residual is kept, so the
@@ -59,7 +58,8 @@ struct NewtonArgs {
     int max_iter;
     int guess;
     const float *dz_guess;  // [npts][5] learned correction (guess == MLP)
-    int use_fact;           // ES: factorised sums with per-point LDS tables
+    int use_fact;           // ES: factorised sums
+    int nph, es_pts;        // ES: lanes that share an x node, points per workgroup
     double delta;           // internal degrees of freedom (the reduced pair)
     double *gfp;            // [npts] delta theta / 2 per point (pair only, else null)
 };
@@ -235,38 +235,76 @@ __device__ void sums_bgk(const NewtonArgs &A, int lane, const double U[3], doubl
     s.Sc2q = K * t4;
 }
 
-// ES sums: kLpp lanes per solution point (two points per wave), reduced by
-// a butterfly inside each half-wave.
-constexpr int kLpp = 32;
+// ---- ES sums: one wave per solution point --------------------------------
+// The state of a point's iteration that its wave and its owner thread share
+// (see k_newton_es): the frame (U, theta^-1/2, A = theta T^-1 as xx yy zz xy
+// xz yz), the point z under evaluation, and two sets of sums.
+constexpr int kSumsD = (int)(sizeof(Sums) / sizeof(double));
+struct EsPoint {
+    double U[3], ist, A[6], z[5];
+    Sums s[2];
+    int req, tgt;  // requested evaluation (kReq*; 0: none) and the set it goes to
+};
+constexpr int kReqSums = 1, kReqJac = 2, kReqDirect = 4;  // kReqJac: all 18 sums, not the residual's 5 only
 
-__device__ __forceinline__ double wave_sum(double v) {
+// Sums over the 64 lanes of N values each, value k left with one lane of the
+// wave: each step halves the values a lane carries (it keeps one half and
+// sends the other to its partner), 21 exchanges for 18 values instead of the
+// 108 of a butterfly per value.  Returns the lane's sum; `slot` is the index
+// of its value (lanes without one: -1).
+template <int N, int O>
+__device__ __forceinline__ double spread_sum(const double *v, int lane, int base, int n_valid, int &slot) {
+    const bool up = (lane & O) != 0;
+    constexpr int H = (N + 1) / 2;  // values kept (an odd count is padded with a zero)
+    double w[H];
+    if constexpr (N == 1) {
+        w[0] = v[0] + __shfl_xor(v[0], O);
+    } else {
 #pragma unroll
-    for (int o = kLpp / 2; o >= 1; o >>= 1) v += __shfl_xor(v, o, kLpp);
-    return v;
+        for (int k = 0; k < H; ++k) {
+            const double lo = v[k], hi = k + H < N ? v[k + H] : 0.0;
+            w[k] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, O);
+        }
+        base += up ? H : 0;
+        n_valid = up ? (n_valid - H < H ? n_valid - H : H) : (n_valid < H ? n_valid : H);
+    }
+    if constexpr (O == 1) {
+        slot = n_valid > 0 ? base : -1;
+        return w[0];
+    } else {
+        return spread_sum<H, O / 2>(w, lane, base, n_valid, slot);
+    }
+}
+template <int N>
+__device__ __forceinline__ void store_sums(const double *v, int lane, double *out) {
+    int slot;
+    const double t = spread_sum<N, 32>(v, lane, 0, N, slot);
+    if (slot >= 0) out[slot] = t;  // (lanes that share a value write the same bits)
 }
 
-// ES sums over all velocity nodes: lane-strided, butterfly reduced.  With
-// jac == false only the residual sums S0, Sc and the trace of Scc (stored in
-// Scc[0]) are formed.
-__device__ void sums_es(const NewtonArgs &A, int lane, const double U[3], double ist, double wscale,
-                        const double Am[3][3], const double z[5], Sums &s, bool jac) {
+// Sums over all velocity nodes, lane-strided, without factorisation.  With
+// JAC == false only the residual sums S0, Sc and the trace of Scc (stored in
+// Scc[0], the other diagonal entries zero) are formed.
+template <bool JAC>
+__device__ void sums_es(const NewtonArgs &A, int lane, const EsPoint &p, double *out) {
     double acc[18];
 #pragma unroll
     for (int a = 0; a < 18; ++a) acc[a] = 0.0;
     const VGrid &vg = A.vg;
-    for (int k = lane; k < vg.nu; k += kLpp) {
+    const double ist = p.ist, wscale = ist * ist * ist;
+    for (int k = lane; k < vg.nu; k += 64) {
         const int i = k % vg.nv[0], j = (k / vg.nv[0]) % vg.nv[1], l = k / (vg.nv[0] * vg.nv[1]);
-        const double c0 = (gridu(vg, 0, i) - U[0]) * ist;
-        const double c1 = (gridu(vg, 1, j) - U[1]) * ist;
-        const double c2 = (gridu(vg, 2, l) - U[2]) * ist;
-        const double q = Am[0][0] * c0 * c0 + Am[1][1] * c1 * c1 + Am[2][2] * c2 * c2 +
-                         2.0 * (Am[0][1] * c0 * c1 + Am[0][2] * c0 * c2 + Am[1][2] * c1 * c2);
+        const double c0 = (gridu(vg, 0, i) - p.U[0]) * ist;
+        const double c1 = (gridu(vg, 1, j) - p.U[1]) * ist;
+        const double c2 = (gridu(vg, 2, l) - p.U[2]) * ist;
+        const double q = p.A[0] * c0 * c0 + p.A[1] * c1 * c1 + p.A[2] * c2 * c2 +
+                         2.0 * (p.A[3] * c0 * c1 + p.A[4] * c0 * c2 + p.A[5] * c1 * c2);
         const double w = A.wax[i] * A.wax[64 + j] * A.wax[128 + l] * wscale;
-        const double ev = w * exp(z[0] + z[1] * c0 + z[2] * c1 + z[3] * c2 - 0.5 * z[4] * q);
+        const double ev = w * exp(p.z[0] + p.z[1] * c0 + p.z[2] * c1 + p.z[3] * c2 - 0.5 * p.z[4] * q);
         const double cc = c0 * c0 + c1 * c1 + c2 * c2;
         acc[0] += ev;
         acc[1] += ev * c0; acc[2] += ev * c1; acc[3] += ev * c2;
-        if (!jac) {
+        if (!JAC) {
             acc[4] += ev * cc;
             continue;
         }
@@ -278,69 +316,31 @@ __device__ void sums_es(const NewtonArgs &A, int lane, const double U[3], double
         acc[14] += ec * c0; acc[15] += ec * c1; acc[16] += ec * c2;
         acc[17] += ec * q;
     }
-    s.S0 = wave_sum(acc[0]);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) s.Sc[d] = wave_sum(acc[1 + d]);
-    if (!jac) {
-        s.Scc[0] = wave_sum(acc[4]);
-        s.Scc[1] = s.Scc[2] = 0.0;
-        return;
-    }
-#pragma unroll
-    for (int a = 0; a < 6; ++a) s.Scc[a] = wave_sum(acc[4 + a]);
-    s.Sq = wave_sum(acc[10]);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) s.Scq[d] = wave_sum(acc[11 + d]);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) s.Sc2c[d] = wave_sum(acc[14 + d]);
-    s.Sc2q = wave_sum(acc[17]);
+    store_sums<JAC ? 18 : 5>(acc, lane, out);
+    if (!JAC && lane == 0) out[5] = out[6] = 0.0;
 }
 
-// ---- factorised ES sums -------------------------------------------------
-// On a tensor grid the exponent z0 + z.c - z4 c^T A c / 2 splits into the
-// one-axis factors X(i), Y(j), Z(l) and the cross factors exp(k01 c0 c1),
-// exp(k02 c0 c2), exp(k12 c1 c2) (k_ab = -z4 A_ab).  The first cross factor
-// is tabulated, P(i,j).  The product of the other two,
-// G(i,j,l) = exp((k02 c0_i + k12 c1_j) c2_l), is geometric in l on a uniform
-// grid with start G0(i) H0(j) and ratio Ra(i) Rb(j), so it is generated along
-// l and needs no table: 3n + 3n + n + 2n exponentials per evaluation.  The
-// sums follow from T_e(i,j) = sum_l Z c2^e G and the pair sums, reduced over
-// the lanes of the point.
+// ---- factorised sums ----
+// On a tensor grid the exponent z0 + z.c - z4 c^T A c / 2 splits into one-axis
+// factors and the cross factors exp(k01 c0 c1), exp(k02 c0 c2), exp(k12 c1 c2)
+// (k_ab = -z4 A_ab).  Each lane keeps one x node (row) i and walks every
+// nph-th y node j (nph = 64 / n0 lanes share a row).  Along l the two factors
+// with c2 are geometric on a uniform grid, with ratio Ra(i) Rb(j), so
+//   T_e(i,j) = sum_l Z(l) c2_l^e (Ra Rb)^l
+// are polynomials in the ratio: one multiply-add per (pair, node, e) by
+// Horner's rule on the table Z c2^e, shared by the pairs a lane works on
+// together.  Along j the factor of c0 c1 is geometric too (no table), and the
+// T_e are collected with powers of c1 into the row's sums over j of c1^b c2^e,
+// b + e <= 4 (15; residual: b + e <= 2, 6), from which the lane's c0 gives its
+// share of the 18 (5) sums once per evaluation.  What this bounds: FP64
+// multiply-adds, 5 (3) n0 n1 n2 / 64 of them per lane; a pair-by-pair finish
+// with two-axis tables cost as much again, and its tables (5.6 KB per point
+// at 20^3, now 1.6) held the occupancy.
 
-// Layout of one point's table region (doubles); rows of P are padded to an
-// odd length to spread LDS banks.
-struct FactLayout {
-    int n0, n1, n2, ld1;  // ld1 = row length of P (over j)
-    int c0, c1, c2, X, Y, Zc, P, G0, Ra, H0, Rb, total;
-};
-
-__host__ __device__ inline FactLayout fact_layout(const VGrid &vg) {
-    FactLayout L;
-    L.n0 = vg.nv[0];
-    L.n1 = vg.nv[1];
-    L.n2 = vg.nv[2];
-    L.ld1 = L.n1 | 1;
-    int o = 0;
-    L.c0 = o; o += L.n0;
-    L.c1 = o; o += L.n1;
-    L.c2 = o; o += L.n2;
-    L.X = o; o += L.n0;
-    L.Y = o; o += L.n1;
-    L.Zc = o; o += 5 * L.n2;
-    L.P = o; o += L.n0 * L.ld1;
-    L.G0 = o; o += L.n0;
-    L.Ra = o; o += L.n0;
-    L.H0 = o; o += L.n1;
-    L.Rb = o; o += L.n1;
-    L.total = o;
-    return L;
-}
-
-__device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-    for (int o = kLpp / 2; o >= 1; o >>= 1) v = fmax(v, __shfl_xor(v, o, kLpp));
-    return v;
-}
+// Doubles of one wave's tables: per y node factor with weight, Rb, c1 (padded
+// with zero weights to the same number of nodes for every lane); Z c2^e.
+__host__ __device__ inline int es_rows(const VGrid &vg, int nph) { return (vg.nv[1] + nph - 1) / nph * nph; }
+__host__ __device__ inline int es_table_doubles(const VGrid &vg, int nph) { return 3 * es_rows(vg, nph) + 5 * vg.nv[2]; }
 
 __device__ __forceinline__ void lds_wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -348,183 +348,149 @@ __device__ __forceinline__ void lds_wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Quadratic-form entries a pair finish needs: A00, A11, A22, 2A01, 2A02, 2A12.
-struct QuadA {
-    double a00, a11, a22, t01, t02, t12;
-};
+// Index of the row sum of c1^b c2^e: for e = 0..D, b = 0..D-e.
+template <int D>
+__device__ __forceinline__ constexpr int row_sum(int b, int e) {
+    int o = 0;
+    for (int x = 0; x < e; ++x) o += D + 1 - x;
+    return o + b;
+}
 
-// B pairs p0 + kLpp b (all < n0 n1) of one lane: T_e = sum_l Z c2^e G for
-// e < NE (5 for the full sums, 3 for the residual sums), then the pairs'
-// contributions to the 18 (5) sums.  Returns the largest |exponent| of G
-// over the pairs (G is exact at both ends of l, hence everywhere between).
-template <int B, int NE>
-__device__ __forceinline__ double pair_block(const FactLayout &L, const double *tb, int p0, double k02, double k12,
-                                             const QuadA &q, double acc[18]) {
-    constexpr bool JAC = NE == 5;
-    double g[B], gr[B], T[B][NE];
-    int ii[B], jj[B];
-    double gmax = 0.0;
-    const double c2a = tb[L.c2], c2b = tb[L.c2 + L.n2 - 1];
+// B y nodes j0, j0 + nph, ... of a lane's row.  W: the row's factor at j0
+// (times Pr per node); D: degree of the sums (4 or 2).
+template <int B, int D>
+__device__ __forceinline__ void row_block(const double *tb, int np, int n2, int j0, int nph, double Ra, double Pr,
+                                          double &W, double *M) {
+    const double *yj = tb + j0, *zc = tb + 3 * np;
+    double r[B], T[B][D + 1];
 #pragma unroll
     for (int b = 0; b < B; ++b) {
-        const unsigned p = (unsigned)(p0 + kLpp * b);  // non-negative: unsigned division is shorter
-        ii[b] = (int)(p % (unsigned)L.n0);
-        jj[b] = (int)(p / (unsigned)L.n0);
-        const double kap = k02 * tb[L.c0 + ii[b]] + k12 * tb[L.c1 + jj[b]];
-        gmax = fmax(gmax, fmax(fabs(kap * c2a), fabs(kap * c2b)));
-        g[b] = tb[L.G0 + ii[b]] * tb[L.H0 + jj[b]];
-        gr[b] = tb[L.Ra + ii[b]] * tb[L.Rb + jj[b]];
+        r[b] = Ra * yj[np + b * nph];
 #pragma unroll
-        for (int e = 0; e < NE; ++e) T[b][e] = 0.0;
+        for (int e = 0; e <= D; ++e) T[b][e] = 0.0;
     }
-    for (int l = 0; l < L.n2; ++l) {
-        const double *zc = tb + L.Zc + 5 * l;
-        double zl[NE];
+#pragma unroll 2
+    for (int l = n2 - 1; l >= 0; --l) {
 #pragma unroll
-        for (int e = 0; e < NE; ++e) zl[e] = zc[e];
+        for (int e = 0; e <= D; ++e) {
+            const double z = zc[5 * l + e];
 #pragma unroll
-        for (int b = 0; b < B; ++b) {
-#pragma unroll
-            for (int e = 0; e < NE; ++e) T[b][e] = fma(zl[e], g[b], T[b][e]);
-            g[b] *= gr[b];
+            for (int b = 0; b < B; ++b) T[b][e] = fma(T[b][e], r[b], z);
         }
     }
 #pragma unroll
     for (int b = 0; b < B; ++b) {
-        const int i = ii[b], j = jj[b];
-        const double T0 = T[b][0], T1 = T[b][1], T2 = T[b][2];
-        const double c0 = tb[L.c0 + i], c1 = tb[L.c1 + j];
-        const double bb = tb[L.X + i] * tb[L.Y + j] * tb[L.P + i * L.ld1 + j];
-        const double r2 = c0 * c0 + c1 * c1;
-        acc[0] += bb * T0;
-        acc[1] += bb * c0 * T0; acc[2] += bb * c1 * T0; acc[3] += bb * T1;
-        if constexpr (!JAC) {
-            acc[4] += bb * (r2 * T0 + T2);
-        } else {
-            const double T3 = T[b][NE > 3 ? 3 : 0], T4 = T[b][NE > 4 ? 4 : 0];
-            const double qa = c0 * (q.a00 * c0 + q.t01 * c1) + q.a11 * c1 * c1, qb = q.t02 * c0 + q.t12 * c1;
-            const double q0 = qa * T0 + qb * T1 + q.a22 * T2;    // sum q
-            const double q1 = qa * T1 + qb * T2 + q.a22 * T3;    // sum c2 q
-            const double q2 = qa * T2 + qb * T3 + q.a22 * T4;    // sum c2^2 q
-            const double s2 = r2 * T0 + T2;                      // sum |c|^2
-            acc[4] += bb * c0 * c0 * T0; acc[5] += bb * c1 * c1 * T0; acc[6] += bb * T2;
-            acc[7] += bb * c0 * c1 * T0; acc[8] += bb * c0 * T1; acc[9] += bb * c1 * T1;
-            acc[10] += bb * q0;
-            acc[11] += bb * c0 * q0; acc[12] += bb * c1 * q0; acc[13] += bb * q1;
-            acc[14] += bb * c0 * s2; acc[15] += bb * c1 * s2; acc[16] += bb * (r2 * T1 + T3);
-            acc[17] += bb * (r2 * q0 + q2);
-        }
-    }
-    return gmax;
-}
-
-// All n0 n1 pairs of the point: full passes of four pairs per lane, then the
-// remainder one pair per lane.
-template <int NE>
-__device__ __forceinline__ double pair_sums(const FactLayout &L, const double *tb, int lane, double k02, double k12,
-                                            const QuadA &q, double acc[18]) {
-    const int nP = L.n0 * L.n1;
-    const int full = nP / (2 * kLpp) * (2 * kLpp);
-    double gmax = 0.0;
-    for (int p0 = lane; p0 < full; p0 += 2 * kLpp) gmax = fmax(gmax, pair_block<2, NE>(L, tb, p0, k02, k12, q, acc));
-    for (int p0 = full + lane; p0 < nP; p0 += kLpp) gmax = fmax(gmax, pair_block<1, NE>(L, tb, p0, k02, k12, q, acc));
-    return gmax;
-}
-
-// Returns false (and leaves s untouched) when a factor exponent exceeds the
-// safe range; the caller then uses the direct sum.  jac as for sums_es.
-__device__ bool sums_es_fact(const NewtonArgs &A, int lane, double *tb, const double U[3], double ist,
-                             const double Am[3][3], const double z[5], Sums &s, bool jac) {
-    // per-evaluation values: nothing derived from the lane or the frame is
-    // hoisted out of the caller's Newton loop (it would stay live across it)
-    asm volatile("" : "+v"(lane), "+v"(ist));
-    const VGrid &vg = A.vg;
-    const FactLayout L = fact_layout(vg);
-    const double hz = 0.5 * z[4];
-    const double k01 = -z[4] * Am[0][1], k02 = -z[4] * Am[0][2], k12 = -z[4] * Am[1][2];
-    // c2 at the first node and the c2 spacing (the G recurrence runs along l)
-    const double c2a = (gridu(vg, 2, 0) - U[2]) * ist, dl2 = vg.du[2] * ist;
-    // largest exponent of a direct factor (X, Y, Z, P: an underflow there is
-    // a true underflow) and largest |exponent| of a G factor (its start and
-    // ratio tables must neither overflow nor underflow)
-    double amax = -1e300;
-    lds_wave_sync();  // previous evaluation's readers are done with the tables
-    // one-axis tables, axis by axis (an axis index varying across lanes would
-    // put the small per-point arrays U, z, Am into scratch memory)
+        const double w = W * yj[b * nph], c1 = yj[2 * np + b * nph];
+        W *= Pr;
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const int nd = d == 0 ? L.n0 : (d == 1 ? L.n1 : L.n2);
-        const int oc = d == 0 ? L.c0 : (d == 1 ? L.c1 : L.c2);
-        for (int i = lane; i < nd; i += kLpp) {
-            const double c = (gridu(vg, d, i) - U[d]) * ist;
-            double arg = c * (z[1 + d] - hz * Am[d][d] * c);
-            if (d == 0) arg += z[0];
-            amax = fmax(amax, arg);
-            const double v = A.wax[64 * d + i] * ist * exp(arg);
-            tb[oc + i] = c;
-            if (d == 0) {
-                tb[L.X + i] = v;
-                const double g0 = k02 * c * c2a, gr = k02 * c * dl2;
-                amax = fmax(amax, fmax(fabs(g0), fabs(gr)));
-                tb[L.G0 + i] = exp(g0);
-                tb[L.Ra + i] = exp(gr);
-            } else if (d == 1) {
-                tb[L.Y + i] = v;
-                const double h0 = k12 * c * c2a, hr = k12 * c * dl2;
-                amax = fmax(amax, fmax(fabs(h0), fabs(hr)));
-                tb[L.H0 + i] = exp(h0);
-                tb[L.Rb + i] = exp(hr);
-            } else {
-                double p = v;
+        for (int e = 0; e <= D; ++e) {
+            double t = w * T[b][e];
 #pragma unroll
-                for (int e = 0; e < 5; ++e) { tb[L.Zc + 5 * i + e] = p; p *= c; }
+            for (int x = 0; x <= D - e; ++x) {
+                M[row_sum<D>(x, e)] += t;
+                if (x < D - e) t *= c1;
             }
         }
     }
-    lds_wave_sync();
-    // P(i,j) = exp(k01 c0_i c1_j): along a row the exponent is affine in j,
-    // so one lane fills a row by a geometric recurrence from its larger end
-    // (2 exponentials per row; values only shrink along the recurrence, so an
-    // underflow is a true underflow).
-    for (int i = lane; i < L.n0; i += kLpp) {
-        const double kc = k01 * tb[L.c0 + i];
-        const int nb = L.n1;
-        double *dst = tb + L.P + i * L.ld1;
-        const double a0 = kc * tb[L.c1], a1 = kc * tb[L.c1 + nb - 1];
-        amax = fmax(amax, fmax(a0, a1));
-        const double step = nb > 1 ? fabs(a1 - a0) / (nb - 1) : 0.0;
-        const double ratio = exp(-step);
-        const bool up = a1 > a0;  // the larger end is the last node
-        double v = exp(up ? a1 : a0);
-        for (int m = 0; m < nb; ++m) {
-            dst[up ? nb - 1 - m : m] = v;
-            v *= ratio;
+}
+
+template <bool JAC>
+__device__ __forceinline__ void sums_es_fact(const NewtonArgs &A, int lane, double *tb, const EsPoint &p, double *out) {
+    constexpr int D = JAC ? 4 : 2, NM = (D + 1) * (D + 2) / 2;
+    // nothing derived from the lane is kept in registers between evaluations
+    asm volatile("" : "+v"(lane));
+    const VGrid &vg = A.vg;
+    const int n0 = vg.nv[0], n1 = vg.nv[1], n2 = vg.nv[2], nph = A.nph;
+    const double ist = p.ist, z4 = p.z[4], hz = 0.5 * z4;
+    const double k01 = -z4 * p.A[3], k02 = -z4 * p.A[4], k12 = -z4 * p.A[5];
+    const double c2a = (gridu(vg, 2, 0) - p.U[2]) * ist, dl2 = vg.du[2] * ist, dl1 = vg.du[1] * ist;
+    lds_wave_sync();  // previous evaluation's readers are done with the tables
+    // the y and z tables: one exponential per entry, the entries of all three
+    // tables dealt to the lanes together
+    const int np = es_rows(vg, nph);
+    for (int t = lane; t < np - n1; t += 64) tb[n1 + t] = tb[np + n1 + t] = tb[2 * np + n1 + t] = 0.0;
+    for (int t = lane; t < 2 * n1 + n2; t += 64) {
+        const bool isz = t >= 2 * n1, isr = !isz && t >= n1;
+        const int i = isz ? t - 2 * n1 : (isr ? t - n1 : t);
+        const double c = isz ? (gridu(vg, 2, i) - p.U[2]) * ist : (gridu(vg, 1, i) - p.U[1]) * ist;
+        const double own = isz ? c * (p.z[3] - hz * p.A[2] * c) : c * (p.z[2] - hz * p.A[1] * c) + k12 * c * c2a;
+        const double v = exp(isr ? k12 * c * dl2 : own);
+        if (isz) {
+            double q = A.wax[128 + i] * ist * v;
+#pragma unroll
+            for (int e = 0; e <= D; ++e) {
+                tb[3 * np + 5 * i + e] = q;
+                q *= c;
+            }
+        } else if (isr) {
+            tb[np + i] = v;
+        } else {
+            tb[i] = A.wax[64 + i] * ist * v;
+            tb[2 * np + i] = c;
         }
     }
+    // the lane's row: x node i, y nodes ph, ph + nph, ...
+    const int ph = lane / n0, i = lane - ph * n0;
+    const bool live = ph < nph;  // (other lanes follow along with weight zero)
+    const int j0 = live ? ph : 0;
+    const double c0 = (gridu(vg, 0, i) - p.U[0]) * ist;
+    const double c1p = (gridu(vg, 1, j0) - p.U[1]) * ist;
+    const double Ra = exp(k02 * c0 * dl2), Pr = exp(k01 * c0 * dl1 * nph);
+    double W = A.wax[i] * ist * exp(p.z[0] + c0 * (p.z[1] - hz * p.A[0] * c0) + k02 * c0 * c2a + k01 * c0 * c1p);
+    W = live ? W : 0.0;
+    double M[NM];
+#pragma unroll
+    for (int a = 0; a < NM; ++a) M[a] = 0.0;
     lds_wave_sync();
-    const QuadA q = {Am[0][0], Am[1][1], Am[2][2], 2.0 * Am[0][1], 2.0 * Am[0][2], 2.0 * Am[1][2]};
-    double acc[18];
-#pragma unroll
-    for (int a = 0; a < 18; ++a) acc[a] = 0.0;
-    const double gmax = jac ? pair_sums<5>(L, tb, lane, k02, k12, q, acc) : pair_sums<3>(L, tb, lane, k02, k12, q, acc);
-    if (wave_max(fmax(amax, gmax)) > 600.0) return false;
-    s.S0 = wave_sum(acc[0]);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) s.Sc[d] = wave_sum(acc[1 + d]);
-    if (!jac) {
-        s.Scc[0] = wave_sum(acc[4]);
-        s.Scc[1] = s.Scc[2] = 0.0;
-        return true;
+    const int cnt = np / nph;
+    int m = 0;
+    for (; m + 4 <= cnt; m += 4) row_block<4, D>(tb, np, n2, j0 + nph * m, nph, Ra, Pr, W, M);
+    if (cnt - m == 3) row_block<3, D>(tb, np, n2, j0 + nph * m, nph, Ra, Pr, W, M);
+    else if (cnt - m == 2) row_block<2, D>(tb, np, n2, j0 + nph * m, nph, Ra, Pr, W, M);
+    else if (cnt - m == 1) row_block<1, D>(tb, np, n2, j0 + nph * m, nph, Ra, Pr, W, M);
+    auto m_ = [&](int b, int e) { return M[row_sum<D>(b, e)]; };
+    const double cc = c0 * c0;
+    if constexpr (!JAC) {
+        const double v[5] = {m_(0, 0), c0 * m_(0, 0), m_(1, 0), m_(0, 1), fma(cc, m_(0, 0), m_(2, 0) + m_(0, 2))};
+        store_sums<5>(v, lane, out);
+        if (lane == 0) out[5] = out[6] = 0.0;
+    } else {
+        const double a00 = p.A[0] * cc, t01 = 2.0 * p.A[3] * c0, t02 = 2.0 * p.A[4] * c0, t12 = 2.0 * p.A[5];
+        // sum of q c1^b c2^e, and of |c|^2 c1^b c2^e
+        auto q_ = [&](int b, int e) {
+            double t = a00 * m_(b, e);
+            t = fma(t01, m_(b + 1, e), t);
+            t = fma(p.A[1], m_(b + 2, e), t);
+            t = fma(t02, m_(b, e + 1), t);
+            t = fma(t12, m_(b + 1, e + 1), t);
+            return fma(p.A[2], m_(b, e + 2), t);
+        };
+        auto s_ = [&](int b, int e) { return fma(cc, m_(b, e), m_(b + 2, e) + m_(b, e + 2)); };
+        const double q0 = q_(0, 0);
+        const double v[18] = {m_(0, 0), c0 * m_(0, 0), m_(1, 0), m_(0, 1),                                 // S0, Sc
+                              cc * m_(0, 0), m_(2, 0), m_(0, 2), c0 * m_(1, 0), c0 * m_(0, 1), m_(1, 1),   // Scc
+                              q0, c0 * q0, q_(1, 0), q_(0, 1),                                             // Sq, Scq
+                              c0 * s_(0, 0), s_(1, 0), s_(0, 1), fma(cc, q0, q_(2, 0) + q_(0, 2))};        // Sc2c, Sc2q
+        store_sums<18>(v, lane, out);
     }
+}
+
+// Whether the factors of an evaluation stay well inside the FP64 range: the
+// largest |exponents| of the cross factors over the grid (their sum bounds
+// the lanes' start values, twice it the range of a geometric factor) and the
+// peaks of the one-axis factors.
+__device__ __forceinline__ bool factors_in_range(const NewtonArgs &A, const EsPoint &p) {
+    const VGrid &vg = A.vg;
+    double cm[3];
 #pragma unroll
-    for (int a = 0; a < 6; ++a) s.Scc[a] = wave_sum(acc[4 + a]);
-    s.Sq = wave_sum(acc[10]);
+    for (int d = 0; d < 3; ++d)
+        cm[d] = fmax(fabs(gridu(vg, d, 0) - p.U[d]), fabs(gridu(vg, d, vg.nv[d] - 1) - p.U[d])) * p.ist;
+    const double z4 = p.z[4];
+    const double cross = z4 * (fabs(p.A[3]) * cm[0] * cm[1] + fabs(p.A[4]) * cm[0] * cm[2] + fabs(p.A[5]) * cm[1] * cm[2]);
+    double peak = fabs(p.z[0]);
 #pragma unroll
-    for (int d = 0; d < 3; ++d) s.Scq[d] = wave_sum(acc[11 + d]);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) s.Sc2c[d] = wave_sum(acc[14 + d]);
-    s.Sc2q = wave_sum(acc[17]);
-    return true;
+    for (int d = 0; d < 3; ++d) peak = fmax(peak, p.z[1 + d] * p.z[1 + d] / (2.0 * z4 * p.A[d]));
+    return cross <= 300.0 && peak <= 25.0;  // (false for NaN)
 }
 
 // Smallest eigenvalue of a symmetric 3x3 matrix (closed form, trigonometric).
@@ -804,35 +770,51 @@ __device__ int newton_solve(const NewtonArgs &A, SumsFn sums, int64_t pt, const 
     return conv;
 }
 
-// The same iteration as newton_solve, written as one loop around a single
-// evaluation of the sums: the two points of a wave evaluate together in
-// whatever phase each is (start, cold start, line-search trial, Jacobian
-// refresh), and the sums code is emitted once.  The sums at the current
-// Jacobian (s) and at the point under evaluation (st) are held by the
-// caller, in LDS, and so is the iteration's state: the start zc, the iterate
-// z, the point under evaluation ze, its residual r and the step dz (the
-// sums need most of the register file).
-template <typename SumsFn>
-__device__ int newton_solve_es(const NewtonArgs &A, SumsFn sums, int64_t pt, const double *zc, double *z,
-                               double *ze, double *r, double *dz, Sums &s, Sums &st, double &res, int &iters,
-                               int &evals) {
-    enum { kStart, kCold, kTrial, kRefresh };
-    double za[5];
-    const bool have_alt = A.guess != FR_DVM_GUESS_COLD && alt_start(A, pt, zc, za);
-#pragma unroll
-    for (int a = 0; a < 5; ++a) z[a] = have_alt ? za[a] : zc[a];
-#pragma unroll
-    for (int a = 0; a < 5; ++a) { ze[a] = z[a]; r[a] = 0.0; dz[a] = 0.0; }
-    int phase = kStart, it = 0, hh = 0, conv = 0;
-    bool jac = true, chord = false;
-    double alpha = 1.0, rn = 0.0, ri = 0.0;
-    evals = 0;
-    for (;;) {
-        Sums &tg = (phase == kStart || phase == kRefresh) ? s : st;
-        sums(ze, tg, jac);
+// The iteration of newton_solve for one point, written as a state machine
+// that is advanced after every evaluation of the sums: advance() takes the
+// sums the last request asked for and makes the next request, or ends.
+// Every point's iteration is the same as newton_solve's.  It lives in LDS:
+// the sums need the registers of every wave.
+struct EsIter {
+    enum Phase { kStart, kCold, kTrial, kRefresh };
+    double z[5], r[5], dz[5], zc0;
+    double alpha, rn, ri, res;
+    double rho, th, inv_tau;  // of the point, for its record
+    int phase, it, hh, conv, evals, cur;  // cur: the set of sums of the current Jacobian
+    int status, chord, have_alt;
+
+    __device__ __forceinline__ void request(const NewtonArgs &A, EsPoint &p, bool jac, int tgt) {
+        p.tgt = tgt;
+        p.req = kReqSums | (jac ? kReqJac : 0) | (A.use_fact && factors_in_range(A, p) ? 0 : kReqDirect);
         ++evals;
+    }
+    __device__ __forceinline__ void point(EsPoint &p, double al) const {
+#pragma unroll
+        for (int a = 0; a < 5; ++a) p.z[a] = z[a] + al * dz[a];
+    }
+    __device__ void start(const NewtonArgs &A, int64_t pt, EsPoint &p, double zc0_) {
+        zc0 = zc0_;
+        const double zc[5] = {zc0, 0.0, 0.0, 0.0, 1.0};
+        double za[5];
+        have_alt = A.guess != FR_DVM_GUESS_COLD && alt_start(A, pt, zc, za);
+#pragma unroll
+        for (int a = 0; a < 5; ++a) {
+            z[a] = have_alt ? za[a] : zc[a];
+            r[a] = dz[a] = 0.0;
+        }
+        alpha = 1.0;
+        rn = ri = res = 0.0;
+        phase = kStart;
+        it = hh = conv = evals = cur = 0;
+        chord = false;
+        point(p, 0.0);
+        request(A, p, true, 0);
+    }
+    // Returns false when the iteration has ended (p.req cleared).
+    __device__ bool advance(const NewtonArgs &A, EsPoint &p) {
+        p.req = 0;
         double re[5];
-        residual(tg, re);
+        residual(p.s[p.tgt], re);
         if (phase == kStart) {
 #pragma unroll
             for (int a = 0; a < 5; ++a) r[a] = re[a];
@@ -840,28 +822,30 @@ __device__ int newton_solve_es(const NewtonArgs &A, SumsFn sums, int64_t pt, con
                 // the alternative start is not already close: evaluate the
                 // cold start too and keep the better one
                 phase = kCold;
-#pragma unroll
-                for (int a = 0; a < 5; ++a) ze[a] = zc[a];
-                continue;
+                p.z[0] = zc0;
+                p.z[1] = p.z[2] = p.z[3] = 0.0;
+                p.z[4] = 1.0;
+                request(A, p, true, cur ^ 1);
+                return true;
             }
         } else if (phase == kCold) {
             if (!(norm2_5(r) <= norm2_5(re))) {
-                s = st;
+                cur = p.tgt;
 #pragma unroll
-                for (int a = 0; a < 5; ++a) { z[a] = zc[a]; r[a] = re[a]; }
+                for (int a = 0; a < 5; ++a) { z[a] = p.z[a]; r[a] = re[a]; }
             }
         } else if (phase == kTrial) {
             const double rt = norm2_5(re);
             if (rt < (1.0 - 1e-4 * alpha) * rn) {
 #pragma unroll
-                for (int a = 0; a < 5; ++a) { z[a] = ze[a]; r[a] = re[a]; }
+                for (int a = 0; a < 5; ++a) { z[a] = p.z[a]; r[a] = re[a]; }
                 if (!chord) {
-                    s = st;
+                    cur = p.tgt;
                 } else if (rt > 1e-2 * rn) {
-                    // slow chord contraction: refresh the Jacobian at z (= ze)
+                    // slow chord contraction: refresh the Jacobian at z
                     phase = kRefresh;
-                    jac = true;
-                    continue;
+                    request(A, p, true, cur);
+                    return true;
                 }
                 ++it;
             } else {
@@ -869,26 +853,28 @@ __device__ int newton_solve_es(const NewtonArgs &A, SumsFn sums, int64_t pt, con
                 do {
                     alpha *= 0.5;
                     ++hh;
-#pragma unroll
-                    for (int a = 0; a < 5; ++a) ze[a] = z[a] + alpha * dz[a];
-                } while (hh < kRejectBudget && !(ze[4] > 0.0));
-                if (hh < kRejectBudget) continue;
+                    point(p, alpha);
+                } while (hh < kRejectBudget && !(p.z[4] > 0.0));
+                if (hh < kRejectBudget) {
+                    request(A, p, !chord, cur ^ 1);
+                    return true;
+                }
                 // stagnation at the rounding floor of the FP64 sums
                 if (ri <= 100.0 * A.tol) { res = ri; conv = 1; ++it; }
-                break;
+                return false;
             }
         } else {  // kRefresh
 #pragma unroll
             for (int a = 0; a < 5; ++a) r[a] = re[a];
             ++it;
         }
-        // Newton step from z with the Jacobian of s
-        if (it >= A.max_iter) break;
+        // Newton step from z with the Jacobian of the current sums
+        if (it >= A.max_iter) return false;
         rn = norm2_5(r);
         ri = normi_5(r);
         double J[5][5], rdum[5];
-        double rhs[5] = {-r[0], -r[1], -r[2], -r[3], -r[4]};
-        assemble(s, rdum, J);
+        const double rhs[5] = {-r[0], -r[1], -r[2], -r[3], -r[4]};
+        assemble(p.s[cur], rdum, J);
         const bool ok = solve5(J, rhs, dz);
         if (ok && ri <= A.tol) {
             // converged: one extra step makes the result path independent
@@ -897,35 +883,34 @@ __device__ int newton_solve_es(const NewtonArgs &A, SumsFn sums, int64_t pt, con
             res = ri;
             conv = 1;
             ++it;
-            break;
+            return false;
         }
-        if (!ok) break;
+        if (!ok) return false;
         chord = rn <= kChord;
         alpha = 1.0;
         // hh counts the rejected trials of the whole solve (not reset here)
-#pragma unroll
-        for (int a = 0; a < 5; ++a) ze[a] = z[a] + alpha * dz[a];
-        while (hh < kRejectBudget && !(ze[4] > 0.0)) {
+        point(p, alpha);
+        while (hh < kRejectBudget && !(p.z[4] > 0.0)) {
             alpha *= 0.5;
             ++hh;
-#pragma unroll
-            for (int a = 0; a < 5; ++a) ze[a] = z[a] + alpha * dz[a];
+            point(p, alpha);
         }
         if (hh >= kRejectBudget) {
             if (ri <= 100.0 * A.tol) { res = ri; conv = 1; ++it; }
-            break;
+            return false;
         }
         phase = kTrial;
-        jac = !chord;
+        request(A, p, !chord, cur ^ 1);
+        return true;
     }
-    iters = it;
-    if (!conv) {
+    __device__ __forceinline__ void finish() {
+        if (conv) return;
         res = normi_5(r);
-#pragma unroll
-        for (int a = 0; a < 5; ++a) z[a] = zc[a];
+        z[0] = zc0;
+        z[1] = z[2] = z[3] = 0.0;
+        z[4] = 1.0;
     }
-    return conv;
-}
+};
 
 constexpr int kBgkBlock = 64;
 // One solution point per LPP lanes; the iteration runs alike in all of them
@@ -966,99 +951,117 @@ __global__ __launch_bounds__(kBgkBlock) void k_newton_bgk(const NewtonArgs A) {
     record_stats(A, pt, iters, evals, conv ? FR_DVM_NEWTON_OK : FR_DVM_NEWTON_FALLBACK, res);
 }
 
+// ES Newton.  The sums over the velocity grid need a wave per point, the rest
+// of the iteration (moments to frame, 5 x 5 solves, step control, equilibrium
+// record) is scalar work per point that a wave would do 64 times over.  So a
+// workgroup takes A.es_pts points: in each round its waves evaluate the sums
+// that the points request, one point per wave after the other, and then one
+// thread per point (the first es_pts threads) advances the point's iteration
+// and makes its next request, until no point has one.  Every wave reaches
+// every barrier, and a point makes at most max_iter + kRejectBudget + 3
+// requests after its first (an accepted step, its refresh, a rejected trial).
+// Warm solves (two evaluations a point), 32 lanes per point running the whole
+// iteration and two-axis tables -> this form: 262,144 points of a 20^3 grid
+// 2.89 -> 1.66 ms, 62,208 of 24^3 1.19 -> 0.75, 51,200 of 24^3 0.97 -> 0.58;
+// the multiply-adds of the sums alone are 0.5 ms of the first.  Register
+// targets of 2 and 4 waves per SIMD: 1.97 and 1.71 ms.
 #ifndef FRDVM_WAVES_ES
 #define FRDVM_WAVES_ES 3
 #endif
-// One solution point per kLpp lanes: two per wave, four per 128-thread
-// workgroup (about 6 KB of LDS per point at 20^3 velocities, so LDS admits
-// six workgroups per CU and registers decide the occupancy).
-constexpr int kEsBlock = 128;
-constexpr int kEsPts = kEsBlock / kLpp;
-constexpr int kSumsD = (int)(sizeof(Sums) / sizeof(double));
-constexpr int kStateD = 38;  // U[3], A[3][3], zc, z, ze, r, dz [5] each, pad
-
-// LDS doubles per point of k_newton_es: two sum sets, the iteration state,
-// then the factor tables.
-__host__ __device__ inline int es_slot_doubles(const VGrid &vg, int use_fact) {
-    return 2 * kSumsD + kStateD + (use_fact ? fact_layout(vg).total : 0);
-}
+constexpr int kEsBlock = 256;
+constexpr int kEsPointD = (int)((sizeof(EsPoint) + sizeof(EsIter)) / sizeof(double));
+static_assert(sizeof(EsPoint) % 8 == 0 && sizeof(EsIter) % 8 == 0, "LDS records of whole doubles");
+constexpr int kEsMaxPts = 64;  // points of a workgroup: at most one per lane of its first wave
 
 __global__ __launch_bounds__(kEsBlock) __attribute__((amdgpu_waves_per_eu(FRDVM_WAVES_ES))) void k_newton_es(
     const NewtonArgs A) {
-    const int lane = threadIdx.x % kLpp;
-    const int slot = threadIdx.x / kLpp;
-    const int64_t pt = (int64_t)blockIdx.x * kEsPts + slot;
-    if (pt >= A.npts) return;  // a point's lanes exit together
-    const double *Q = A.Q + pt * A.nmom;
-    const double rho = Q[0];
-    const double irho = 1.0 / rho;
-    double U[3] = {Q[1] * irho, Q[2] * irho, Q[3] * irho};
-    // raw second moments -> pressure tensor Pi = M2 - rho U U^T
-    const double Pi[6] = {Q[4] - rho * U[0] * U[0], Q[5] - rho * U[1] * U[1], Q[6] - rho * U[2] * U[2],
-                          Q[7] - rho * U[0] * U[1], Q[8] - rho * U[0] * U[2], Q[9] - rho * U[1] * U[2]};
-    // (3 + delta) rho theta = tr Pi + 2 (integral of G)
-    const double th = (Pi[0] + Pi[1] + Pi[2] + (A.nmom == 11 ? 2.0 * Q[10] : 0.0)) / ((3.0 + A.delta) * rho);
-    if (!(rho > 0.0) || !(th > 0.0) || !isfinite(rho) || !isfinite(th)) {
-        if (lane == 0) {
+    extern __shared__ double es_lds[];
+    const int npw = A.es_pts;  // <= kEsMaxPts
+    EsPoint *const P = reinterpret_cast<EsPoint *>(es_lds);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    double *const tb = es_lds + npw * kEsPointD + wave * es_table_doubles(A.vg, A.nph);
+    const int64_t p0 = (int64_t)blockIdx.x * npw;
+    const bool owner = (int)threadIdx.x < npw && p0 + threadIdx.x < A.npts;
+    const int64_t pt = p0 + threadIdx.x;
+    EsIter &I = reinterpret_cast<EsIter *>(P + npw)[threadIdx.x < npw ? threadIdx.x : 0];
+    bool active = false;
+    if ((int)threadIdx.x < npw) P[threadIdx.x].req = 0;
+    if (owner) {
+        EsPoint &p = P[threadIdx.x];
+        const double *Q = A.Q + pt * A.nmom;
+        const double rho = Q[0];
+        const double irho = 1.0 / rho;
+        const double U[3] = {Q[1] * irho, Q[2] * irho, Q[3] * irho};
+        // raw second moments -> pressure tensor Pi = M2 - rho U U^T
+        const double Pi[6] = {Q[4] - rho * U[0] * U[0], Q[5] - rho * U[1] * U[1], Q[6] - rho * U[2] * U[2],
+                              Q[7] - rho * U[0] * U[1], Q[8] - rho * U[0] * U[2], Q[9] - rho * U[1] * U[2]};
+        // (3 + delta) rho theta = tr Pi + 2 (integral of G)
+        const double th = (Pi[0] + Pi[1] + Pi[2] + (A.nmom == 11 ? 2.0 * Q[10] : 0.0)) / ((3.0 + A.delta) * rho);
+        if (!(rho > 0.0) || !(th > 0.0) || !isfinite(rho) || !isfinite(th)) {
             write_nonreal(A, pt);
             if (A.gfp) A.gfp[pt] = 0.0;
             record_stats(A, pt, 0, 0, FR_DVM_NEWTON_NONREAL, -1.0);
-        }
-        return;
-    }
-    if (A.gfp && lane == 0) A.gfp[pt] = 0.5 * A.delta * th;
-    const double Pr = A.Pr;
-    const double inv_tau = Pr * rho * th / viscosity(A, th);
-    const double ist = 1.0 / sqrt(th);
-    double Am[3][3] = {{1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
-    int status = FR_DVM_NEWTON_OK;
-    {
-        const double a1 = th / Pr, a2 = (1.0 - 1.0 / Pr) * irho;
-        const double T[3][3] = {{a1 + a2 * Pi[0], a2 * Pi[3], a2 * Pi[4]},
-                                {a2 * Pi[3], a1 + a2 * Pi[1], a2 * Pi[5]},
-                                {a2 * Pi[4], a2 * Pi[5], a1 + a2 * Pi[2]}};
-        if (sym3_min_eig(T) <= 1e-8 * th) {
-            status = FR_DVM_NEWTON_ESGUARD;
         } else {
-            double Ti[3][3];
-            inv3(T, Ti);
+            if (A.gfp) A.gfp[pt] = 0.5 * A.delta * th;
+            const double Pr = A.Pr;
+            I.rho = rho;
+            I.th = th;
+            I.inv_tau = Pr * rho * th / viscosity(A, th);
+            I.status = FR_DVM_NEWTON_OK;
+            double Am[3][3] = {{1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
+            const double a1 = th / Pr, a2 = (1.0 - 1.0 / Pr) * irho;
+            const double T[3][3] = {{a1 + a2 * Pi[0], a2 * Pi[3], a2 * Pi[4]},
+                                    {a2 * Pi[3], a1 + a2 * Pi[1], a2 * Pi[5]},
+                                    {a2 * Pi[4], a2 * Pi[5], a1 + a2 * Pi[2]}};
+            if (sym3_min_eig(T) <= 1e-8 * th) {
+                I.status = FR_DVM_NEWTON_ESGUARD;
+            } else {
+                double Ti[3][3];
+                inv3(T, Ti);
 #pragma unroll
-            for (int i = 0; i < 3; ++i)
+                for (int i = 0; i < 3; ++i)
 #pragma unroll
-                for (int j = 0; j < 3; ++j) Am[i][j] = th * Ti[i][j];
+                    for (int j = 0; j < 3; ++j) Am[i][j] = th * Ti[i][j];
+            }
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                p.U[d] = U[d];
+                p.A[d] = Am[d][d];
+            }
+            p.A[3] = Am[0][1];
+            p.A[4] = Am[0][2];
+            p.A[5] = Am[1][2];
+            p.ist = 1.0 / sqrt(th);
+            I.start(A, pt, p, -1.5 * log(kTwoPi) + 0.5 * log(det3(Am)));
+            active = true;
         }
     }
-    const double zc[5] = {-1.5 * log(kTwoPi) + 0.5 * log(det3(Am)), 0.0, 0.0, 0.0, 1.0};
-    double z[5];
-    const double wscale = ist * ist * ist;
-    // per point: the two sum sets of the iteration, the iteration state and
-    // the point's frame (U, A), then the factor tables
-    extern __shared__ double es_lds[];
-    double *sl = es_lds + slot * es_slot_doubles(A.vg, A.use_fact);
-    Sums &s_cur = *reinterpret_cast<Sums *>(sl);
-    Sums &s_try = *reinterpret_cast<Sums *>(sl + kSumsD);
-    double *ns = sl + 2 * kSumsD;
-    double *Us = ns, *zcs = ns + 12, *zs = ns + 17, *zes = ns + 22, *rs = ns + 27, *dzs = ns + 32;
-    double(*Ams)[3] = reinterpret_cast<double(*)[3]>(ns + 3);
-    double *tb = ns + kStateD;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        Us[d] = U[d];
-#pragma unroll
-        for (int b = 0; b < 3; ++b) Ams[d][b] = Am[d][b];
-    }
-#pragma unroll
-    for (int a = 0; a < 5; ++a) zcs[a] = zc[a];
-    auto fn = [&](const double *zz, Sums &s, bool jac) {
-        if (!(A.use_fact && sums_es_fact(A, lane, tb, Us, ist, Ams, zz, s, jac)))
-            sums_es(A, lane, Us, ist, wscale, Ams, zz, s, jac);
-    };
-    double res;
-    int iters, evals;
-    const int conv = newton_solve_es(A, fn, pt, zcs, zs, zes, rs, dzs, s_cur, s_try, res, iters, evals);
-    if (lane == 0) {
-        write_point(A, pt, rho, Us, th, Ams, zs, inv_tau, res);
-        record_stats(A, pt, iters, evals, conv ? status : FR_DVM_NEWTON_FALLBACK, res);
+    while (__syncthreads_or(active)) {
+        for (int s = wave; s < npw; s += kEsBlock / 64) {
+            EsPoint &p = P[s];
+            const int req = __builtin_amdgcn_readfirstlane(p.req);
+            if (!req) continue;
+            double *out = reinterpret_cast<double *>(&p.s[__builtin_amdgcn_readfirstlane(p.tgt)]);
+            if (req & kReqJac) {
+                if (req & kReqDirect) sums_es<true>(A, lane, p, out);
+                else sums_es_fact<true>(A, lane, tb, p, out);
+            } else {
+                if (req & kReqDirect) sums_es<false>(A, lane, p, out);
+                else sums_es_fact<false>(A, lane, tb, p, out);
+            }
+        }
+        __syncthreads();
+        if (active) {
+            EsPoint &p = P[threadIdx.x];
+            active = I.advance(A, p);
+            if (!active) {
+                I.finish();
+                const double Am[3][3] = {{p.A[0], p.A[3], p.A[4]}, {p.A[3], p.A[1], p.A[5]}, {p.A[4], p.A[5], p.A[2]}};
+                write_point(A, pt, I.rho, p.U, I.th, Am, I.z, I.inv_tau, I.res);
+                record_stats(A, pt, I.it, I.evals, I.conv ? I.status : FR_DVM_NEWTON_FALLBACK, I.res);
+            }
+        }
     }
 }
 
@@ -1362,6 +1365,18 @@ void launch_bgk(const NewtonArgs &A, int64_t all, hipStream_t s) {
     else launch_bgk_lanes<1>(A, s);
 }
 
+// Points per workgroup: 64 on large solves (a full wave of owner threads),
+// fewer where that would leave fewer than four workgroups per CU.
+void launch_es(const fr_dvm *h, NewtonArgs &A, hipStream_t s) {
+    A.use_fact = !h->es_direct;
+    A.nph = std::max(1, std::min(64 / A.vg.nv[0], A.vg.nv[1]));
+    int pts = kEsMaxPts;
+    while (pts > 4 && A.npts < (int64_t)pts * 1024) pts /= 2;
+    A.es_pts = pts;
+    const size_t shm = sizeof(double) * (size_t)(pts * kEsPointD + (kEsBlock / 64) * es_table_doubles(A.vg, A.nph));
+    hipLaunchKernelGGL(k_newton_es, dim3((unsigned)((A.npts + pts - 1) / pts)), dim3(kEsBlock), shm, s, A);
+}
+
 // The Newton kernel and its statistics over the points [p0, p0 + np) on
 // stream s: every per-point array of A is offset to p0, so the kernels see a
 // contiguous range starting at their point 0.
@@ -1379,9 +1394,7 @@ int newton_run(fr_dvm *h, NewtonArgs A, int64_t p0, int64_t np, hipStream_t s) {
     A.pt_resid = h->d_pt_resid + p0;
     ProfScope ps(h, 1, s);
     if (h->prm.model == FR_DVM_ESBGK) {
-        A.use_fact = (kEsPts * sizeof(double) * (size_t)es_slot_doubles(h->vg, 1) <= 65536) && !h->es_direct;
-        const size_t shm = kEsPts * sizeof(double) * (size_t)es_slot_doubles(h->vg, A.use_fact);
-        hipLaunchKernelGGL(k_newton_es, dim3((unsigned)((A.npts + kEsPts - 1) / kEsPts)), dim3(kEsBlock), shm, s, A);
+        launch_es(h, A, s);
     } else {
         launch_bgk(A, h->ne * h->ns, s);
     }
