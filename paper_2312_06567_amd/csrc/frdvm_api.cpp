@@ -126,6 +126,18 @@ StageArgs stage_args(fr_dvm *h, void *f, double dt, int st, int collide) {
         a.fout = f;
         a.dF = h->d_reg;
     }
+    if (h->mx) {
+        // Mixed meshes: the flux points are solution points, so a stage reads
+        // its neighbours' traces from the stage value itself and never writes
+        // over it: the step goes from the caller's buffer through two of the
+        // handle's and back.
+        void *v[2];
+        v[0] = a.scheme == 0 ? h->d_reg : h->d_tr[0];
+        v[1] = a.scheme == 0 ? h->d_tr[0] : h->d_tr[1];
+        a.f = st == 0 ? f : v[st - 1];
+        a.fout = st == 2 ? f : v[st];
+        a.tr_in = a.tr_out = nullptr;
+    }
     return a;
 }
 

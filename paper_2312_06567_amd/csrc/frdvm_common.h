@@ -66,16 +66,17 @@ struct MixType {
     std::vector<double> D;       // [3][ns][ns] reference derivatives
     std::vector<double> lift;    // [nft][ns] correction of a unit jump at each face point
     std::vector<double> W;       // [ns] integral of each Lagrange function (reference)
+    std::vector<double> stream;  // prisms, tetrahedra: the operators in the kernel's order (frdvm_simplex.h)
     std::vector<int32_t> elems;  // elements of this type
-    double *d_D = nullptr, *d_lift = nullptr;
-    float *d_Df = nullptr, *d_liftf = nullptr;
+    double *d_D = nullptr, *d_lift = nullptr, *d_stream = nullptr;  // (hexahedra: D, lift; others: stream)
+    float *d_Df = nullptr, *d_liftf = nullptr, *d_streamf = nullptr;
     int32_t *d_elems = nullptr, *d_fnode = nullptr, *d_ffac = nullptr;
 };
 struct Mixed {
     int64_t ne = 0, npts = 0, nfp = 0;  // elements, solution points, face points (all elements)
     std::vector<int64_t> poff, toff;    // [ne+1] first solution point / face point of each element
     int64_t *d_poff = nullptr, *d_toff = nullptr;
-    int64_t *d_tnb = nullptr;           // [nfp] the neighbour's face point at the same position
+    int64_t *d_pnb = nullptr;           // [nfp] the neighbour's solution point at the same position
     double *d_geo = nullptr;            // [ne][kMixGeo]
     float *d_geof = nullptr;
     MixType t[3];
@@ -247,14 +248,14 @@ int launch_fr_axis(fr_dvm *h, int mode, const StageArgs &a, int do_traces, int d
 int box_split(const fr_dvm *h, bool prime);
 // element references of the current equilibrium records into ref [ne][kRefW]
 int launch_elem_ref(fr_dvm *h, double *ref);
-// ---- mixed meshes (frdvm_gen.hip): same modes and arguments ----
-int launch_fr_mixed(fr_dvm *h, int mode, const StageArgs &a, int do_traces, int do_moments);
+// ---- mixed meshes (frdvm_gen.hip): same modes and arguments, no traces ----
+int launch_fr_mixed(fr_dvm *h, int mode, const StageArgs &a, int do_moments);
 // ---- general meshes (frdvm_gen.hip): same modes and arguments ----
 int launch_fr_gen(fr_dvm *h, int mode, const StageArgs &a, int do_traces, int do_moments);
 // boundary tables of the current parameters (wall and farfield Maxwellians)
 int gen_boundary_tables(fr_dvm *h);
 inline int launch_fr(fr_dvm *h, int mode, const StageArgs &a, int do_traces, int do_moments) {
-    if (h->mx) return launch_fr_mixed(h, mode, a, do_traces, do_moments);
+    if (h->mx) return launch_fr_mixed(h, mode, a, do_moments);
     return h->axis_mode ? launch_fr_axis(h, mode, a, do_traces, do_moments)
                         : launch_fr_gen(h, mode, a, do_traces, do_moments);
 }

@@ -29,6 +29,7 @@
 
 #include "frdvm_common.h"
 #include "frdvm_dev.h"
+#include "frdvm_simplex.h"
 
 namespace frdvm {
 
@@ -652,161 +653,170 @@ int gen_p(fr_dvm *h, int mode, const GenArgs &A, int do_moments) {
 //         - sum_t lift[i][t] s_f min(u.n_f, 0) (f_nb,t - f_node(t)),
 // c_a = u . grad xi_a (constant on a straight element), t running over the
 // face points (the solution points on each face, faces in order), f_nb,t the
-// neighbour's trace at the same position, s_f = |J_face| / |J|.  One wave per
-// (element, 64 velocities), one lane per velocity, the values and residuals
-// of the lane in LDS columns, the operators read through the scalar cache.
-// The collision source and the RK combination are those of the hexahedral
-// kernels; the result's traces are its values at the face points.
+// neighbour's value at the same position, s_f = |J_face| / |J|.  The flux
+// points are solution points, so the neighbours' traces are read from the
+// stage value itself; no trace is stored (a stage never writes over the value
+// it reads).  One wave per (element, 64 velocities), one lane per velocity,
+// the operators read through the scalar cache.  The collision source and the
+// RK combination are those of the hexahedral kernels.
 struct MixArgs {
     VGrid vg;
     int nu, nvw;
     const int32_t *elems;                 // elements of the launched type
-    const int64_t *poff, *toff, *tnb;     // first point / face point of each element; neighbour face point
+    const int64_t *poff, *toff, *pnb;     // first point / face point of each element; the neighbour's point at each face point
     const double *geo;                    // [ne][kMixGeo]
     const float *geof;
-    const double *D, *lift;               // the type's operators: D [3][ns][ns], lift [nft][ns]
-    const float *Df, *liftf;
-    const int32_t *fnode, *ffac;          // [nft] solution point and face of each face point
+    const double *D, *lift, *stream;      // the type's operators: hexahedra D [3][ns][ns], lift [nft][ns]; others the stream
+    const float *Df, *liftf, *streamf;
+    const int32_t *fnode, *ffac;          // hexahedra: [nft] solution point and face of each face point
     StageArgs sa;
-    int do_traces;
 };
 
 template <typename Real>
 struct MixOps {
-    cptr<Real> geo, D, lift;
+    cptr<Real> geo, D, lift, stream;
 };
 __device__ __forceinline__ MixOps<float> mix_ops(const MixArgs &A, float) {
-    return {(cptr<float>)A.geof, (cptr<float>)A.Df, (cptr<float>)A.liftf};
+    return {(cptr<float>)A.geof, (cptr<float>)A.Df, (cptr<float>)A.liftf, (cptr<float>)A.streamf};
 }
 __device__ __forceinline__ MixOps<double> mix_ops(const MixArgs &A, double) {
-    return {(cptr<double>)A.geo, (cptr<double>)A.D, (cptr<double>)A.lift};
+    return {(cptr<double>)A.geo, (cptr<double>)A.D, (cptr<double>)A.lift, (cptr<double>)A.stream};
 }
 
-// PL: Gauss-Lobatto layers of a prism (0: other element types).  A prism's
-// in-plane derivative operators couple only the points of one layer and its
-// axial one only those of one column, an end-face point lifts onto its
-// column and a side-face point onto its layer (the host stores the other
-// entries as exact zeros and checks the face order): the volume term reads
-// 2 NS (NS / PL) + NS PL operator entries instead of 3 NS^2 and the faces
-// 2 NS + 3 PL NS instead of NS NFT, in the order of the dense sums.
-template <typename Real, int NS, int NFT, int MODE, int PL>
-__global__ __launch_bounds__(kGWave) void k_mix_stage(const MixArgs A) {
-    // up to 40 points (tetrahedra, prisms, hexahedra to p = 2) a lane keeps
-    // its values and residuals in registers and the dense products run fully
-    // unrolled with the operator entries as scalar operands; above, both sit
-    // in LDS columns
-    constexpr bool REG = NS <= 40;
+// The wave's element, its lane's velocity and the velocity's contravariant
+// components; an idle lane (past the last node) works on node 0 and stores
+// nothing.
+template <typename Real>
+struct MixLane {
+    int64_t e, p0, t0, nu;
+    int k;
+    bool act;
+    uint32_t ko;
+    double ud[3];
+    Real u0, u1, u2, c[3];
+    cptr<Real> g;
+    __device__ __forceinline__ MixLane(const MixArgs &A, const MixOps<Real> &op) {
+        e = A.elems[blockIdx.x / A.nvw];
+        k = (int)(blockIdx.x % A.nvw) * kGWave + threadIdx.x;
+        act = k < A.nu;
+        const int kk = act ? k : 0;
+        nu = A.nu;
+        ko = (uint32_t)kk * (uint32_t)sizeof(Real);
+        p0 = A.poff[e];
+        t0 = A.toff[e];
+        g = op.geo + e * kMixGeo;
+        int iv[3];
+        split_k(A.vg, kk, iv);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) ud[d] = node_u(A.vg, d, iv[d]);
+        u0 = (Real)ud[0];
+        u1 = (Real)ud[1];
+        u2 = (Real)ud[2];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) c[a] = u0 * g[3 * a] + u1 * g[3 * a + 1] + u2 * g[3 * a + 2];
+    }
+    __device__ __forceinline__ Real un(int f) const { return u0 * g[9 + 3 * f] + u1 * g[10 + 3 * f] + u2 * g[11 + 3 * f]; }
+};
+
+// Collision source and Runge-Kutta combination of point i with value fq,
+// advective residual L and second-register value xv; stores the result.
+// rs: the lane's stream of random bits (one xorshift step per value).
+template <typename Real>
+__device__ __forceinline__ Real mix_point(const MixArgs &A, const MixLane<Real> &v, int i, Real fq, Real L, Real xv,
+                                          bool useX, uint32_t &rs) {
+    if (A.sa.collide) {
+        const cptr<double> q = (cptr<double>)A.sa.eq + (v.p0 + i) * kEqW;
+        const double c0 = v.ud[0] - q[EQ_V], c1 = v.ud[1] - q[EQ_V + 1], c2 = v.ud[2] - q[EQ_V + 2];
+        double t0 = -0.5 * q[EQ_B] * c0;
+        t0 = fma(-q[EQ_B + 3], c1, t0);
+        t0 = fma(-q[EQ_B + 4], c2, t0);
+        double t1 = -0.5 * q[EQ_B + 1] * c1;
+        t1 = fma(-q[EQ_B + 5], c2, t1);
+        const double t2 = -0.5 * q[EQ_B + 2] * c2;
+        double E = fma(c0, t0, q[EQ_C0]);
+        E = fma(c1, t1, E);
+        E = fma(c2, t2, E);
+        L += (gexp<Real>(E) - fq) * (Real)q[EQ_INVTAU];
+    }
+    const Real dt = (Real)A.sa.dt;
+    const int64_t row = (v.p0 + i) * v.nu;
+    double fod;
+    if (A.sa.scheme == 0) {
+        fod = A.sa.beta * ((double)fq + (double)(dt * L));
+        if (useX) fod = fma(A.sa.alpha, (double)xv, fod);
+    } else {
+        Real dd = dt * L;
+        if (useX) dd += (Real)A.sa.lsA * xv;
+        if (v.act && A.sa.keep_dF) sto(reinterpret_cast<Real *>(A.sa.dF) + row, v.ko, dd);
+        fod = fma(A.sa.lsB, (double)dd, (double)fq);
+    }
+    Real fo;
+    if constexpr (sizeof(Real) == 4) {
+        rs = xorshift32(rs);
+        fo = round_stochastic(fod, rs);
+    } else {
+        fo = (Real)fod;
+    }
+    if (v.act) sto(reinterpret_cast<Real *>(A.sa.fout) + row, v.ko, fo);
+    return fo;
+}
+
+// Hexahedra: dense operators; up to 27 points the values and residuals in
+// registers, above in LDS columns.
+template <typename Real, int NS, int NFT, int MODE>
+__global__ __launch_bounds__(kGWave) void k_mix_hex(const MixArgs A) {
+    constexpr bool REG = NS <= 27;
     __shared__ Real sf[NS][kGWave];
     __shared__ Real sa[REG ? 1 : NS][kGWave];
-    const int64_t e = A.elems[blockIdx.x / A.nvw];
-    const int lane = threadIdx.x;
-    const int k = (int)(blockIdx.x % A.nvw) * kGWave + lane;
-    const bool act = k < A.nu;
-    const int kk = act ? k : 0;  // an idle lane works on node 0 and stores nothing
-    const int64_t nu = A.nu;
-    const uint32_t ko = (uint32_t)kk * (uint32_t)sizeof(Real);
-    const int64_t p0 = A.poff[e], t0 = A.toff[e];
     const MixOps<Real> op = mix_ops(A, Real(0));
-    const cptr<Real> g = op.geo + e * kMixGeo;
+    const MixLane<Real> v(A, op);
+    const int lane = threadIdx.x;
+    const int64_t nu = v.nu;
     const cptr<int32_t> fnode = (cptr<int32_t>)A.fnode, ffac = (cptr<int32_t>)A.ffac;
-    int iv[3];
-    split_k(A.vg, kk, iv);
-    const double ud[3] = {node_u(A.vg, 0, iv[0]), node_u(A.vg, 1, iv[1]), node_u(A.vg, 2, iv[2])};
-    const Real u0 = (Real)ud[0], u1 = (Real)ud[1], u2 = (Real)ud[2];
-    Real c[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) c[a] = u0 * g[3 * a] + u1 * g[3 * a + 1] + u2 * g[3 * a + 2];
-    const Real *fE = reinterpret_cast<const Real *>(A.sa.f) + p0 * nu;
-    const Real *trI = reinterpret_cast<const Real *>(A.sa.tr_in);
+    const cptr<int64_t> pnb = (cptr<int64_t>)A.pnb + v.t0;
+    const Real *fin = reinterpret_cast<const Real *>(A.sa.f);
+    const Real *fE = fin + v.p0 * nu;
     // the upwind jump at face point t, scaled (0 where the velocity leaves)
     auto jump_at = [&](int t) {
         const int f = ffac[t];
-        const Real un = u0 * g[9 + 3 * f] + u1 * g[10 + 3 * f] + u2 * g[11 + 3 * f];
+        const Real un = v.un(f);
         Real jump = Real(0);
-        if (un < Real(0)) jump = un * g[27 + f] * (ldo(trI + A.tnb[t0 + t] * nu, ko) - sf[fnode[t]][lane]);
+        if (un < Real(0)) jump = un * v.g[27 + f] * (ldo(fin + pnb[t] * nu, v.ko) - sf[fnode[t]][lane]);
         return jump;
     };
     Real fv[REG ? NS : 1], r[REG ? NS : 1];
     if constexpr (REG) {
 #pragma unroll
         for (int i = 0; i < NS; ++i) {
-            fv[i] = ldo(fE + i * nu, ko);
+            fv[i] = ldo(fE + i * nu, v.ko);
             sf[i][lane] = fv[i];
             r[i] = Real(0);
         }
-        // volume: r_i = -sum_a c_a (D_a f)_i
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
 #pragma unroll
             for (int i = 0; i < NS; ++i) {
                 Real gi = Real(0);
-                if constexpr (PL > 0) {
-                    constexpr int NT = NS / PL;  // points per layer
-                    if (a < 2) {
-                        const int j0 = i / NT * NT;  // the layer of point i
 #pragma unroll
-                        for (int m = 0; m < NT; ++m) gi = fma(op.D[(a * NS + i) * NS + j0 + m], fv[j0 + m], gi);
-                    } else {
-                        const int m0 = i % NT;  // the column of point i
-#pragma unroll
-                        for (int k = 0; k < PL; ++k) gi = fma(op.D[(a * NS + i) * NS + m0 + NT * k], fv[m0 + NT * k], gi);
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < NS; ++j) gi = fma(op.D[(a * NS + i) * NS + j], fv[j], gi);
-                }
-                r[i] = fma(-c[a], gi, r[i]);
+                for (int j = 0; j < NS; ++j) gi = fma(op.D[(a * NS + i) * NS + j], fv[j], gi);
+                r[i] = fma(-v.c[a], gi, r[i]);
             }
         }
-        // faces
-        if constexpr (PL > 0) {
-            constexpr int NT = NS / PL;
-            // bottom and top faces: face point m lifts onto column m
 #pragma unroll 1
-            for (int f = 0; f < 2; ++f) {
+        for (int t = 0; t < NFT; ++t) {
+            const Real jump = jump_at(t);
 #pragma unroll
-                for (int m = 0; m < NT; ++m) {
-                    const int t = f * NT + m;
-                    const Real jump = jump_at(t);
-#pragma unroll
-                    for (int k = 0; k < PL; ++k) {
-                        const int i = m + NT * k;
-                        r[i] = fma(-op.lift[t * NS + i], jump, r[i]);
-                    }
-                }
-            }
-            // side faces, per (face, edge point): face point e + PL k lifts
-            // onto layer k
-#pragma unroll 1
-            for (int u = 0; u < 3 * PL; ++u) {
-#pragma unroll
-                for (int k = 0; k < PL; ++k) {
-                    const int t = 2 * NT + u / PL * (PL * PL) + u % PL + PL * k;
-                    const Real jump = jump_at(t);
-#pragma unroll
-                    for (int m = 0; m < NT; ++m) {
-                        const int i = m + NT * k;
-                        r[i] = fma(-op.lift[t * NS + i], jump, r[i]);
-                    }
-                }
-            }
-        } else {
-#pragma unroll 1
-            for (int t = 0; t < NFT; ++t) {
-                const Real jump = jump_at(t);
-#pragma unroll
-                for (int i = 0; i < NS; ++i) r[i] = fma(-op.lift[t * NS + i], jump, r[i]);
-            }
+            for (int i = 0; i < NS; ++i) r[i] = fma(-op.lift[t * NS + i], jump, r[i]);
         }
     } else {
 #pragma unroll 4
-        for (int i = 0; i < NS; ++i) sf[i][lane] = ldo(fE + i * nu, ko);
+        for (int i = 0; i < NS; ++i) sf[i][lane] = ldo(fE + i * nu, v.ko);
 #pragma unroll 1
         for (int i = 0; i < NS; ++i) {
             Real acc = Real(0);
 #pragma unroll 4
             for (int j = 0; j < NS; ++j) {
-                const Real w = c[0] * op.D[i * NS + j] + c[1] * op.D[(NS + i) * NS + j] + c[2] * op.D[(2 * NS + i) * NS + j];
+                const Real w = v.c[0] * op.D[i * NS + j] + v.c[1] * op.D[(NS + i) * NS + j] + v.c[2] * op.D[(2 * NS + i) * NS + j];
                 acc = fma(w, sf[j][lane], acc);
             }
             sa[i][lane] = -acc;
@@ -827,110 +837,230 @@ __global__ __launch_bounds__(kGWave) void k_mix_stage(const MixArgs A) {
         else return sf[i][lane];
     };
     if (MODE == GMODE_RESID) {
-        Real *R = reinterpret_cast<Real *>(A.sa.fout) + p0 * nu;
-        if (act)
+        Real *R = reinterpret_cast<Real *>(A.sa.fout) + v.p0 * nu;
+        if (v.act)
 #pragma unroll
-            for (int i = 0; i < NS; ++i) sto(R + i * nu, ko, res(i));
+            for (int i = 0; i < NS; ++i) sto(R + i * nu, v.ko, res(i));
         return;
     }
-    // collision source and the Runge-Kutta combination, point by point
-    const Real dt = (Real)A.sa.dt;
-    const bool collide = A.sa.collide;
     const bool useX = A.sa.scheme == 0 ? A.sa.alpha != 0.0 : A.sa.lsA != 0.0;
-    const Real *XE = reinterpret_cast<const Real *>(A.sa.scheme == 0 ? A.sa.fn : A.sa.dF) + p0 * nu;
-    Real *outE = reinterpret_cast<Real *>(A.sa.fout) + p0 * nu;
-    Real *dFE = reinterpret_cast<Real *>(A.sa.dF) + p0 * nu;
+    const Real *XE = reinterpret_cast<const Real *>(A.sa.scheme == 0 ? A.sa.fn : A.sa.dF) + v.p0 * nu;
+    uint32_t rs = sizeof(Real) == 4 ? round_bits(A.sa.seed, (uint32_t)v.p0, (uint32_t)v.k) | 1u : 0u;
 #pragma unroll
-    for (int i = 0; i < NS; ++i) {
-        const Real fq = val(i);
-        Real L = res(i);
-        if (collide) {
-            const cptr<double> q = (cptr<double>)A.sa.eq + (p0 + i) * kEqW;
-            const double c0 = ud[0] - q[EQ_V], c1 = ud[1] - q[EQ_V + 1], c2 = ud[2] - q[EQ_V + 2];
-            double t0_ = -0.5 * q[EQ_B] * c0;
-            t0_ = fma(-q[EQ_B + 3], c1, t0_);
-            t0_ = fma(-q[EQ_B + 4], c2, t0_);
-            double t1 = -0.5 * q[EQ_B + 1] * c1;
-            t1 = fma(-q[EQ_B + 5], c2, t1);
-            const double t2 = -0.5 * q[EQ_B + 2] * c2;
-            double E = fma(c0, t0_, q[EQ_C0]);
-            E = fma(c1, t1, E);
-            E = fma(c2, t2, E);
-            L += (gexp<Real>(E) - fq) * (Real)q[EQ_INVTAU];
+    for (int i = 0; i < NS; ++i)
+        mix_point(A, v, i, val(i), res(i), useX ? ldo(XE + i * nu, v.ko) : Real(0), useX, rs);
+}
+
+// Prisms (DIM 2: the triangle's points on the PL = p + 1 Gauss-Lobatto layers
+// of a line) and tetrahedra (DIM 3): values and residuals in registers, the
+// operators as scalar operands from one stream in the order of use, only
+// their nonzero entries (frdvm_simplex.h); a prism's entry serves all layers
+// (columns) at once.  A face's normal is constant, so whether a velocity
+// enters is decided once per face: a wave none of whose velocities enter
+// skips the face, and the neighbour's values of a face are requested
+// together.  What bounds it: HBM (f, the neighbours' face values, the result,
+// the second register).  A stage of 51,200 points at p = 3, 24^3 velocities,
+// FP32 low-storage: tetrahedra 3.44 -> 1.64 ms (4.5 TB/s of those bytes),
+// prisms 2.70 -> 1.23 ms (3.9 TB/s); before, with dense tetrahedral
+// products, the face points one after the other through LDS and their
+// traces stored and read back, VALU issue and load latency bound it.
+template <typename Real, int DIM, int P, int MODE>
+__global__ __launch_bounds__(kGWave) void k_mix_simplex(const MixArgs A) {
+    using S = Simplex<DIM, P>;
+    constexpr auto tb = S::table();
+    constexpr auto rest = S::rest();
+    constexpr auto face = S::faces();
+    constexpr int NT = S::NP, NM = S::NM, PL = DIM == 2 ? P + 1 : 1, NS = NT * PL;
+    const MixOps<Real> op = mix_ops(A, Real(0));
+    const MixLane<Real> v(A, op);
+    const int64_t nu = v.nu;
+    const cptr<int64_t> pnb = (cptr<int64_t>)A.pnb + v.t0;
+    const Real *fin = reinterpret_cast<const Real *>(A.sa.f);
+    const Real *fE = fin + v.p0 * nu;
+    Real fv[NS], r[NS];
+#pragma unroll
+    for (int i = 0; i < NS; ++i) fv[i] = ldo(fE + i * nu, v.ko);
+    int o = 0;  // position in the stream (a constant everywhere once unrolled)
+    // volume: r = -sum_a c_a D_a f at the sub points, then interpolated
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+        Real gm[PL];
+#pragma unroll
+        for (int k = 0; k < PL; ++k) gm[k] = Real(0);
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) {
+            Real s[PL];
+#pragma unroll
+            for (int k = 0; k < PL; ++k) s[k] = Real(0);
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+                if ((tb.d[a][m] >> j) & 1) {
+                    const Real w = op.stream[o++];
+#pragma unroll
+                    for (int k = 0; k < PL; ++k) s[k] = fma(w, fv[j + NT * k], s[k]);
+                }
+#pragma unroll
+            for (int k = 0; k < PL; ++k) gm[k] = fma(-v.c[a], s[k], gm[k]);
         }
-        const Real xv = useX ? ldo(XE + i * nu, ko) : Real(0);
-        double fod;
-        if (A.sa.scheme == 0) {
-            fod = A.sa.beta * ((double)fq + (double)(dt * L));
-            if (useX) fod = fma(A.sa.alpha, (double)xv, fod);
-        } else {
-            Real dd = dt * L;
-            if (useX) dd += (Real)A.sa.lsA * xv;
-            if (act && A.sa.keep_dF) sto(dFE + i * nu, ko, dd);
-            fod = fma(A.sa.lsB, (double)dd, (double)fq);
-        }
-        Real fo;
-        if constexpr (sizeof(Real) == 4)
-            fo = round_stochastic(fod, round_bits(A.sa.seed, (uint32_t)(p0 + i), (uint32_t)k));
-        else
-            fo = (Real)fod;
-        sf[i][lane] = fo;
-        if (act) sto(outE + i * nu, ko, fo);
+#pragma unroll
+        for (int k = 0; k < PL; ++k) r[tb.sub[m] + NT * k] = gm[k];
     }
-    if (A.do_traces && act) {
-        Real *trO = reinterpret_cast<Real *>(A.sa.tr_out) + t0 * nu;
-#pragma unroll 1
-        for (int t = 0; t < NFT; ++t) sto(trO + t * nu, ko, sf[fnode[t]][lane]);
+#pragma unroll
+    for (int q = 0; q < NT - NM; ++q) {
+        Real s[PL];
+#pragma unroll
+        for (int k = 0; k < PL; ++k) s[k] = Real(0);
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+            if ((tb.e[q] >> m) & 1) {
+                const Real w = op.stream[o++];
+#pragma unroll
+                for (int k = 0; k < PL; ++k) s[k] = fma(w, r[tb.sub[m] + NT * k], s[k]);
+            }
+#pragma unroll
+        for (int k = 0; k < PL; ++k) r[rest.i[q] + NT * k] = s[k];
+    }
+    if constexpr (DIM == 3) {
+#pragma unroll
+        for (int f = 0; f < S::NFACE; ++f) {
+            const Real un = v.un(f);
+            if (un < Real(0)) {
+                const Real sc = un * v.g[27 + f];
+                Real ext[S::NF];
+#pragma unroll
+                for (int t = 0; t < S::NF; ++t) ext[t] = ldo(fin + pnb[f * S::NF + t] * nu, v.ko);
+#pragma unroll
+                for (int t = 0; t < S::NF; ++t) {
+                    const Real jump = sc * (ext[t] - fv[face.n[f][t]]);
+#pragma unroll
+                    for (int i = 0; i < NS; ++i)
+                        r[i] = fma(-op.stream[o + (f * S::NF + t) * NS + i], jump, r[i]);
+                }
+            }
+        }
+    } else {
+        // axial derivative, column by column
+#pragma unroll
+        for (int i = 0; i < PL; ++i)
+#pragma unroll
+            for (int m = 0; m < NT; ++m) {
+                Real s = Real(0);
+#pragma unroll
+                for (int k = 0; k < PL; ++k) s = fma(op.stream[o + i * PL + k], fv[m + NT * k], s);
+                r[m + NT * i] = fma(-v.c[2], s, r[m + NT * i]);
+            }
+        o += PL * PL;
+        // bottom and top: point m lifts onto its column
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            const Real un = v.un(f);
+            if (un < Real(0)) {
+                const Real sc = un * v.g[27 + f];
+                Real ext[NT];
+#pragma unroll
+                for (int m = 0; m < NT; ++m) ext[m] = ldo(fin + pnb[f * NT + m] * nu, v.ko);
+#pragma unroll
+                for (int m = 0; m < NT; ++m) {
+                    const Real jump = sc * (ext[m] - fv[m + (f ? NT * (PL - 1) : 0)]);
+#pragma unroll
+                    for (int k = 0; k < PL; ++k) r[m + NT * k] = fma(-op.stream[o + f * PL + k], jump, r[m + NT * k]);
+                }
+            }
+        }
+        o += 2 * PL;
+        // sides: edge point e on layer k lifts onto the layer; the points of
+        // EB edge points requested together
+        constexpr int EB = sizeof(Real) == 4 || PL < 3 ? PL : 2;
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+            const Real un = v.un(2 + f);
+            if (un < Real(0)) {
+                const Real sc = un * v.g[29 + f];
+#pragma unroll
+                for (int e0 = 0; e0 < PL; e0 += EB) {
+                    Real ext[EB][PL];
+#pragma unroll
+                    for (int x = 0; x < EB; ++x)
+                        if (e0 + x < PL)
+#pragma unroll
+                            for (int k = 0; k < PL; ++k)
+                                ext[x][k] = ldo(fin + pnb[2 * NT + f * PL * PL + e0 + x + PL * k] * nu, v.ko);
+#pragma unroll
+                    for (int x = 0; x < EB; ++x)
+                        if (e0 + x < PL) {
+                            Real jump[PL];
+#pragma unroll
+                            for (int k = 0; k < PL; ++k) jump[k] = sc * (ext[x][k] - fv[face.n[f][e0 + x] + NT * k]);
+#pragma unroll
+                            for (int m = 0; m < NT; ++m) {
+                                const Real w = -op.stream[o + (f * PL + e0 + x) * NT + m];
+#pragma unroll
+                                for (int k = 0; k < PL; ++k) r[m + NT * k] = fma(w, jump[k], r[m + NT * k]);
+                            }
+                        }
+                }
+            }
+        }
+    }
+    if (MODE == GMODE_RESID) {
+        Real *R = reinterpret_cast<Real *>(A.sa.fout) + v.p0 * nu;
+        if (v.act)
+#pragma unroll
+            for (int i = 0; i < NS; ++i) sto(R + i * nu, v.ko, r[i]);
+        return;
+    }
+    // collision source and the Runge-Kutta combination, a layer's (the
+    // tetrahedron: ten points') second-register values requested together
+    constexpr int XB = DIM == 2 ? NT : (NS < 10 ? NS : 10);
+    const bool useX = A.sa.scheme == 0 ? A.sa.alpha != 0.0 : A.sa.lsA != 0.0;
+    const Real *XE = reinterpret_cast<const Real *>(A.sa.scheme == 0 ? A.sa.fn : A.sa.dF) + v.p0 * nu;
+    uint32_t rs = sizeof(Real) == 4 ? round_bits(A.sa.seed, (uint32_t)v.p0, (uint32_t)v.k) | 1u : 0u;
+#pragma unroll
+    for (int i0 = 0; i0 < NS; i0 += XB) {
+        Real xv[XB];
+#pragma unroll
+        for (int x = 0; x < XB; ++x) xv[x] = useX ? ldo(XE + (i0 + x) * nu, v.ko) : Real(0);
+#pragma unroll
+        for (int x = 0; x < XB; ++x) mix_point(A, v, i0 + x, fv[i0 + x], r[i0 + x], xv[x], useX, rs);
     }
 }
 
-// Traces of f: its values at the face points.
 template <typename Real, int NS, int NFT>
-__global__ __launch_bounds__(kGWave) void k_mix_traces(const MixArgs A, const Real *__restrict__ f, Real *__restrict__ tr) {
-    const int64_t e = A.elems[blockIdx.x / A.nvw];
-    const int k = (int)(blockIdx.x % A.nvw) * kGWave + threadIdx.x;
-    if (k >= A.nu) return;
-    const int64_t nu = A.nu, p0 = A.poff[e], t0 = A.toff[e];
-#pragma unroll 1
-    for (int t = 0; t < NFT; ++t) tr[(t0 + t) * nu + k] = f[(p0 + A.fnode[t]) * nu + k];
-}
-
-template <typename Real, int NS, int NFT, int PL = 0>
-int mix_launch(fr_dvm *h, int mode, const MixArgs &A, unsigned blocks) {
-    if (mode == 0)
-        hipLaunchKernelGGL((k_mix_traces<Real, NS, NFT>), dim3(blocks), dim3(kGWave), 0, h->stream, A,
-                           reinterpret_cast<const Real *>(A.sa.f), reinterpret_cast<Real *>(A.sa.tr_out));
-    else if (mode == GMODE_RESID)
-        hipLaunchKernelGGL((k_mix_stage<Real, NS, NFT, GMODE_RESID, PL>), dim3(blocks), dim3(kGWave), 0, h->stream, A);
+int mix_hex(fr_dvm *h, int mode, const MixArgs &A, unsigned blocks) {
+    if (mode == GMODE_RESID)
+        hipLaunchKernelGGL((k_mix_hex<Real, NS, NFT, GMODE_RESID>), dim3(blocks), dim3(kGWave), 0, h->stream, A);
     else
-        hipLaunchKernelGGL((k_mix_stage<Real, NS, NFT, GMODE_STAGE, PL>), dim3(blocks), dim3(kGWave), 0, h->stream, A);
+        hipLaunchKernelGGL((k_mix_hex<Real, NS, NFT, GMODE_STAGE>), dim3(blocks), dim3(kGWave), 0, h->stream, A);
+    return gcheck(h, "mixed-mesh kernel");
+}
+template <typename Real, int DIM, int P>
+int mix_simplex(fr_dvm *h, int mode, const MixArgs &A, unsigned blocks) {
+    if (mode == GMODE_RESID)
+        hipLaunchKernelGGL((k_mix_simplex<Real, DIM, P, GMODE_RESID>), dim3(blocks), dim3(kGWave), 0, h->stream, A);
+    else
+        hipLaunchKernelGGL((k_mix_simplex<Real, DIM, P, GMODE_STAGE>), dim3(blocks), dim3(kGWave), 0, h->stream, A);
     return gcheck(h, "mixed-mesh kernel");
 }
 
 // (type, order) -> the kernel instantiation for its point counts
 template <typename Real>
-int mix_dispatch(fr_dvm *h, int mode, const MixArgs &A, int t, const MixType &T, unsigned blocks) {
-    const int key = 10 * t + h->p;
-    int ns = 0, nft = 0, rc = FR_DVM_EUNSUPPORTED;
-    switch (key) {
-        case 1: ns = 8; nft = 24; rc = mix_launch<Real, 8, 24>(h, mode, A, blocks); break;
-        case 2: ns = 27; nft = 54; rc = mix_launch<Real, 27, 54>(h, mode, A, blocks); break;
-        case 3: ns = 64; nft = 96; rc = mix_launch<Real, 64, 96>(h, mode, A, blocks); break;
-        case 11: ns = 6; nft = 18; rc = mix_launch<Real, 6, 18, 2>(h, mode, A, blocks); break;
-        case 12: ns = 18; nft = 39; rc = mix_launch<Real, 18, 39, 3>(h, mode, A, blocks); break;
-        case 13: ns = 40; nft = 68; rc = mix_launch<Real, 40, 68, 4>(h, mode, A, blocks); break;
-        case 21: ns = 4; nft = 12; rc = mix_launch<Real, 4, 12>(h, mode, A, blocks); break;
-        case 22: ns = 10; nft = 24; rc = mix_launch<Real, 10, 24>(h, mode, A, blocks); break;
-        case 23: ns = 20; nft = 40; rc = mix_launch<Real, 20, 40>(h, mode, A, blocks); break;
-        default: return h->fail(FR_DVM_EUNSUPPORTED, "mixed-mesh element type / order");
+int mix_dispatch(fr_dvm *h, int mode, const MixArgs &A, int t, unsigned blocks) {
+    switch (10 * t + h->p) {
+        case 1: return mix_hex<Real, 8, 24>(h, mode, A, blocks);
+        case 2: return mix_hex<Real, 27, 54>(h, mode, A, blocks);
+        case 3: return mix_hex<Real, 64, 96>(h, mode, A, blocks);
+        case 11: return mix_simplex<Real, 2, 1>(h, mode, A, blocks);
+        case 12: return mix_simplex<Real, 2, 2>(h, mode, A, blocks);
+        case 13: return mix_simplex<Real, 2, 3>(h, mode, A, blocks);
+        case 21: return mix_simplex<Real, 3, 1>(h, mode, A, blocks);
+        case 22: return mix_simplex<Real, 3, 2>(h, mode, A, blocks);
+        case 23: return mix_simplex<Real, 3, 3>(h, mode, A, blocks);
     }
-    (void)ns;
-    (void)nft;
-    return rc;
+    return h->fail(FR_DVM_EUNSUPPORTED, "mixed-mesh element type / order");
 }
 
 template <typename Real>
-int mix_run(fr_dvm *h, int mode, const StageArgs &sa, int do_traces, int do_moments) {
+int mix_run(fr_dvm *h, int mode, const StageArgs &sa, int do_moments) {
     const Mixed &mx = *h->mx;
     MixArgs A;
     std::memset(&A, 0, sizeof(A));
@@ -939,13 +1069,12 @@ int mix_run(fr_dvm *h, int mode, const StageArgs &sa, int do_traces, int do_mome
     A.nvw = (A.nu + kGWave - 1) / kGWave;
     A.poff = mx.d_poff;
     A.toff = mx.d_toff;
-    A.tnb = mx.d_tnb;
+    A.pnb = mx.d_pnb;
     A.geo = mx.d_geo;
     A.geof = mx.d_geof;
     A.sa = sa;
-    A.do_traces = do_traces;
     int rc;
-    if (mode != 0 || do_traces) {
+    if (mode != 0) {  // (the incoming f needs no pass for its traces)
         for (int t = 0; t < 3; ++t) {
             const MixType &T = mx.t[t];
             if (T.elems.empty()) continue;
@@ -956,9 +1085,11 @@ int mix_run(fr_dvm *h, int mode, const StageArgs &sa, int do_traces, int do_mome
             A.lift = T.d_lift;
             A.Df = T.d_Df;
             A.liftf = T.d_liftf;
+            A.stream = T.d_stream;
+            A.streamf = T.d_streamf;
             A.fnode = T.d_fnode;
             A.ffac = T.d_ffac;
-            if ((rc = mix_dispatch<Real>(h, mode, A, t, T, (unsigned)(T.elems.size() * A.nvw)))) return rc;
+            if ((rc = mix_dispatch<Real>(h, mode, A, t, (unsigned)(T.elems.size() * A.nvw)))) return rc;
         }
     }
     const bool moments = (mode == 0 || mode == GMODE_STAGE) && do_moments;
@@ -984,10 +1115,10 @@ int mix_run(fr_dvm *h, int mode, const StageArgs &sa, int do_traces, int do_mome
 
 }  // namespace
 
-int launch_fr_mixed(fr_dvm *h, int mode, const StageArgs &sa, int do_traces, int do_moments) {
+int launch_fr_mixed(fr_dvm *h, int mode, const StageArgs &sa, int do_moments) {
     if (sa.e0 != 0 || sa.ecount != 0) return h->fail(FR_DVM_EINVAL, "element ranges need an axis-aligned box mesh");
-    return h->prm.precision == FR_DVM_FP64 ? mix_run<double>(h, mode, sa, do_traces, do_moments)
-                                           : mix_run<float>(h, mode, sa, do_traces, do_moments);
+    return h->prm.precision == FR_DVM_FP64 ? mix_run<double>(h, mode, sa, do_moments)
+                                           : mix_run<float>(h, mode, sa, do_moments);
 }
 
 int launch_fr_gen(fr_dvm *h, int mode, const StageArgs &sa, int do_traces, int do_moments) {

@@ -32,6 +32,7 @@
 #include <vector>
 
 #include "frdvm_common.h"
+#include "frdvm_simplex.h"
 
 using namespace frdvm;
 
@@ -322,6 +323,110 @@ int prism_structure(fr_dvm *h, MixType &T, int p) {
     return FR_DVM_OK;
 }
 
+// The operator stream (frdvm_simplex.h) of prisms (DIM 2: the triangle, times
+// the line) and tetrahedra (DIM 3) from the dense operators.  The point order
+// on the faces, every entry a mask leaves out, the interpolation of the
+// derivatives and (prisms) the equality of layers and columns are checked.
+template <int DIM, int P>
+int fill_stream(fr_dvm *h, MixType &T, const std::vector<V3> &x) {
+    using S = Simplex<DIM, P>;
+    constexpr auto tb = S::table();
+    constexpr auto rest = S::rest();
+    constexpr auto face = S::faces();
+    constexpr int NP = S::NP, NM = S::NM, PL = DIM == 2 ? P + 1 : 1;
+    auto bad = [&](const char *what) { return h->fail(FR_DVM_EINVAL, std::string("simplex operators: ") + what); };
+    if (T.ns != NP * PL || T.nft != (DIM == 3 ? S::NFACE * S::NF : 2 * NP + 3 * PL * PL)) return bad("point counts");
+    const int ns = T.ns;
+    auto D = [&](int a, int i, int j) { return T.D[(size_t)(a * ns + i) * ns + j]; };
+    auto lift = [&](int t, int i) { return T.lift[(size_t)t * ns + i]; };
+    double dmax = 0.0, lmax = 0.0;
+    for (double v : T.D) dmax = std::max(dmax, std::fabs(v));
+    for (double v : T.lift) lmax = std::max(lmax, std::fabs(v));
+    const double dtol = 1e-9 * dmax, ltol = 1e-9 * lmax;
+    // interpolation of P_(p-1) from the sub points
+    std::vector<std::array<int, 3>> ex;
+    for (const auto &q : exponents(FR_DVM_TET, P - 1))
+        if (DIM == 3 || q[2] == 0) ex.push_back(q);
+    if ((int)ex.size() != NM) return bad("derivative space");
+    std::vector<double> V(NM * NM), E((NP - NM) * NM, 0.0), phi(NM);
+    for (int m = 0; m < NM; ++m) {
+        basis(ex, P, x[tb.sub[m]], phi.data(), nullptr);
+        for (int k = 0; k < NM; ++k) V[m * NM + k] = phi[k];
+    }
+    if (!invert(V, NM)) return bad("interpolation points");
+    for (int q = 0; q < NP - NM; ++q) {
+        basis(ex, P, x[rest.i[q]], phi.data(), nullptr);
+        for (int m = 0; m < NM; ++m)
+            for (int k = 0; k < NM; ++k) E[q * NM + m] += phi[k] * V[k * NM + m];
+    }
+    std::vector<double> &st = T.stream;
+    st.clear();
+    for (int m = 0; m < NM; ++m)
+        for (int a = 0; a < DIM; ++a)
+            for (int j = 0; j < NP; ++j) {
+                if ((tb.d[a][m] >> j) & 1) st.push_back(D(a, tb.sub[m], j));
+                else if (std::fabs(D(a, tb.sub[m], j)) > dtol) return bad("derivative pattern");
+                for (int k = 1; k < PL; ++k)
+                    if (std::fabs(D(a, tb.sub[m] + NP * k, j + NP * k) - D(a, tb.sub[m], j)) > dtol) return bad("layers");
+            }
+    for (int q = 0; q < NP - NM; ++q) {
+        for (int m = 0; m < NM; ++m) {
+            if ((tb.e[q] >> m) & 1) st.push_back(E[q * NM + m]);
+            else if (std::fabs(E[q * NM + m]) > 1e-9) return bad("interpolation pattern");
+        }
+        for (int k = 0; k < PL; ++k)
+            for (int a = 0; a < DIM; ++a)
+                for (int j = 0; j < NP; ++j) {
+                    double v = 0.0;
+                    for (int m = 0; m < NM; ++m) v += E[q * NM + m] * D(a, tb.sub[m] + NP * k, j + NP * k);
+                    if (std::fabs(v - D(a, rest.i[q] + NP * k, j + NP * k)) > dtol) return bad("interpolated derivative");
+                }
+    }
+    if constexpr (DIM == 3) {
+        for (int f = 0; f < S::NFACE; ++f)
+            for (int t = 0; t < S::NF; ++t) {
+                const int g = f * S::NF + t;
+                if (T.ffac[g] != f || T.fnode[g] != face.n[f][t]) return bad("face points");
+                for (int i = 0; i < NP; ++i) st.push_back(lift(g, i));
+            }
+        return (int)st.size() == tet_stream<P>() ? FR_DVM_OK : bad("stream length");
+    } else {
+        for (int i = 0; i < PL; ++i)
+            for (int k = 0; k < PL; ++k) {
+                st.push_back(D(2, NP * i, NP * k));
+                for (int m = 1; m < NP; ++m)
+                    if (std::fabs(D(2, m + NP * i, m + NP * k) - D(2, NP * i, NP * k)) > dtol) return bad("columns");
+            }
+        // (the order of the face points is checked by prism_structure, the edges' points here)
+        for (int f = 0; f < 2; ++f)
+            for (int k = 0; k < PL; ++k) {
+                st.push_back(lift(f * NP, NP * k));
+                for (int m = 1; m < NP; ++m)
+                    if (std::fabs(lift(f * NP + m, m + NP * k) - lift(f * NP, NP * k)) > ltol) return bad("end lifting");
+            }
+        for (int f = 0; f < 3; ++f)
+            for (int e = 0; e < PL; ++e) {
+                const int t0 = 2 * NP + f * PL * PL + e;
+                for (int k = 0; k < PL; ++k)
+                    if (T.fnode[t0 + PL * k] != face.n[f][e] + NP * k) return bad("side points");
+                for (int m = 0; m < NP; ++m) {
+                    st.push_back(lift(t0, m));
+                    for (int k = 1; k < PL; ++k)
+                        if (std::fabs(lift(t0 + PL * k, m + NP * k) - lift(t0, m)) > ltol) return bad("side lifting");
+                }
+            }
+        return (int)st.size() == prism_stream<P>() ? FR_DVM_OK : bad("stream length");
+    }
+}
+template <int DIM>
+int fill_stream_p(fr_dvm *h, MixType &T, int p, const std::vector<V3> &x) {
+    switch (p) {
+        case 1: return fill_stream<DIM, 1>(h, T, x);
+        case 2: return fill_stream<DIM, 2>(h, T, x);
+    }
+    return fill_stream<DIM, 3>(h, T, x);
+}
+
 // Reference operators of one element type.
 int build_type(fr_dvm *h, MixType &T, int t, int p) {
     T.etype = t;
@@ -410,7 +515,10 @@ int build_type(fr_dvm *h, MixType &T, int t, int p) {
     T.lift.assign((size_t)ns * T.nft, 0.0);
     for (int tt = 0; tt < T.nft; ++tt)
         for (int i = 0; i < ns; ++i) T.lift[(size_t)tt * ns + i] = cols[tt][i];
-    return t == FR_DVM_PRISM ? prism_structure(h, T, p) : FR_DVM_OK;
+    if (t == FR_DVM_HEX) return FR_DVM_OK;
+    if (t == FR_DVM_TET) return fill_stream_p<3>(h, T, p, x);
+    const int rc = prism_structure(h, T, p);
+    return rc ? rc : fill_stream_p<2>(h, T, p, simplex_points(p, 2));
 }
 
 template <typename T>
@@ -553,8 +661,9 @@ extern "C" int fr_dvm_create_mixed(const fr_dvm_mixed_mesh *mesh, int order, con
         }
     }
     h->hmin = hmin;
-    // face-point matching with the neighbours
-    std::vector<int64_t> tnb((size_t)mx.nfp, -1);
+    // face-point matching with the neighbours: the neighbour's solution point
+    // at the same position
+    std::vector<int64_t> pnb((size_t)mx.nfp, -1);
     const double tol = 1e-9 * (1.0 + scale);
     for (int64_t e = 0; e < ne; ++e) {
         const int t = mesh->elem_type[e];
@@ -593,7 +702,7 @@ extern "C" int fr_dvm_create_mixed(const fr_dvm_mixed_mesh *mesh, int order, con
                 }
                 if (hit < 0) return bail(h->fail(FR_DVM_EINVAL, "face points of element " + std::to_string(e) +
                                                                      " face " + std::to_string(f) + " have no match"));
-                tnb[s] = hit;
+                pnb[s] = mx.poff[n2] + T2.fnode[hit - mx.toff[n2]];
             }
         }
     }
@@ -603,16 +712,21 @@ extern "C" int fr_dvm_create_mixed(const fr_dvm_mixed_mesh *mesh, int order, con
     h->nfp = 0;
     h->ncomp = 1;
     if ((rc = finish_create(h, wq))) return bail(rc);
-    if ((rc = dput(h, &mx.d_poff, mx.poff)) || (rc = dput(h, &mx.d_toff, mx.toff)) || (rc = dput(h, &mx.d_tnb, tnb)) ||
+    if ((rc = dput(h, &mx.d_poff, mx.poff)) || (rc = dput(h, &mx.d_toff, mx.toff)) || (rc = dput(h, &mx.d_pnb, pnb)) ||
         (rc = dput(h, &mx.d_geo, geo)) || (rc = dput(h, &mx.d_geof, to_f32(geo))))
         return bail(rc);
     for (int t = 0; t < 3; ++t) {
         MixType &T = mx.t[t];
         if (T.elems.empty()) continue;
-        if ((rc = dput(h, &T.d_D, T.D)) || (rc = dput(h, &T.d_lift, T.lift)) || (rc = dput(h, &T.d_Df, to_f32(T.D))) ||
-            (rc = dput(h, &T.d_liftf, to_f32(T.lift))) || (rc = dput(h, &T.d_elems, T.elems)) ||
-            (rc = dput(h, &T.d_fnode, T.fnode)) || (rc = dput(h, &T.d_ffac, T.ffac)))
+        if ((rc = dput(h, &T.d_elems, T.elems))) return bail(rc);
+        if (t == FR_DVM_HEX) {
+            if ((rc = dput(h, &T.d_D, T.D)) || (rc = dput(h, &T.d_lift, T.lift)) || (rc = dput(h, &T.d_Df, to_f32(T.D))) ||
+                (rc = dput(h, &T.d_liftf, to_f32(T.lift))) || (rc = dput(h, &T.d_fnode, T.fnode)) ||
+                (rc = dput(h, &T.d_ffac, T.ffac)))
+                return bail(rc);
+        } else if ((rc = dput(h, &T.d_stream, T.stream)) || (rc = dput(h, &T.d_streamf, to_f32(T.stream)))) {
             return bail(rc);
+        }
     }
     *out = h;
     return FR_DVM_OK;
@@ -623,11 +737,11 @@ namespace frdvm {
 void free_mixed(fr_dvm *h) {
     if (!h->mx) return;
     Mixed &mx = *h->mx;
-    void *ptrs[] = {mx.d_poff, mx.d_toff, mx.d_tnb, mx.d_geo, mx.d_geof};
+    void *ptrs[] = {mx.d_poff, mx.d_toff, mx.d_pnb, mx.d_geo, mx.d_geof};
     for (void *p : ptrs)
         if (p) hipFree(p);
     for (MixType &T : mx.t) {
-        void *tp[] = {T.d_D, T.d_lift, T.d_Df, T.d_liftf, T.d_elems, T.d_fnode, T.d_ffac};
+        void *tp[] = {T.d_D, T.d_lift, T.d_Df, T.d_liftf, T.d_elems, T.d_fnode, T.d_ffac, T.d_stream, T.d_streamf};
         for (void *p : tp)
             if (p) hipFree(p);
     }

@@ -676,8 +676,9 @@ extern "C" int fr_dvm_set_params(fr_dvm_t h, const fr_dvm_params *p) {
     size_t tes = p->precision != FR_DVM_FP64 ? sizeof(float) : sizeof(double);
     int64_t npts = h->ne * h->ns;
     int64_t nu = h->vg.nu * h->ncomp;  // state values per point
-    // trace values per buffer
-    const size_t trn = h->mx ? (size_t)h->mx->nfp * h->vg.nu : (size_t)(h->ne * h->tl.elem);
+    // trace values per buffer (mixed meshes store no traces: the two buffers
+    // take the stage values, see stage_args)
+    const size_t trn = h->mx ? (size_t)npts * h->vg.nu : (size_t)(h->ne * h->tl.elem);
     int rc;
     if (realloc_all) {
         if (h->d_reg) { hipFree(h->d_reg); h->owned_bytes -= npts * nu * es_old; h->d_reg = nullptr; }
