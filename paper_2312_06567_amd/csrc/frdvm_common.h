@@ -125,9 +125,9 @@ struct fr_dvm {
     // device: geometry and tables
     double *d_gfac = nullptr;    // [ne][3]
     // general (curved / re-oriented / bounded) meshes, axis_mode == false
-    double *d_S = nullptr;       // [ne][ns][3][3] S[d][c] = (|J| J^-1)_dc, rows a^d = |J| grad xi_d
+    double *d_S = nullptr;       // [ne][3][nfp][n][3] a^d = |J| grad xi_d at the points of each line of direction d
     double *d_ijac = nullptr;    // [ne][ns] 1/|J|
-    double *d_nf = nullptr;      // [ne][6][nfp][3] outward area-scaled normal at the flux points
+    double *d_nf = nullptr;      // [ne][6][nfp][4] outward area-scaled normal at the flux points, margin of u.n
     float *d_Sf = nullptr, *d_ijacf = nullptr, *d_nff = nullptr;  // FP32 copies
     int32_t *d_conn = nullptr;   // [ne][6][4] neighbour, its face, orientation code, bc tag
     int32_t *d_wall = nullptr;   // [nwall] e*6+face of every diffuse-wall face

@@ -17,11 +17,13 @@
 // Work decomposition: one wave per (element, 64 velocities), one lane per
 // velocity; the element's metrics and normals are read through the scalar
 // cache, its equilibrium records staged in LDS.  A lane keeps its velocity's
-// N^3 values and their residual in a private LDS column; the derivative and
+// N^3 values in registers and their residual in a private LDS column; the derivative and
 // the face terms are formed line by line, direction by direction.  Every access to f, the
 // RK registers and the traces is a run of consecutive velocities.  Traces
-// are full (every velocity at every flux point, [e][face][point][k]); a lane
-// reads the neighbour trace only where its velocity enters the element.
+// have a place for every velocity at every flux point, [e][face][point][k]; a
+// lane stores one only where its velocity leaves the element there (within a
+// margin for rounding), which is where the neighbour, the wall and the mirror
+// image read it.
 // The per-point moments are a separate reduction over the velocity axis.
 #include <hip/hip_runtime.h>
 
@@ -56,9 +58,9 @@ struct GenArgs {
     const double *gfp;   // [npts] the pair's G equilibrium factor delta theta / 2
     const double *wax;   // [3][64] 1-D trapezoid weights
     const double *wJ;    // [ne][ns] Gauss weight x |J| (positivity limiter)
-    const double *S;     // [ne][ns][3][3]
+    const double *S;     // [ne][3][nfp][n][3] a^d at the points of each line of direction d
     const double *ijac;  // [ne][ns]
-    const double *nf;    // [ne][6][nfp][3]
+    const double *nf;    // [ne][6][nfp][4] normal, margin of u.n
     const float *Sf, *ijacf, *nff;  // the same in FP32
     const int32_t *conn; // [ne][6][4]
     const int32_t *wall; // [nwall]
@@ -145,7 +147,11 @@ __device__ __forceinline__ int nbr_point(int o, int a, int b) {
     return x + N * y;
 }
 
-// Traces of f at every flux point of the element, every velocity.
+// Traces of f, stored at the flux points where one of the wave's velocities
+// leaves the element (u.n above minus the margin).  The decision is the
+// wave's, since a row stored in part costs more than a whole one: with every
+// value stored the prime pass of the Mach-8 O-grid (p = 2, FP32) takes 1.82
+// ms, with each lane storing for itself 2.66, so 1.57.
 template <typename Real, int P>
 __global__ __launch_bounds__(kGBlock) void k_gen_traces(const GenArgs A, const Real *__restrict__ f,
                                                          Real *__restrict__ tr) {
@@ -160,19 +166,30 @@ __global__ __launch_bounds__(kGBlock) void k_gen_traces(const GenArgs A, const R
     Real v[NS];
 #pragma unroll
     for (int s = 0; s < NS; ++s) v[s] = ldo(fe + s * nu, ko);
+    int iv[3];
+    split_k(A.vg, k >= A.nu ? k - A.nu : k, iv);
+    const Real u0 = (Real)node_u(A.vg, 0, iv[0]), u1 = (Real)node_u(A.vg, 1, iv[1]), u2 = (Real)node_u(A.vg, 2, iv[2]);
+    const Real ul1 = (u0 < 0 ? -u0 : u0) + (u1 < 0 ? -u1 : u1) + (u2 < 0 ? -u2 : u2);
+    const cptr<Real> gN = metrics(A, Real(0)).nf + e * 6 * NFP * 4;
     Real *te = tr + e * 6 * NFP * nu;
 #pragma unroll
     for (int face = 0; face < 6; ++face) {
         const int d = face / 2, side = face & 1;
+        // (the decisions of a face first: a branch around each value would
+        // wait for its own scalar loads)
+        uint32_t kept = 0;
+        Real t[NFP];
 #pragma unroll
-        for (int b = 0; b < N; ++b)
+        for (int q = 0; q < NFP; ++q) {
+            const cptr<Real> n4 = gN + 4 * (face * NFP + q);
+            kept |= __ballot(n4[0] * u0 + n4[1] * u1 + n4[2] * u2 + n4[3] * ul1 > Real(0)) ? 1u << q : 0u;
+            t[q] = Real(0);
 #pragma unroll
-            for (int a = 0; a < N; ++a) {
-                Real t = Real(0);
+            for (int m = 0; m < N; ++m) t[q] += op.lam[side][m] * v[line_pt<N>(d, q % N, q / N, m)];
+        }
 #pragma unroll
-                for (int m = 0; m < N; ++m) t += op.lam[side][m] * v[line_pt<N>(d, a, b, m)];
-                sto(te + (face * NFP + a + N * b) * nu, ko, t);
-            }
+        for (int q = 0; q < NFP; ++q)
+            if ((kept >> q) & 1) sto(te + (face * NFP + q) * nu, ko, t[q]);
     }
 }
 
@@ -259,7 +276,7 @@ __global__ __launch_bounds__(kGBlock) void k_gen_wall(const GenArgs A, const Rea
     __shared__ double red[kGBlock / 64][2];
     const int64_t fid = A.wall[blockIdx.x / NFP];
     const int fp = blockIdx.x % NFP;
-    const double *nv = A.nf + (fid * NFP + fp) * 3;
+    const double *nv = A.nf + (fid * NFP + fp) * 4;
     const double n0 = nv[0], n1 = nv[1], n2 = nv[2];
     const Real *t = tr + (fid * NFP + fp) * (int64_t)A.nut;  // F part of the trace
     double out = 0.0, in = 0.0;
@@ -295,35 +312,105 @@ __global__ __launch_bounds__(kGBlock) void k_gen_wall(const GenArgs A, const Rea
     }
 }
 
+// What a lane needs to find its exterior values (load_ext).
+template <typename Real>
+struct ExtArgs {
+    cptr<int32_t> conn;   // the element's [6][4]
+    cptr<double> rwall;   // wall densities of its faces [6][nfp]
+    cptr<Real> gN;        // its normals
+    const double *finf, *mwall;
+    const Real *tin;
+    double gw;            // wall factor of the lane's component
+    int64_t e, nu;
+    uint32_t ko, k8, kv8;
+    Real u0, u1, u2, ul1;
+};
+
+// u.n and the exterior values of both faces of axis d, requested together
+// (the connectivity through the scalar cache: a vector load of it would put
+// its latency before every direction's requests).  km0..2: the node mirrored
+// in each axis (passed by value: a choice between members of X would keep X in
+// scratch memory).  KEEP: kept gets the (wave-uniform) bits of the flux points
+// whose traces the wave has to store.
+template <typename Real, int N, bool KEEP>
+__device__ __forceinline__ void load_ext(const ExtArgs<Real> &X, int d, int km0, int km1, int km2,
+                                         Real (&un)[2][N * N], Real (&ext)[2][N * N], uint64_t (&kept)[2]) {
+    constexpr int NFP = N * N;
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+        const int face = 2 * d + side;
+        const cptr<int32_t> c = X.conn + face * 4;
+        const int32_t nb = c[0], nface = c[1], orient = c[2], bc = c[3];
+        const cptr<Real> nv = X.gN + face * NFP * 4;
+#pragma unroll
+        for (int q = 0; q < NFP; ++q)
+            un[side][q] = nv[4 * q] * X.u0 + nv[4 * q + 1] * X.u1 + nv[4 * q + 2] * X.u2;
+        if constexpr (KEEP) {
+#pragma unroll
+            for (int q = 0; q < NFP; ++q) {
+                const int b = face * NFP + q;
+                const uint64_t bit = __ballot(un[side][q] + nv[4 * q + 3] * X.ul1 > Real(0)) ? 1ull << (b & 63) : 0ull;
+                if (b < 64) kept[0] |= bit;
+                else kept[1] |= bit;
+            }
+        }
+        if (nb >= 0) {
+            const Real *tn = X.tin + ((int64_t)nb * 6 + nface) * NFP * X.nu;
+#pragma unroll
+            for (int q = 0; q < NFP; ++q)
+                ext[side][q] =
+                    un[side][q] < Real(0) ? ldo(tn + nbr_point<N>(orient, q % N, q / N) * X.nu, X.ko) : Real(0);
+        } else if (bc == 1) {
+            const Real fi = (Real)ldo(X.finf, X.k8);
+#pragma unroll
+            for (int q = 0; q < NFP; ++q) ext[side][q] = fi;
+        } else if (bc == 3) {
+            // specular: the own trace at the velocity mirrored in the face's
+            // axis (orient holds the axis), same component
+            const uint32_t kmo = (uint32_t)(orient == 0 ? km0 : (orient == 1 ? km1 : km2)) * (uint32_t)sizeof(Real);
+            const Real *to = X.tin + (X.e * 6 + face) * NFP * X.nu;
+#pragma unroll
+            for (int q = 0; q < NFP; ++q) ext[side][q] = un[side][q] < Real(0) ? ldo(to + q * X.nu, kmo) : Real(0);
+        } else {
+            const double mw = ldo(X.mwall, X.kv8) * X.gw;
+            const cptr<double> rw = X.rwall + face * NFP;
+#pragma unroll
+            for (int q = 0; q < NFP; ++q) ext[side][q] = (Real)(rw[q] * mw);
+        }
+    }
+}
+
 // One wave per (element, 64 velocities).  Each lane keeps its velocity's N^3
-// residual accumulators in its own LDS column (lane-private: no barrier
-// between the phases), and its N^3 stage values in registers (p <= 2: the
-// loops over directions, lines and flux points unrolled, so every value has
-// a fixed register; the LDS left per wave admits 3 (FP32) / 2 (FP64) waves
-// per SIMD, which the register target matches) or in a second LDS column
-// (p = 3: loops rolled, the registers holding only the current line).  (With the accumulators in
-// registers and the direction loop unrolled, p = 2 needs 175 VGPRs in FP32
-// and p = 3 all 256 with scratch: no occupancy is gained.)
+// stage values in registers (all loops over directions, lines and flux points
+// unrolled, so every value has a fixed register) and its N^3 residual
+// accumulators in its own LDS column (lane-private: no barrier between the
+// phases; in registers too, p = 2 would need 175 in FP32).  The register
+// targets are what LDS admits: 3 (FP32) / 2 (FP64) waves per SIMD at p <= 2,
+// 2 / 1 at p = 3.  (With the values of p = 3 in a second LDS column, loops
+// rolled, LDS held 4 / 2 waves per CU: 3.07 / 6.60 ms per stage at 256
+// elements, 20^3 velocities, against 1.33 / 2.62.)  What bounds it: half
+// VALU issue, half HBM (3.3-4.0 TB/s); p = 2 FP32, 2304 elements, 24^3,
+// limiter on: 5.99 -> 5.39 ms per stage with the exterior values requested a
+// direction ahead, the connectivity and the metrics of whole lines through
+// the scalar cache, one random-number hash per lane instead of per value, and
+// the traces of waves that only enter left out.
 template <typename Real, int P>
-constexpr bool gen_freg() {
-    return P <= 2;
+constexpr int gen_waves() {
+    return P == 3 ? (sizeof(Real) == 4 ? 2 : 1) : (sizeof(Real) == 4 ? 3 : 2);
+}
+// Whether the next direction's exterior values are requested ahead: where
+// that costs no wave per SIMD (at p = 2 it does in FP64 and for the residual
+// alone: 1.44 -> 1.46 and 0.79 -> 0.84 ms at 1024 elements, 20^3).
+template <typename Real, int P, int MODE>
+constexpr bool gen_ahead() {
+    return P == 1 || (P == 2 && sizeof(Real) == 4 && MODE == GMODE_STAGE);
 }
 template <typename Real, int P, int MODE>
-__global__ __launch_bounds__(kGWave) __attribute__((amdgpu_waves_per_eu(gen_freg<Real, P>() ? (sizeof(Real) == 4 ? 3 : 2) : 1))) void
+__global__ __launch_bounds__(kGWave) __attribute__((amdgpu_waves_per_eu(gen_waves<Real, P>()))) void
 k_gen_stage(const GenArgs A) {
     constexpr int N = P + 1, NS = N * N * N, NFP = N * N;
     constexpr bool STAGE = MODE == GMODE_STAGE;
-    constexpr int CHF = NS <= 27 ? NS : 2 * NFP;  // values requested together
-    constexpr bool FREG = gen_freg<Real, P>();
-    constexpr bool EARLY_X = STAGE && NS <= 27 && !FREG;
-    constexpr int UNR = FREG ? 64 : 1;  // unroll of the loops that index the stage values
-    __shared__ Real sf[FREG ? 1 : NS][kGWave];
-    Real fv[FREG ? NS : 1];
-    // the lane's stage value at point s (s a compile-time index where FREG)
-    auto F = [&](int s) -> Real & {
-        if constexpr (FREG) return fv[s];
-        else return sf[s][threadIdx.x];
-    };
+    Real fv[NS];  // the lane's stage value
     __shared__ Real sa[NS][kGWave];
     __shared__ double sEb[STAGE ? NS * 8 : 1];
     __shared__ double sEv[STAGE ? NS * 3 : 1];
@@ -347,8 +434,10 @@ k_gen_stage(const GenArgs A) {
             sEv[s * 3] = q[EQ_V];
             sEv[s * 3 + 1] = q[EQ_V + 1];
             sEv[s * 3 + 2] = q[EQ_V + 2];
-            const double gf = A.ncomp == 2 ? A.gfp[e * NS + s] : 1.0;
-            sLg[s] = gf > 0.0 ? log(gf) : -1000.0;
+            if (A.ncomp == 2) {
+                const double gf = A.gfp[e * NS + s];
+                sLg[s] = gf > 0.0 ? log(gf) : -1000.0;
+            }
         }
     }
     __syncthreads();
@@ -356,7 +445,7 @@ k_gen_stage(const GenArgs A) {
 
     const GOps<Real> &op = gops<Real>(A);
     const Metrics<Real> G = metrics(A, Real(0));
-    const cptr<Real> gS = G.S + e * NS * 9, gJ = G.ijac + e * NS, gN = G.nf + e * 6 * NFP * 3;
+    const cptr<Real> gS = G.S + e * NS * 9, gJ = G.ijac + e * NS, gN = G.nf + e * 6 * NFP * 4;
     const int64_t nu = A.nut;  // stride of a solution point
     const int comp = k >= A.nu, kv = k - comp * A.nu;  // component, velocity node
     int iv[3];
@@ -366,24 +455,11 @@ k_gen_stage(const GenArgs A) {
     const int64_t eoff = e * NS * nu;
     const uint32_t ko = (uint32_t)k * (uint32_t)sizeof(Real), k8 = (uint32_t)k * 8u, kv8 = (uint32_t)kv * 8u;
     const Real *fe = reinterpret_cast<const Real *>(A.sa.f) + eoff;
-    // all of f (two layers at a time at p = 3) requested together
-#pragma unroll 1
-    for (int s0 = 0; s0 < NS; s0 += CHF) {
-        Real v[CHF];
 #pragma unroll
-        for (int r = 0; r < CHF; ++r) v[r] = ldo(fe + (s0 + r) * nu, ko);
-#pragma unroll
-        for (int r = 0; r < CHF; ++r) F(s0 + r) = v[r];
-    }
-    // the second RK register of the stage, requested now (p <= 2) so that
-    // the FR work covers its latency
+    for (int s = 0; s < NS; ++s) fv[s] = ldo(fe + s * nu, ko);
+    // the second RK register of the stage
     const bool useX = STAGE && (A.sa.scheme == 0 ? A.sa.alpha != 0.0 : A.sa.lsA != 0.0);
     const Real *XE = (A.sa.scheme == 0 ? reinterpret_cast<const Real *>(A.sa.fn) : reinterpret_cast<const Real *>(A.sa.dF)) + eoff;
-    Real xe[EARLY_X ? NS : 1];
-    if constexpr (EARLY_X) {
-#pragma unroll
-        for (int s = 0; s < NS; ++s) xe[s] = useX ? ldo(XE + s * nu, ko) : Real(0);
-    }
     // Divergence and interface corrections, direction by direction: along
     // each line of direction d the transformed flux F_d = (a^d . u) f, its
     // derivative, and the corrections of the line's two flux points on the
@@ -391,60 +467,53 @@ k_gen_stage(const GenArgs A) {
     // is then written once per direction (the first direction initialises
     // it), so no accumulator waits on another update of itself.
     const Real *tin = reinterpret_cast<const Real *>(A.sa.tr_in);
-#pragma unroll UNR
+    const Real ul1 = (u0 < 0 ? -u0 : u0) + (u1 < 0 ? -u1 : u1) + (u2 < 0 ? -u2 : u2);
+    uint64_t kept[2] = {0, 0};  // flux points (face * NFP + q) whose traces the wave stores
+    const ExtArgs<Real> X = {(cptr<int32_t>)A.conn + e * 24, (cptr<double>)A.rw + e * 6 * NFP, gN, A.finf, A.mw, tin,
+                             comp ? A.gwall : 1.0, e, nu, ko, k8, kv8, u0, u1, u2, ul1};
+    const int km0 = k + A.vg.nv[0] - 1 - 2 * iv[0], km1 = k + (A.vg.nv[1] - 1 - 2 * iv[1]) * A.vg.nv[0],
+              km2 = k + (A.vg.nv[2] - 1 - 2 * iv[2]) * (A.vg.nv[0] * A.vg.nv[1]);
+    // the next direction's exterior values, and before the last direction the
+    // first layer's second-register values, are requested while a direction
+    // is computed
+    constexpr bool AHEAD = gen_ahead<Real, P, MODE>();
+    Real unx[2][2][NFP], exx[2][2][NFP];
+    if constexpr (AHEAD) load_ext<Real, N, STAGE>(X, 0, km0, km1, km2, unx[0], exx[0], kept);
+    Real xv[2][NFP];
+    auto load_x = [&](int s0, Real(&x)[NFP]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < NFP; ++r) x[r] = useX ? ldo(XE + (s0 + r) * nu, ko) : Real(0);
+    };
+#pragma unroll
     for (int d = 0; d < 3; ++d) {
-        if constexpr (FREG) {
-            // one direction's exterior values in registers at a time
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        // the exterior values of both faces of the axis, requested together
         Real un[2][NFP], ext[2][NFP];
+        // one direction's exterior values (and the next one's) in registers at a time
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (AHEAD) {
+            if (d < 2) load_ext<Real, N, STAGE>(X, d + 1, km0, km1, km2, unx[(d + 1) & 1], exx[(d + 1) & 1], kept);
+            else if (STAGE) load_x(0, xv[0]);
 #pragma unroll
-        for (int side = 0; side < 2; ++side) {
-            const int face = 2 * d + side;
-            const int32_t *c = A.conn + (e * 6 + face) * 4;
-            const int32_t nb = c[0], nface = c[1], orient = c[2], bc = c[3];
-            const cptr<Real> nv = gN + face * NFP * 3;
+            for (int side = 0; side < 2; ++side)
 #pragma unroll
-            for (int q = 0; q < NFP; ++q)
-                un[side][q] = nv[3 * q] * u0 + nv[3 * q + 1] * u1 + nv[3 * q + 2] * u2;
-            if (nb >= 0) {
-                const Real *tn = tin + ((int64_t)nb * 6 + nface) * NFP * nu;
-#pragma unroll
-                for (int q = 0; q < NFP; ++q)
-                    ext[side][q] =
-                        un[side][q] < Real(0) ? ldo(tn + nbr_point<N>(orient, q % N, q / N) * nu, ko) : Real(0);
-            } else if (bc == 1) {
-                const Real fi = (Real)ldo(A.finf, k8);
-#pragma unroll
-                for (int q = 0; q < NFP; ++q) ext[side][q] = fi;
-            } else if (bc == 3) {
-                // specular: the own trace at the velocity mirrored in the
-                // face's axis (orient holds the axis)
-                const int str = orient == 0 ? 1 : (orient == 1 ? A.vg.nv[0] : A.vg.nv[0] * A.vg.nv[1]);
-                const int ia = orient == 0 ? iv[0] : (orient == 1 ? iv[1] : iv[2]);
-                const int km = k + (A.vg.nv[orient] - 1 - 2 * ia) * str;  // same component
-                const uint32_t kmo = (uint32_t)km * (uint32_t)sizeof(Real);
-                const Real *to = tin + (e * 6 + face) * NFP * nu;
-#pragma unroll
-                for (int q = 0; q < NFP; ++q) ext[side][q] = un[side][q] < Real(0) ? ldo(to + q * nu, kmo) : Real(0);
-            } else {
-                const double mw = ldo(A.mw, kv8) * (comp ? A.gwall : 1.0);
-#pragma unroll
-                for (int q = 0; q < NFP; ++q) ext[side][q] = (Real)(A.rw[(e * 6 + face) * NFP + q] * mw);
-            }
+                for (int q = 0; q < NFP; ++q) {
+                    un[side][q] = unx[d & 1][side][q];
+                    ext[side][q] = exx[d & 1][side][q];
+                }
+        } else {
+            load_ext<Real, N, STAGE>(X, d, km0, km1, km2, un, ext, kept);
         }
 #pragma unroll
         for (int q = 0; q < NFP; ++q) {
             const int a = q % N, b = q / N;
             int pts[N];
             Real fl[N], Fd[N];
+            const cptr<Real> Sq = gS + (d * NFP + q) * N * 3;
 #pragma unroll
             for (int m = 0; m < N; ++m) {
                 pts[m] = line_pt<N>(d, a, b, m);
-                fl[m] = F(pts[m]);
-                const cptr<Real> Sm = gS + pts[m] * 9 + 3 * d;
+                fl[m] = fv[pts[m]];
+                const cptr<Real> Sm = Sq + m * 3;
                 Fd[m] = (Sm[0] * u0 + Sm[1] * u1 + Sm[2] * u2) * fl[m];
             }
             Real acc[N];
@@ -484,19 +553,22 @@ k_gen_stage(const GenArgs A) {
     // element mean and smallest value are known
     const bool limit = A.sa.positivity != 0;
     const cptr<double> gW = (cptr<double>)A.wJ + e * NS;
-    double lim_int = 0.0, lim_w = 0.0;
     Real lim_min = Real(0);
+    // random bits of the stochastic rounding: one hash per lane, a xorshift
+    // step per value
+    uint32_t rs = sizeof(Real) == 4 ? round_bits(A.sa.seed, (uint32_t)(e * NS), (uint32_t)k) | 1u : 0u;
 #pragma unroll
     for (int s0 = 0; s0 < NS; s0 += NFP) {
-        // (p = 3) the layer's second-register values requested together
-        Real xv[NFP];
-#pragma unroll
-        for (int r = 0; r < NFP; ++r)
-            xv[r] = EARLY_X ? xe[EARLY_X ? s0 + r : 0] : (useX ? ldo(XE + (s0 + r) * nu, ko) : Real(0));
+        // a layer's second-register values requested together
+        if constexpr (AHEAD) {
+            if (s0 + NFP < NS) load_x(s0 + NFP, xv[(s0 / NFP + 1) & 1]);
+        } else {
+            load_x(s0, xv[(s0 / NFP) & 1]);
+        }
 #pragma unroll
         for (int r = 0; r < NFP; ++r) {
             const int s = s0 + r;
-            const Real fq = F(s);
+            const Real fq = fv[s];
             Real L = -sa[s][lane] * gJ[s];
             if (collide) {
                 const double *bq = &sEb[s * 8];
@@ -516,42 +588,32 @@ k_gen_stage(const GenArgs A) {
             double fod;
             if (A.sa.scheme == 0) {
                 fod = A.sa.beta * ((double)fq + (double)(dt * L));
-                if (useX) fod = fma(A.sa.alpha, (double)xv[r], fod);
+                if (useX) fod = fma(A.sa.alpha, (double)xv[(s0 / NFP) & 1][r], fod);
             } else {
                 Real dd = dt * L;
-                if (useX) dd += (Real)A.sa.lsA * xv[r];
+                if (useX) dd += (Real)A.sa.lsA * xv[(s0 / NFP) & 1][r];
                 if (A.sa.keep_dF) sto(dFE + s * nu, ko, dd);
                 fod = fma(A.sa.lsB, (double)dd, (double)fq);
             }
             Real fo;
-            if constexpr (sizeof(Real) == 4)
-                fo = round_stochastic(fod, round_bits(A.sa.seed, (uint32_t)(e * NS + s), (uint32_t)k));
-            else
+            if constexpr (sizeof(Real) == 4) {
+                rs = xorshift32(rs);
+                fo = round_stochastic(fod, rs);
+            } else {
                 fo = (Real)fod;
-            F(s) = fo;
+            }
+            fv[s] = fo;
+            lim_min = s == 0 ? fo : (fo < lim_min ? fo : lim_min);
             sto(outE + s * nu, ko, fo);
-            if constexpr (FREG) {
-                // two points' chains in flight at a time
-                if (r % 2 == 1) {
-                    asm volatile("" ::: "memory");
-                    __builtin_amdgcn_sched_barrier(0);
-                }
+            // two points' chains in flight at a time
+            if (r % 2 == 1) {
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
     }
-    if (limit) {
-        // the result's element integral and smallest value at the solution points
-#pragma unroll UNR
-        for (int s = 0; s < NS; ++s) {
-            Real fo = F(s);
-            asm volatile("" : "+v"(fo));  // (converted here, not kept in FP64 from the stage loop)
-            lim_int = fma(gW[s], (double)fo, lim_int);
-            lim_w += gW[s];
-            lim_min = s == 0 ? fo : (fo < lim_min ? fo : lim_min);
-        }
-    }
-    // Traces of the result at every flux point; with the positivity limiter
-    // the same pass finds the smallest value of the element polynomial at its
+    // Traces of the result where the velocity leaves; with the positivity limiter
+    // the same pass (over every flux point) finds the smallest value of the element polynomial at its
     // solution and flux points.  Where that is negative (rare: f is positive
     // almost everywhere) the lane scales its polynomial about the element mean
     // (weights Gauss x |J|), so that the smallest value becomes zero and the
@@ -559,33 +621,38 @@ k_gen_stage(const GenArgs A) {
     // the values and traces again.
     Real *te = reinterpret_cast<Real *>(A.sa.tr_out) + e * 6 * NFP * nu;
     auto trace_pass = [&](bool store, bool find_min) {
-#pragma unroll UNR
+#pragma unroll
         for (int face = 0; face < 6; ++face) {
             const int d = face / 2, side = face & 1;
-            if constexpr (FREG) {
-                // one face's traces in registers at a time
-                asm volatile("" ::: "memory");
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll UNR
+            // one face's traces in registers at a time
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
             for (int q = 0; q < NFP; ++q) {
                 const int a = q % N, b = q / N;
                 Real t = Real(0);
 #pragma unroll
-                for (int m = 0; m < N; ++m) t += op.lam[side][m] * F(line_pt<N>(d, a, b, m));
-                if (store) sto(te + (face * NFP + q) * nu, ko, t);
+                for (int m = 0; m < N; ++m) t += op.lam[side][m] * fv[line_pt<N>(d, a, b, m)];
+                const int pt = face * NFP + q;
+                if (store && ((kept[pt >> 6] >> (pt & 63)) & 1)) sto(te + pt * nu, ko, t);
                 if (find_min) lim_min = t < lim_min ? t : lim_min;
             }
         }
     };
     if (A.do_traces || limit) trace_pass(A.do_traces, limit);
     if (limit && lim_min < Real(0)) {
+        double lim_int = 0.0, lim_w = 0.0;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            lim_int = fma(gW[s], (double)fv[s], lim_int);
+            lim_w += gW[s];
+        }
         const double mean = lim_int / lim_w;
         const double th = mean > 0.0 ? mean / (mean - (double)lim_min) : 0.0;
-#pragma unroll UNR
+#pragma unroll
         for (int s = 0; s < NS; ++s) {
-            const Real v = (Real)fma(th, (double)F(s) - mean, mean);
-            F(s) = v;
+            const Real v = (Real)fma(th, (double)fv[s] - mean, mean);
+            fv[s] = v;
             sto(outE + s * nu, ko, v);
         }
         if (A.do_traces) trace_pass(true, false);

@@ -1194,10 +1194,13 @@ __global__ __launch_bounds__(64 * kKnElems) void k_kn_gll(NewtonArgs A, Ops1D op
         d2 += ops.D[l * n + m] * srho[w][i + n * (j + n * m)];
     }
     if (S) {  // general element: grad = (1/|J|) sum_d a^d d/dxi_d
-        const double *a = S + pt * 9;
-        const double g0 = ijac[pt] * (a[0] * d0 + a[3] * d1 + a[6] * d2);
-        const double g1 = ijac[pt] * (a[1] * d0 + a[4] * d1 + a[7] * d2);
-        const double g2 = ijac[pt] * (a[2] * d0 + a[5] * d1 + a[8] * d2);
+        // (stored line by line of each direction)
+        const double *a = S + (e * 3 * ns + (j + n * l) * n + i) * 3;
+        const double *b = S + ((e * 3 + 1) * ns + (i + n * l) * n + j) * 3;
+        const double *c = S + ((e * 3 + 2) * ns + (i + n * j) * n + l) * 3;
+        const double g0 = ijac[pt] * (a[0] * d0 + b[0] * d1 + c[0] * d2);
+        const double g1 = ijac[pt] * (a[1] * d0 + b[1] * d1 + c[1] * d2);
+        const double g2 = ijac[pt] * (a[2] * d0 + b[2] * d1 + c[2] * d2);
         d0 = g0;
         d1 = g1;
         d2 = g2;

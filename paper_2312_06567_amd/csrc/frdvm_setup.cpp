@@ -336,7 +336,10 @@ int setup_general(fr_dvm *h, const fr_dvm_mesh *mesh, std::vector<double> &wq3J)
                     if (!(J > 0)) return h->fail(FR_DVM_EINVAL, "non-positive Jacobian in element " + std::to_string(e));
                     const int64_t pt = e * ns + s;
                     for (int d = 0; d < 3; ++d) {
-                        for (int c = 0; c < 3; ++c) S[pt * 9 + 3 * d + c] = a[d][c];
+                        // line by line of each direction, as the stage kernel reads it
+                        const int line = d == 0 ? j + n * l : (d == 1 ? i + n * l : i + n * j);
+                        const int at = d == 0 ? i : (d == 1 ? j : l);
+                        for (int c = 0; c < 3; ++c) S[((e * 3 + d) * ns + line * n + at) * 3 + c] = a[d][c];
                         hmin = std::min(hmin, 2.0 * J / std::sqrt(a[d][0] * a[d][0] + a[d][1] * a[d][1] + a[d][2] * a[d][2]));
                     }
                     h->h_detJ[pt] = J;
@@ -432,13 +435,26 @@ int setup_general(fr_dvm *h, const fr_dvm_mesh *mesh, std::vector<double> &wq3J)
         return rc;
     if ((rc = dev_alloc(h, &h->d_ijac, ijac.size())) || (rc = upload(h, h->d_ijac, ijac.data(), ijac.size() * sizeof(double))))
         return rc;
-    if ((rc = dev_alloc(h, &h->d_nf, nf.size())) || (rc = upload(h, h->d_nf, nf.data(), nf.size() * sizeof(double))))
+    // normals with a margin in the fourth place: |n|_1 times a bound on how far
+    // (relative to |n|_1 |u|_1) the rounded u.n of the two sides of a face may
+    // differ, the rounding of three products and the gap of the two normals
+    // allowed above; a trace is stored for every velocity that leaves within it
+    std::vector<double> nf4(nf.size() / 3 * 4);
+    std::vector<float> nff4(nf4.size());
+    for (size_t i = 0; i < nf.size() / 3; ++i) {
+        const double l1 = std::fabs(nf[3 * i]) + std::fabs(nf[3 * i + 1]) + std::fabs(nf[3 * i + 2]);
+        for (int c = 0; c < 4; ++c) {
+            nf4[4 * i + c] = c < 3 ? nf[3 * i + c] : 1e-8 * l1;
+            nff4[4 * i + c] = (float)(c < 3 ? nf[3 * i + c] : 1e-5 * l1);
+        }
+    }
+    if ((rc = dev_alloc(h, &h->d_nf, nf4.size())) || (rc = upload(h, h->d_nf, nf4.data(), nf4.size() * sizeof(double))))
         return rc;
     {
-        std::vector<float> Sf(S.begin(), S.end()), jf(ijac.begin(), ijac.end()), nff(nf.begin(), nf.end());
+        std::vector<float> Sf(S.begin(), S.end()), jf(ijac.begin(), ijac.end());
         if ((rc = dev_alloc(h, &h->d_Sf, Sf.size())) || (rc = upload(h, h->d_Sf, Sf.data(), Sf.size() * sizeof(float))) ||
             (rc = dev_alloc(h, &h->d_ijacf, jf.size())) || (rc = upload(h, h->d_ijacf, jf.data(), jf.size() * sizeof(float))) ||
-            (rc = dev_alloc(h, &h->d_nff, nff.size())) || (rc = upload(h, h->d_nff, nff.data(), nff.size() * sizeof(float))))
+            (rc = dev_alloc(h, &h->d_nff, nff4.size())) || (rc = upload(h, h->d_nff, nff4.data(), nff4.size() * sizeof(float))))
             return rc;
     }
     if ((rc = dev_alloc(h, &h->d_conn, conn.size())) || (rc = upload(h, h->d_conn, conn.data(), conn.size() * sizeof(int32_t))))
