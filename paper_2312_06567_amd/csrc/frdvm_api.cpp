@@ -40,6 +40,13 @@ int guess_mode(fr_dvm *h) {
     return h->prm.guess;
 }
 
+// How the moments a Newton solve is about to read are wanted: on small boxes
+// as the workgroups' parts, added by the solve itself (the learned start's
+// features read the sums).
+int solve_moments(fr_dvm *h, int guess) {
+    return h->axis_mode && h->ne * h->ns <= 16384 && newton_part_ok(h, guess) ? kMomentParts : 1;
+}
+
 }  // namespace
 
 extern "C" int fr_dvm_moments(fr_dvm_t h, const void *f, double *Q, double *totals) {
@@ -88,7 +95,7 @@ extern "C" int fr_dvm_collide(fr_dvm_t h, const void *f, void *S, double *Qp, in
             return h->fail(FR_DVM_EHIP, "memset");
         return FR_DVM_OK;
     }
-    if ((rc = prime(h, f, 0, 1))) return rc;
+    if ((rc = prime(h, f, 0, solve_moments(h, guess_mode(h))))) return rc;
     if ((rc = launch_newton(h, guess_mode(h)))) return rc;
     if ((rc = launch_collide(h, f, S, accumulate))) return rc;
     if (Qp && (rc = launch_prim_out(h, Qp))) return rc;
@@ -171,8 +178,8 @@ extern "C" int fr_dvm_rk_steps(fr_dvm_t h, void *f, double dt, int nsteps) {
     const int collide = h->prm.model != FR_DVM_FREE;
     // traces and moments of the incoming f (afterwards each stage leaves those
     // of its result for the next stage)
-    if ((rc = prime(h, f, 1, collide))) return rc;
     const int guess = guess_mode(h);
+    if ((rc = prime(h, f, 1, collide ? solve_moments(h, guess) : 0))) return rc;
     if (collide && (rc = launch_newton(h, guess))) return rc;
     // Overlap: the elements are taken in two halves (z slabs).  Stage k of
     // half 0, then of half 1, on the handle's stream; as soon as stage k of a
@@ -202,7 +209,7 @@ extern "C" int fr_dvm_rk_steps(fr_dvm_t h, void *f, double dt, int nsteps) {
     for (int k = 0; k < nst; ++k) {
         const int st = k % 3;
         const int last = k == nst - 1;
-        const int traces = last ? 0 : 1, moments = (last || !collide) ? 0 : 1;
+        const int traces = last ? 0 : 1, moments = (last || !collide) ? 0 : (split ? 1 : solve_moments(h, guess));
         if (!split && k > 0 && collide) {
             if ((rc = launch_newton(h, guess))) return rc;
             if (dev) {

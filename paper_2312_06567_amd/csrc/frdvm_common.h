@@ -154,6 +154,7 @@ struct fr_dvm {
     int cur_tr = 0;
     double *d_Q = nullptr;       // [ne*ns][nmom]
     int nsplit[2] = {1, 1};      // workgroups per element of the box kernel: stage and residual, prime pass
+    int q_parts = 0;             // > 1: the last moment pass left its moments as that many parts in d_Qpart
     double *d_Qpart = nullptr;   // [largest nsplit][ne*ns][nmom] their moments (where it is above 1)
     double *d_eq = nullptr;      // [ne*ns][kEqW]
     // [ne][kRefW] element references (FP32 deviation storage): three sets,
@@ -254,7 +255,12 @@ int launch_fr_mixed(fr_dvm *h, int mode, const StageArgs &a, int do_moments);
 int launch_fr_gen(fr_dvm *h, int mode, const StageArgs &a, int do_traces, int do_moments);
 // boundary tables of the current parameters (wall and farfield Maxwellians)
 int gen_boundary_tables(fr_dvm *h);
+// do_moments: 1 into d_Q; kMomentParts: a box whose elements are split over
+// workgroups leaves the parts for the Newton solve to add (h->q_parts), which
+// saves a launch
+constexpr int kMomentParts = 2;
 inline int launch_fr(fr_dvm *h, int mode, const StageArgs &a, int do_traces, int do_moments) {
+    if (do_moments) h->q_parts = 0;
     if (h->mx) return launch_fr_mixed(h, mode, a, do_moments);
     return h->axis_mode ? launch_fr_axis(h, mode, a, do_traces, do_moments)
                         : launch_fr_gen(h, mode, a, do_traces, do_moments);

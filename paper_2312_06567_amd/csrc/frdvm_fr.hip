@@ -914,7 +914,9 @@ int launch_p(fr_dvm *h, int mode, const FrArgs &A) {
         hipLaunchKernelGGL((k_fr_layer<Real, SReal, P, NMOM, MODE_STAGE, ER>), grid, block, 0, h->stream, A);
     else
         hipLaunchKernelGGL((k_fr_layer<Real, SReal, P, NMOM, MODE_RESID, false>), grid, block, 0, h->stream, A);
-    if (A.nsplit > 1 && A.do_moments) {
+    if (A.nsplit > 1 && A.do_moments == kMomentParts) {
+        h->q_parts = A.nsplit;
+    } else if (A.nsplit > 1 && A.do_moments) {
         const int64_t n = ne * h->ns * NMOM;
         hipLaunchKernelGGL(k_moment_parts, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, h->stream, A.Qpart, A.nsplit,
                            A.npts * NMOM, A.sa.e0 * h->ns * NMOM, n, A.sa.Q);

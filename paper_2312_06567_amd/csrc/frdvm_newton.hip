@@ -43,6 +43,8 @@ struct NewtonArgs {
     int nmom;
     const double *wax;   // [3][64]
     const double *Q;     // [npts][nmom]
+    const double *Qpart; // nparts > 1: [nparts][npts][nmom], the moments as parts to be added in order
+    int nparts;
     double *eq;          // [npts][kEqW]
     double *z;           // [npts][5]
     double *prim;        // [npts][5]
@@ -575,8 +577,19 @@ __device__ void write_nonreal(const NewtonArgs &A, int64_t pt) {
     for (int a = 0; a < 5; ++a) A.prim[pt * 5 + a] = 0.0;
 }
 
+// Moment a of point pt from its parts.
+__device__ __forceinline__ double moment_part_sum(const NewtonArgs &A, int64_t pt, int a) {
+    const double *q = A.Qpart + pt * A.nmom + a;
+    const int64_t step = A.npts * A.nmom;
+    double t = q[0];
+#pragma unroll 4
+    for (int s = 1; s < A.nparts; ++s) t += q[s * step];
+    return t;
+}
+
 // Per-point outcome; the counters are aggregated afterwards by k_stats_reduce
-// (per-point atomics on a handful of counters would serialise the kernel).
+// (per-point atomics on a handful of counters would serialise the kernel,
+// also on small solves: 1620 points 31 -> 46 us for the 5 us of that launch).
 __device__ void record_stats(const NewtonArgs &A, int64_t pt, int iters, int evals, int status, double res) {
     if (A.pt_iters) A.pt_iters[pt] = iters;
     if (A.pt_evals) A.pt_evals[pt] = evals;
@@ -921,7 +934,20 @@ __global__ __launch_bounds__(kBgkBlock) void k_newton_bgk(const NewtonArgs A) {
     const int lane = threadIdx.x % LPP;
     if (pt >= A.npts) return;  // a point's lanes leave together
     const bool first = lane == 0;
-    const double *Q = A.Q + pt * A.nmom;
+    double Q[6];  // (records of 5 or 6 values)
+    if (A.nparts > 1) {
+        // lane a of the point adds the parts of moment a, a + LPP, ...
+#pragma unroll
+        for (int a0 = 0; a0 < 6; a0 += LPP) {
+            const int a = a0 + lane;
+            const double t = a < A.nmom ? moment_part_sum(A, pt, a) : 0.0;
+#pragma unroll
+            for (int b = 0; b < LPP && a0 + b < 6; ++b) Q[a0 + b] = __shfl(t, b, LPP);
+        }
+    } else {
+#pragma unroll
+        for (int a = 0; a < 6; ++a) Q[a] = a < A.nmom ? A.Q[pt * A.nmom + a] : 0.0;
+    }
     const double rho = Q[0];
     const double irho = 1.0 / rho;
     double U[3] = {Q[1] * irho, Q[2] * irho, Q[3] * irho};
@@ -987,9 +1013,17 @@ __global__ __launch_bounds__(kEsBlock) __attribute__((amdgpu_waves_per_eu(FRDVM_
     EsIter &I = reinterpret_cast<EsIter *>(P + npw)[threadIdx.x < npw ? threadIdx.x : 0];
     bool active = false;
     if ((int)threadIdx.x < npw) P[threadIdx.x].req = 0;
+    if (A.nparts > 1) {
+        // the points' moments from their parts, into the space of their sums
+        for (int t = threadIdx.x; t < npw * A.nmom; t += kEsBlock) {
+            const int q = t / A.nmom, a = t - q * A.nmom;
+            if (p0 + q < A.npts) reinterpret_cast<double *>(&P[q].s[0])[a] = moment_part_sum(A, p0 + q, a);
+        }
+        __syncthreads();
+    }
     if (owner) {
         EsPoint &p = P[threadIdx.x];
-        const double *Q = A.Q + pt * A.nmom;
+        const double *Q = A.nparts > 1 ? reinterpret_cast<const double *>(&p.s[0]) : A.Q + pt * A.nmom;
         const double rho = Q[0];
         const double irho = 1.0 / rho;
         const double U[3] = {Q[1] * irho, Q[2] * irho, Q[3] * irho};
@@ -1272,6 +1306,8 @@ NewtonArgs newton_args(fr_dvm *h, int guess) {
     A.nmom = h->nmom;
     A.wax = h->d_wax;
     A.Q = h->d_Q;
+    A.Qpart = h->d_Qpart;
+    A.nparts = h->q_parts;
     A.eq = h->d_eq;
     A.z = h->d_z;
     A.prim = h->d_prim;
@@ -1458,6 +1494,7 @@ int launch_newton_points(fr_dvm *h, const double *Q, int64_t n, int guess, doubl
         A.npts = n;
         A.nmom = 5;
         A.Q = Q;
+        A.nparts = 0;
         A.eq = nullptr;
         A.prim = nullptr;
         A.z = z;
