@@ -27,6 +27,8 @@ StageArgs blank() {
 
 // Moments (and, if traces, the outflow traces) of f into h->d_Q / h->d_tr[cur].
 int prime(fr_dvm *h, const void *f, int traces, int moments) {
+    if (no_traces(h)) traces = 0;
+    if (!traces && !moments) return FR_DVM_OK;
     StageArgs a = blank();
     a.f = f;
     a.tr_out = h->d_tr[h->cur_tr];
@@ -133,11 +135,10 @@ StageArgs stage_args(fr_dvm *h, void *f, double dt, int st, int collide) {
         a.fout = f;
         a.dF = h->d_reg;
     }
-    if (h->mx) {
-        // Mixed meshes: the flux points are solution points, so a stage reads
-        // its neighbours' traces from the stage value itself and never writes
-        // over it: the step goes from the caller's buffer through two of the
-        // handle's and back.
+    if (no_traces(h)) {
+        // a stage reads its neighbours' traces from the stage value and never
+        // writes over it: the step goes from the caller's buffer through two
+        // of the handle's and back
         void *v[2];
         v[0] = a.scheme == 0 ? h->d_reg : h->d_tr[0];
         v[1] = a.scheme == 0 ? h->d_tr[0] : h->d_tr[1];
@@ -209,7 +210,7 @@ extern "C" int fr_dvm_rk_steps(fr_dvm_t h, void *f, double dt, int nsteps) {
     for (int k = 0; k < nst; ++k) {
         const int st = k % 3;
         const int last = k == nst - 1;
-        const int traces = last ? 0 : 1, moments = (last || !collide) ? 0 : (split ? 1 : solve_moments(h, guess));
+        const int traces = last || no_traces(h) ? 0 : 1, moments = (last || !collide) ? 0 : (split ? 1 : solve_moments(h, guess));
         if (!split && k > 0 && collide) {
             if ((rc = launch_newton(h, guess))) return rc;
             if (dev) {

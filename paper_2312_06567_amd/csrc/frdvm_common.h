@@ -151,6 +151,8 @@ struct fr_dvm {
     // work buffers
     void *d_reg = nullptr;       // second RK register [ne*ns*nu]
     void *d_tr[2] = {nullptr, nullptr};
+    size_t tr_bytes[2] = {0, 0};
+    int keep_traces = 0;   // no room for stage values in place of traces, see no_traces()
     int cur_tr = 0;
     double *d_Q = nullptr;       // [ne*ns][nmom]
     int nsplit[2] = {1, 1};      // workgroups per element of the box kernel: stage and residual, prime pass
@@ -193,6 +195,15 @@ struct fr_dvm {
 };
 
 namespace frdvm {
+// Meshes whose flux points are solution points: mixed ones, and boxes with
+// Gauss-Lobatto points.  A stage reads its neighbours' traces from the stage
+// value itself, so it must not write over that value, and no traces are kept:
+// d_tr holds stage values.  A box for which the device has no room for these
+// keeps traces (shorter than a stage value from p = 3 on).
+inline bool no_traces(const fr_dvm *h) {
+    return h->mx || (h->axis_mode && h->nodes == FR_DVM_NODES_LOBATTO && !h->keep_traces);
+}
+
 // Brackets a launch with events when profiling is on.
 struct ProfScope {
     fr_dvm *h;

@@ -197,9 +197,20 @@ template <typename Real>
 struct LdsTab {
     Real lam[2][kMaxN], corr[2][kMaxN];
     Real D[kMaxN * kMaxN];  // read with a wave-uniform address (z lines)
+};
+// (the FP64 stage at p = 3 fills half a CU's LDS to the byte: what only one
+// kind of trace access needs is left out of the other)
+template <typename Real, bool GLL>
+struct LdsTraces {
+    LdsTab<Real> t;
     int64_t nb[6];     // element offset of each neighbour's trace block
     uint32_t cnt[6];   // trace entries per face point of each face slot
     uint32_t fo[6];    // offset of each face slot inside a block
+};
+template <typename Real>
+struct LdsTraces<Real, true> {
+    LdsTab<Real> t;
+    uint32_t pt[6];    // first solution point of the neighbour across each face
 };
 
 // The velocity node a lane works on in one chunk.
@@ -255,17 +266,42 @@ struct TraceOff {
 };
 
 template <typename Real>
-__device__ __forceinline__ TraceOff trace_in(const FrArgs &A, const LdsTab<Real> &T, const Vel &v, int d, int fp0) {
+__device__ __forceinline__ TraceOff trace_in(const FrArgs &A, const LdsTraces<Real, false> &X, const Vel &v, int d, int fp0) {
     TraceOff t;
     const bool flow = v.sgn[d] != 0;  // (a lane past the end reads what the last node reads)
     const int sin_ = v.sgn[d] > 0 ? 0 : 1;  // inflow face side
     const int slot = 2 * d + (sin_ ^ 1);     // the upwind neighbour's outflow face
-    const uint32_t cnt = T.cnt[slot], fo = T.fo[slot];
+    const uint32_t cnt = X.cnt[slot], fo = X.fo[slot];
     const uint32_t idx = fo + (uint32_t)compact_index(A.vg, d, sin_ ^ 1, v.iv) +
                          (uint32_t)fp0 * cnt;
     t.off = flow ? idx * (uint32_t)sizeof(Real) : 0u;
     t.stride = flow ? cnt * (uint32_t)sizeof(Real) : 0u;
     return t;
+}
+
+// Gauss-Lobatto points: the end nodes of a line are its flux points, so the
+// inflow trace of face point (a, b) is the neighbour's stage value at the node
+// on the shared face.  It is read from there (the stage never writes over the
+// value it reads), no trace is stored, and none has to be formed before the
+// first stage or a residual.  Stored traces are 3 / (p + 1) of a state, once
+// written and once read per stage, and the written ones are the dearest
+// bytes of the box stage: short runs per face row.  12^3 elements, 16^3
+// velocities, ES, per step, traces stored against read from the state: p = 3
+// FP64 12.5 against 10.3 ms (SSP) and 13.3 against 11.0 (low storage), FP32
+// deviations 9.0 against 7.9; residual 2.99 against 1.65 ms.  The state goes
+// through plain loads here (the neighbours read its faces again): streaming
+// ones cost 10.8 for 10.3 and 8.4 for 7.9 ms.
+// gll_in: the lane's address of layer l's first face point in the upwind
+// neighbour in direction d, the node at the far end of the line through the
+// layer's first point on the shared face.
+template <typename Real, int N>
+__device__ __forceinline__ const Real *gll_in(const Real *f, const LdsTraces<Real, true> &X, const Vel &v, int d, int l,
+                                              int64_t row, int off) {
+    constexpr int NL = N * N;
+    const int lo = (d == 2 ? N : NL) * l, far = (N - 1) * (d == 0 ? 1 : (d == 1 ? N : NL));
+    const bool plus = v.sgn[d] > 0;  // entering through side 0, from the neighbour's far end
+    const uint32_t s = X.pt[2 * d + (plus ? 0 : 1)] + (uint32_t)lo + (plus ? far : 0);
+    return f + ((int64_t)s * row + off + v.k);
 }
 
 // A value the compiler cannot see through (nor hoist out of a loop).
@@ -311,7 +347,8 @@ typedef const __attribute__((address_space(4))) double cdouble;
 // second RK register and the output.  ER (FP32 deviation storage, stage
 // mode, FP32): the stage value and the inflow traces arrive as FP32
 // deviations from element references and the result leaves as one.
-template <typename Real, typename SReal, int P, int NMOM, int MODE, bool ER>
+// GLL: Gauss-Lobatto points (stage and residual), see gll_in().
+template <typename Real, typename SReal, int P, int NMOM, int MODE, bool ER, bool GLL>
 __global__ __launch_bounds__(kChunk *(P + 1)) __attribute__((amdgpu_waves_per_eu(fr_waves<Real, MODE>()))) void
 k_fr_layer(const FrArgs A) {
     constexpr int N = P + 1, NS = N * N * N, NL = N * N;
@@ -335,7 +372,8 @@ k_fr_layer(const FrArgs A) {
     Real *const tZ = tS + TS;
     Real *const tP = tZ + TZ_;
     double *const red = reinterpret_cast<double *>(s_tiles);
-    __shared__ __attribute__((aligned(16))) LdsTab<Real> T;
+    __shared__ __attribute__((aligned(16))) LdsTraces<Real, GLL> X;
+    LdsTab<Real> &T = X.t;
     // equilibrium records staged per workgroup: the exponent as a polynomial
     // in u (10 coefficients), the G exponent shift (reduced pair), and 1/tau
     // in the working precision, read with a wave-uniform address
@@ -357,6 +395,7 @@ k_fr_layer(const FrArgs A) {
     // FP32 deviation storage: the element references of the previous stage's
     // records (own, and the neighbour across each face: the inflow traces are
     // deviations from the writer's) and of this stage's (own: the result)
+    static_assert(!GLL || (FLUX && sizeof(Real) == sizeof(SReal)), "traces read from the state");
     static_assert(!ER || (sizeof(Real) == 4 && sizeof(SReal) == 4 && MODE == MODE_STAGE && NCOMP == 1),
                   "deviation storage: FP32 monatomic stage kernel");
     const bool in_dev = ER && A.sa.in_dev;
@@ -402,13 +441,19 @@ k_fr_layer(const FrArgs A) {
         T.D[tid - 64] = op.D[tid - 64];
     } else if (tid < 2 * kMaxN + 6) {
         const int fc = tid - 2 * kMaxN;
-        T.nb[fc] = (int64_t)A.nbr[6 * e + fc] * A.tl.elem;
-        T.cnt[fc] = (uint32_t)A.tl.cnt[fc];
-        T.fo[fc] = (uint32_t)A.tl.face_off[fc];
+        if constexpr (GLL) {
+            X.pt[fc] = (uint32_t)A.nbr[6 * e + fc] * NS;
+        } else {
+            X.nb[fc] = (int64_t)A.nbr[6 * e + fc] * A.tl.elem;
+            X.cnt[fc] = (uint32_t)A.tl.cnt[fc];
+            X.fo[fc] = (uint32_t)A.tl.face_off[fc];
+        }
     }
     // trace blocks: the own one (inflow of this stage) and the neighbours'
     // (outflow of the produced value)
-    const Real *__restrict__ trE = reinterpret_cast<const Real *>(A.sa.tr_in) + (FLUX ? e * A.tl.elem : 0);
+    const Real *__restrict__ trE = reinterpret_cast<const Real *>(A.sa.tr_in) + (FLUX && !GLL ? e * A.tl.elem : 0);
+    const Real *__restrict__ fG = reinterpret_cast<const Real *>(A.sa.f);  // GLL: the neighbours' state
+    const int64_t rowG = (int64_t)nu * NCOMP;
     // running moments of the solution point tid % 64 over this wave's share
     // of every chunk (one partial per wave, added in wave order at the end)
     double Mrun[NMOM];
@@ -443,11 +488,21 @@ k_fr_layer(const FrArgs A) {
         const Vel v0 = velocity(A, (cc0 - comp0 * nchunk) * kChunk + vl, true);
         const uint32_t o = (lrow + (uint32_t)(comp0 * nu + v0.k)) * (uint32_t)sizeof(SReal);
 #pragma unroll
-        for (int q = 0; q < NL; ++q) fc[q] = ldn(fE, o + q * QB);
-        if (FLUX) {
-            const TraceOff sx = trace_in<Real>(A, T, v0, 0, N * l);
-            const TraceOff sy = trace_in<Real>(A, T, v0, 1, N * l);
-            const TraceOff sz = trace_in<Real>(A, T, v0, 2, N * l);
+        for (int q = 0; q < NL; ++q) fc[q] = GLL ? ldb(fE, o + q * QB) : ldn(fE, o + q * QB);
+        if constexpr (GLL) {
+            const Real *px = gll_in<Real, N>(fG, X, v0, 0, l, rowG, comp0 * nu);
+            const Real *py = gll_in<Real, N>(fG, X, v0, 1, l, rowG, comp0 * nu);
+            const Real *pz = gll_in<Real, N>(fG, X, v0, 2, l, rowG, comp0 * nu);
+#pragma unroll
+            for (int a = 0; a < N; ++a) {
+                TX[a] = px[a * N * rowG];
+                TY[a] = py[a * rowG];
+                TZ[a] = pz[a * rowG];
+            }
+        } else if constexpr (FLUX) {
+            const TraceOff sx = trace_in<Real>(A, X, v0, 0, N * l);
+            const TraceOff sy = trace_in<Real>(A, X, v0, 1, N * l);
+            const TraceOff sz = trace_in<Real>(A, X, v0, 2, N * l);
 #pragma unroll
             for (int a = 0; a < N; ++a) {
                 TX[a] = ldb(tr0, sx.off + a * sx.stride);
@@ -515,15 +570,16 @@ k_fr_layer(const FrArgs A) {
         // chunk's values (loads complete in order: waiting for these in the
         // collision then leaves the next chunk's loads in flight) and before
         // the x/y/z passes, which cover its latency
-        SReal X[NL];
+        SReal x2[NL];
         if (useX) {
 #pragma unroll
-            for (int q = 0; q < NL; ++q) X[q] = ldn(XE, o + q * QB);
+            for (int q = 0; q < NL; ++q) x2[q] = ldn(XE, o + q * QB);
         } else {
 #pragma unroll
-            for (int q = 0; q < NL; ++q) X[q] = SReal(0);
+            for (int q = 0; q < NL; ++q) x2[q] = SReal(0);
         }
         TraceOff nx{0u, 0u}, ny{0u, 0u};
+        const Real *gx = nullptr, *gy = nullptr;  // GLL: where the next chunk's x and y traces are
         // the next chunk (possibly the first of the next component; after
         // the workgroup's last one every lane requests the last node)
         const int compn = NCOMP == 2 && cc + 1 >= nchunk ? 1 : 0;
@@ -533,11 +589,17 @@ k_fr_layer(const FrArgs A) {
             const Vel vn = velocity(A, chn * kChunk + vl, cc + 1 < cc1);
             const uint32_t on = (lrow + (uint32_t)(compn * nu + vn.k)) * (uint32_t)sizeof(SReal);
 #pragma unroll
-            for (int q = 0; q < NL; ++q) fc[q] = ldn(fE, on + q * QB);
-            if (FLUX) {
-                nx = trace_in<Real>(A, T, vn, 0, N * l);
-                ny = trace_in<Real>(A, T, vn, 1, N * l);
-                const TraceOff nz = trace_in<Real>(A, T, vn, 2, N * l);
+            for (int q = 0; q < NL; ++q) fc[q] = GLL ? ldb(fE, on + q * QB) : ldn(fE, on + q * QB);
+            if constexpr (GLL) {
+                gx = gll_in<Real, N>(fG, X, vn, 0, l, rowG, compn * nu);
+                gy = gll_in<Real, N>(fG, X, vn, 1, l, rowG, compn * nu);
+                const Real *pz = gll_in<Real, N>(fG, X, vn, 2, l, rowG, compn * nu);
+#pragma unroll
+                for (int a = 0; a < N; ++a) TZ[a] = pz[a * rowG];
+            } else if constexpr (FLUX) {
+                nx = trace_in<Real>(A, X, vn, 0, N * l);
+                ny = trace_in<Real>(A, X, vn, 1, N * l);
+                const TraceOff nz = trace_in<Real>(A, X, vn, 2, N * l);
 #pragma unroll
                 for (int a = 0; a < N; ++a) TZ[a] = ldb(trEn, nz.off + a * nz.stride);
             }
@@ -566,11 +628,16 @@ k_fr_layer(const FrArgs A) {
 #pragma unroll
                     for (int m = 0; m < N; ++m) g[m] = tS[tix<Real>(l * NL + (d == 0 ? m + N * a : a + N * m), vt)];
                     Real fm = Real(0);
+                    if constexpr (GLL) {
+                        fm = sin_ ? g[N - 1] : g[0];
+                    } else {
 #pragma unroll
-                    for (int m = 0; m < N; ++m) fm += T.lam[sin_][m] * g[m];
+                        for (int m = 0; m < N; ++m) fm += T.lam[sin_][m] * g[m];
+                    }
                     Real &tin = d == 0 ? TX[a] : TY[a];
                     const Real jmp = flow ? un * ((ER ? tin + (Real)dl[d] : tin) - fm) : Real(0);
-                    tin = ldb(trEn, sn.off + a * sn.stride);
+                    if constexpr (GLL) tin = d == 0 ? gx[a * N * rowG] : gy[a * rowG];
+                    else tin = ldb(trEn, sn.off + a * sn.stride);
 #pragma unroll
                     for (int i = 0; i < N; ++i) {
                         Real t = Real(0);
@@ -648,10 +715,10 @@ k_fr_layer(const FrArgs A) {
                     double fod;
                     if constexpr (!LSRK) {
                         fod = A.sa.beta * ((double)fq + (double)(dt * L));
-                        fod = fma(A.sa.alpha, (double)X[q], fod);  // (X = 0 when not read)
+                        fod = fma(A.sa.alpha, (double)x2[q], fod);  // (0 when not read)
                     } else {
                         Real dd = dt * L;
-                        dd += (Real)A.sa.lsA * (Real)X[q];
+                        dd += (Real)A.sa.lsA * (Real)x2[q];
                         if constexpr (KEEP) stn(dFE, o + q * QB, (SReal)dd);
                         fod = fma(A.sa.lsB, (double)dd, (double)fq);
                     }
@@ -686,14 +753,15 @@ k_fr_layer(const FrArgs A) {
 
         // outflow traces of the produced value on the x and y faces, into
         // the neighbours' blocks
+        if constexpr (!GLL)
         if (A.do_traces) {
 #pragma unroll
             for (int d = 0; d < 2; ++d) {
                 if (v.sgn[d] != 0) {
                     const int side = v.sgn[d] > 0 ? 1 : 0;
                     const int face = 2 * d + side;
-                    const int cnt = (int)T.cnt[face];
-                    Real *tp = trout + T.nb[face] + (NCOMP == 2 ? comp * A.elem_comp : 0) + T.fo[face] +
+                    const int cnt = (int)X.cnt[face];
+                    Real *tp = trout + X.nb[face] + (NCOMP == 2 ? comp * A.elem_comp : 0) + X.fo[face] +
                                compact_index(A.vg, d, side, v.iv) +
                                (int64_t)(N * l) * cnt;
 #pragma unroll
@@ -721,12 +789,13 @@ k_fr_layer(const FrArgs A) {
                 for (int q = 0; q < NL; ++q) tP[tix<Real>(l * NL + q, vt)] = f[q];
             }
             __syncthreads();  // the produced tile is complete (and the stage tile no longer read)
+            if constexpr (!GLL)
             if (A.do_traces && v.sgn[2] != 0) {
                 // this wave writes the z-face points (i, j = l)
                 const int side = v.sgn[2] > 0 ? 1 : 0;
                 const int face = 4 + side;
-                const int cnt = (int)T.cnt[face];
-                Real *tp = trout + T.nb[face] + (NCOMP == 2 ? comp * A.elem_comp : 0) + T.fo[face] +
+                const int cnt = (int)X.cnt[face];
+                Real *tp = trout + X.nb[face] + (NCOMP == 2 ? comp * A.elem_comp : 0) + X.fo[face] +
                            compact_index(A.vg, 2, side, v.iv) +
                            (int64_t)(N * l) * cnt;
 #pragma unroll
@@ -904,16 +973,16 @@ __global__ __launch_bounds__(kRefBlock) void k_elem_ref(const FrArgs A, int ns, 
     }
 }
 
-template <typename Real, typename SReal, int P, int NMOM, bool ER>
+template <typename Real, typename SReal, int P, int NMOM, bool ER, bool GLL>
 int launch_p(fr_dvm *h, int mode, const FrArgs &A) {
     const int64_t ne = A.sa.ecount ? A.sa.ecount : h->ne;
     dim3 grid((unsigned)(ne * A.nsplit)), block(kChunk * (P + 1));
     if (mode == MODE_PRIME)
-        hipLaunchKernelGGL((k_fr_layer<Real, SReal, P, NMOM, MODE_PRIME, false>), grid, block, 0, h->stream, A);
+        hipLaunchKernelGGL((k_fr_layer<Real, SReal, P, NMOM, MODE_PRIME, false, false>), grid, block, 0, h->stream, A);
     else if (mode == MODE_STAGE)
-        hipLaunchKernelGGL((k_fr_layer<Real, SReal, P, NMOM, MODE_STAGE, ER>), grid, block, 0, h->stream, A);
+        hipLaunchKernelGGL((k_fr_layer<Real, SReal, P, NMOM, MODE_STAGE, ER, GLL>), grid, block, 0, h->stream, A);
     else
-        hipLaunchKernelGGL((k_fr_layer<Real, SReal, P, NMOM, MODE_RESID, false>), grid, block, 0, h->stream, A);
+        hipLaunchKernelGGL((k_fr_layer<Real, SReal, P, NMOM, MODE_RESID, false, GLL>), grid, block, 0, h->stream, A);
     if (A.nsplit > 1 && A.do_moments == kMomentParts) {
         h->q_parts = A.nsplit;
     } else if (A.nsplit > 1 && A.do_moments) {
@@ -926,14 +995,19 @@ int launch_p(fr_dvm *h, int mode, const FrArgs &A) {
     return FR_DVM_OK;
 }
 
-template <typename Real, typename SReal, int NMOM, bool ER = false>
-int launch_np(fr_dvm *h, int mode, const FrArgs &A) {
+template <typename Real, typename SReal, int NMOM, bool ER, bool GLL>
+int launch_order(fr_dvm *h, int mode, const FrArgs &A) {
     switch (h->p) {
-        case 1: return launch_p<Real, SReal, 1, NMOM, ER>(h, mode, A);
-        case 2: return launch_p<Real, SReal, 2, NMOM, ER>(h, mode, A);
-        case 3: return launch_p<Real, SReal, 3, NMOM, ER>(h, mode, A);
+        case 1: return launch_p<Real, SReal, 1, NMOM, ER, GLL>(h, mode, A);
+        case 2: return launch_p<Real, SReal, 2, NMOM, ER, GLL>(h, mode, A);
+        case 3: return launch_p<Real, SReal, 3, NMOM, ER, GLL>(h, mode, A);
     }
     return h->fail(FR_DVM_EUNSUPPORTED, "order");
+}
+template <typename Real, typename SReal, int NMOM, bool ER = false>
+int launch_np(fr_dvm *h, int mode, const FrArgs &A) {
+    return no_traces(h) ? launch_order<Real, SReal, NMOM, ER, true>(h, mode, A)
+                        : launch_order<Real, SReal, NMOM, ER, false>(h, mode, A);
 }
 
 // Streaming copy with 16-byte accesses, grid-stride, four loads in flight

@@ -624,18 +624,52 @@ extern "C" int fr_dvm_create(const fr_dvm_mesh *mesh, int order, const fr_dvm_vg
 
 namespace {
 
+void free_traces(fr_dvm *h) {
+    for (int b = 0; b < 2; ++b)
+        if (h->d_tr[b]) {
+            hipFree(h->d_tr[b]);
+            h->owned_bytes -= h->tr_bytes[b];
+            h->d_tr[b] = nullptr;
+            h->tr_bytes[b] = 0;
+        }
+    h->keep_traces = 0;
+}
+
+// Buffers of stage values a step needs beside the register (see stage_args).
+int stage_buffers(const fr_dvm *h) { return h->prm.rk == FR_DVM_LSRK3_2N ? 2 : 1; }
+
+// Allocates what is not there yet.
+int alloc_traces(fr_dvm *h) {
+    const size_t es = h->prm.precision != FR_DVM_FP64 ? sizeof(float) : sizeof(double);  // of the stage arithmetic
+    for (;;) {
+        const bool values = no_traces(h);
+        const int n = values ? stage_buffers(h) : 2;
+        const size_t bytes = es * (values ? h->ne * h->ns * h->vg.nu * h->ncomp : h->ne * h->tl.elem);
+        int b = 0;
+        for (; b < n; ++b) {
+            if (h->d_tr[b]) continue;
+            if (hipMalloc(&h->d_tr[b], bytes) != hipSuccess) break;
+            h->tr_bytes[b] = bytes;
+            h->owned_bytes += bytes;
+        }
+        if (b == n) return FR_DVM_OK;
+        h->d_tr[b] = nullptr;
+        if (!values || h->mx) {
+            h->have_params = false;  // (not ready for a step)
+            return h->fail(FR_DVM_ENOMEM, "trace allocation failed");
+        }
+        hipGetLastError();  // (the failed allocation's: not the next launch's)
+        free_traces(h);
+        h->keep_traces = 1;
+    }
+}
+
 // A box handle moves to the general-mesh path (the positivity limiter runs
 // in the general stage kernel): pointwise metrics, full traces, its own
 // boundary tables.  The box path's trace buffers are released here (their
 // size depends on the path) and reallocated by the caller.
 int move_to_general(fr_dvm *h) {
-    const size_t es = h->prm.precision == FR_DVM_FP32 ? sizeof(float) : sizeof(double);  // trace values
-    for (int b = 0; b < 2; ++b)
-        if (h->d_tr[b]) {
-            hipFree(h->d_tr[b]);
-            h->d_tr[b] = nullptr;
-            if (h->have_params) h->owned_bytes -= h->ne * h->tl.elem * es;
-        }
+    free_traces(h);
     const fr_dvm::MeshCopy &mc = h->mesh_copy;
     fr_dvm_mesh m;
     m.n_elem = mc.n_elem;
@@ -683,29 +717,19 @@ extern "C" int fr_dvm_set_params(fr_dvm_t h, const fr_dvm_params *p) {
     bool realloc_mom = !h->have_params || nmom != h->nmom;
     // element size of the buffers allocated under the previous parameters
     const size_t es_old = h->have_params && h->prm.precision != FR_DVM_FP64 ? sizeof(float) : sizeof(double);
-    // traces: in the precision of the stage arithmetic (FP32 for both FP32 forms)
-    const size_t tes_old = h->have_params && h->prm.precision != FR_DVM_FP64 ? sizeof(float) : sizeof(double);
     h->prm = *p;
     h->nmom = nmom;
     h->stage_count = 0;
     size_t es = p->precision == FR_DVM_FP64 ? sizeof(double) : sizeof(float);
-    size_t tes = p->precision != FR_DVM_FP64 ? sizeof(float) : sizeof(double);
     int64_t npts = h->ne * h->ns;
     int64_t nu = h->vg.nu * h->ncomp;  // state values per point
-    // trace values per buffer (mixed meshes store no traces: the two buffers
-    // take the stage values, see stage_args)
-    const size_t trn = h->mx ? (size_t)npts * h->vg.nu : (size_t)(h->ne * h->tl.elem);
     int rc;
     if (realloc_all) {
         if (h->d_reg) { hipFree(h->d_reg); h->owned_bytes -= npts * nu * es_old; h->d_reg = nullptr; }
-        for (int b = 0; b < 2; ++b)
-            if (h->d_tr[b]) { hipFree(h->d_tr[b]); h->d_tr[b] = nullptr; h->owned_bytes -= trn * tes_old; }
+        free_traces(h);
         if (hipMalloc(&h->d_reg, npts * nu * es) != hipSuccess) { h->d_reg = nullptr; return h->fail(FR_DVM_ENOMEM, "register allocation failed"); }
         h->owned_bytes += npts * nu * es;
-        for (int b = 0; b < 2; ++b) {
-            if (hipMalloc(&h->d_tr[b], trn * tes) != hipSuccess) { h->d_tr[b] = nullptr; return h->fail(FR_DVM_ENOMEM, "trace allocation failed"); }
-            h->owned_bytes += trn * tes;
-        }
+        if ((rc = alloc_traces(h))) return rc;
         if ((rc = dev_alloc(h, &h->d_eq, npts * kEqW))) return rc;
         for (int b = 0; b < 3; ++b)
             if ((rc = dev_alloc(h, &h->d_ref[b], p->precision == FR_DVM_FP32_DEV ? h->ne * kRefW : 0))) return rc;
@@ -717,6 +741,8 @@ extern "C" int fr_dvm_set_params(fr_dvm_t h, const fr_dvm_params *p) {
         if ((rc = dev_alloc(h, &h->d_pt_status, npts))) return rc;
         if ((rc = dev_alloc(h, &h->d_pt_resid, npts))) return rc;
         h->zvalid = 0;
+    } else if (no_traces(h) && stage_buffers(h) == 2 && !h->d_tr[1]) {
+        if ((rc = alloc_traces(h))) return rc;
     }
     if (realloc_mom) {
         if ((rc = dev_alloc(h, &h->d_Q, npts * nmom))) return rc;
