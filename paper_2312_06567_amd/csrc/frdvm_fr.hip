@@ -622,6 +622,12 @@ k_fr_layer(const FrArgs A) {
                 const Real un = (Real)((sin_ ? 1.0 : -1.0) * gf[d] * v.u[d]);
                 const Real ad = d == 0 ? ax : ay;
                 const TraceOff sn = d == 0 ? nx : ny;
+                Real lam[N], cor[N];  // of the inflow side
+#pragma unroll
+                for (int m = 0; m < N; ++m) {
+                    lam[m] = T.lam[sin_][m];
+                    cor[m] = T.corr[sin_][m];
+                }
 #pragma unroll
                 for (int a = 0; a < N; ++a) {
                     Real g[N];
@@ -632,10 +638,11 @@ k_fr_layer(const FrArgs A) {
                         fm = sin_ ? g[N - 1] : g[0];
                     } else {
 #pragma unroll
-                        for (int m = 0; m < N; ++m) fm += T.lam[sin_][m] * g[m];
+                        for (int m = 0; m < N; ++m) fm += lam[m] * g[m];
                     }
                     Real &tin = d == 0 ? TX[a] : TY[a];
-                    const Real jmp = flow ? un * ((ER ? tin + (Real)dl[d] : tin) - fm) : Real(0);
+                    Real jmp = un * ((ER ? tin + (Real)dl[d] : tin) - fm);
+                    jmp = flow ? jmp : Real(0);
                     if constexpr (GLL) tin = d == 0 ? gx[a * N * rowG] : gy[a * rowG];
                     else tin = ldb(trEn, sn.off + a * sn.stride);
 #pragma unroll
@@ -645,7 +652,7 @@ k_fr_layer(const FrArgs A) {
                         for (int m = 0; m < N; ++m) t += op.D[i * N + m] * g[m];
                         Real &ri = r[d == 0 ? i + N * a : a + N * i];
                         ri = fma(ad, t, ri);
-                        ri = fma(T.corr[sin_][i], jmp, ri);
+                        ri = fma(cor[i], jmp, ri);
                         keep(ri);
                     }
                     phase_fence();
@@ -659,20 +666,35 @@ k_fr_layer(const FrArgs A) {
                 const bool zflow = v.sgn[2] != 0;
                 const Real unz = (Real)((zin ? 1.0 : -1.0) * gf[2] * v.u[2]);
                 const Real cz = zflow ? T.corr[zin][l] * unz : Real(0);
+                Real cm[N];
 #pragma unroll
-                for (int m = 0; m < N; ++m) {
-                    const Real cm = az * T.D[l * N + m] - cz * T.lam[zin][m];
+                for (int m = 0; m < N; ++m) cm[m] = az * T.D[l * N + m] - cz * T.lam[zin][m];
+                // The tile's values are requested B at a time and waited for
+                // together; one by one, each multiply-add waited out an LDS
+                // access, and so did the masked trace reads and the operator
+                // entries of the inflow side, read again for every line.
+                // Stage kernels at p = 3, one by one / 16 (FP32) or 8 (FP64)
+                // together: FP32 deviations, 16^3 elements, 20^3 velocities
+                // 10.28 / 9.40 ms; FP64 BGK 16^3, 16^3 6.90 / 6.23 ms; FP32
+                // pair 6^3, 16^3 0.638 / 0.550 ms.  8 in FP32 9.52 ms; 16 in
+                // FP64 no gain.
+                constexpr int kB = sizeof(Real) == 4 ? 16 : 8, B = kB < NL ? kB : NL;
 #pragma unroll
-                    for (int q = 0; q < NL; ++q) {
-                        r[q] = fma(cm, tS[tix<Real>(m * NL + q, vt)], r[q]);
-                        keep(r[q]);
+                for (int m = 0; m <= N; ++m) {
+#pragma unroll
+                    for (int q0 = 0; q0 < NL; q0 += B) {
+                        Real g[B];
+#pragma unroll
+                        for (int i = 0; i < B; ++i)
+                            if (q0 + i < NL) g[i] = m < N ? tS[tix<Real>(m * NL + q0 + i, vt)] : tZ[tix<Real>(q0 + i, vt)];
+                        phase_fence();
+#pragma unroll
+                        for (int i = 0; i < B; ++i)
+                            if (q0 + i < NL) {
+                                r[q0 + i] = fma(m < N ? cm[m] : cz, m < N || zflow ? g[i] : Real(0), r[q0 + i]);
+                                keep(r[q0 + i]);
+                            }
                     }
-                    phase_fence();
-                }
-#pragma unroll
-                for (int q = 0; q < NL; ++q) {
-                    const Real fp = zflow ? tZ[tix<Real>(q, vt)] : Real(0);
-                    r[q] = fma(cz, fp, r[q]);
                 }
                 phase_fence();
             }
