@@ -20,26 +20,41 @@ __device__ __forceinline__ double fma3(double a, double b, double c) {
     return d;
 }
 
+template <int W>
+__device__ __forceinline__ void exp_to_f32(const double (&E)[W], float (&g)[W]) {
+    double n[W], t[W], p[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        // (an exponent of -inf, a point without an equilibrium, gives 0 and
+        // not the NaN of its reduction)
+        const double e2 = fmax(E[w], -2000.0) * 1.4426950408889634074;  // log2(e)
+        n[w] = rint(e2);
+        t[w] = (e2 - n[w]) * 0.69314718055994530942;  // ln(2)
+        // Horner on 1/k!, k = 8 .. 0.  The three-operand FMA is spelled out:
+        // left to itself the compiler takes the accumulating two-operand form,
+        // which first copies each (loop-invariant) coefficient into the result
+        // register.
+        p[w] = 1.0 / 40320.0;
+    }
+    constexpr double c[5] = {1.0 / 5040.0, 1.0 / 720.0, 1.0 / 120.0, 1.0 / 24.0, 1.0 / 6.0};
+#pragma unroll
+    for (int k = 0; k < 5; ++k)
+#pragma unroll
+        for (int w = 0; w < W; ++w) p[w] = fma3(p[w], t[w], c[k]);
+#pragma unroll
+    for (int w = 0; w < W; ++w) p[w] = fma(p[w], t[w], 0.5);
+#pragma unroll
+    for (int w = 0; w < W; ++w) p[w] = fma(p[w], t[w], 1.0);
+#pragma unroll
+    for (int w = 0; w < W; ++w) p[w] = fma(p[w], t[w], 1.0);
+#pragma unroll
+    for (int w = 0; w < W; ++w) g[w] = (float)ldexp(p[w], (int)n[w]);
+}
 __device__ __forceinline__ float exp_to_f32(double E) {
-    // (an exponent of -inf, a point without an equilibrium, gives 0 and not
-    // the NaN of its reduction)
-    const double e2 = fmax(E, -2000.0) * 1.4426950408889634074;  // log2(e)
-    const double n = rint(e2);
-    const double t = (e2 - n) * 0.69314718055994530942;  // ln(2)
-    // Horner on 1/k!, k = 8 .. 0.  The three-operand FMA is spelled out:
-    // left to itself the compiler takes the accumulating two-operand form,
-    // which first copies each (loop-invariant) coefficient into the result
-    // register.
-    double p = 1.0 / 40320.0;
-    p = fma3(p, t, 1.0 / 5040.0);
-    p = fma3(p, t, 1.0 / 720.0);
-    p = fma3(p, t, 1.0 / 120.0);
-    p = fma3(p, t, 1.0 / 24.0);
-    p = fma3(p, t, 1.0 / 6.0);
-    p = fma(p, t, 0.5);
-    p = fma(p, t, 1.0);
-    p = fma(p, t, 1.0);
-    return (float)ldexp(p, (int)n);
+    const double e[1] = {E};
+    float g[1];
+    exp_to_f32<1>(e, g);
+    return g[0];
 }
 
 // a * b + c in FP64 with c a wave-uniform constant (one scalar register pair
@@ -50,30 +65,45 @@ __device__ __forceinline__ double fma3s(double a, double b, double c) {
     return d;
 }
 
-// exp of an exponent held in FP64, in FP64 to a few ulp: E = n ln 2 + t with
+// exp of exponents held in FP64, in FP64 to a few ulp: E = n ln 2 + t with
 // n = rint(E log2 e), t = E - n ln 2 reduced with ln 2 split into its nearest
-// double and the remainder (|t| <= 0.347), e^t by its Taylor series to degree
-// 12 (truncation below 2e-16 relative), scaled by 2^n (0 below the FP64
-// range).
+// double and the remainder (|t| <= 0.347), e^t = 1 + t + t^2 q(t) with q of
+// degree 9, the interpolant of (e^t - 1 - t) / t^2 at the Chebyshev points of
+// |t| <= ln(2)/2 (error of e^t below 2e-17 relative; the Taylor series needs
+// one degree more for 2e-16), scaled by 2^n (0 below the FP64 range).  W
+// exponents run side by side: one is a chain of 16 dependent operations.
+template <int W>
+__device__ __forceinline__ void exp_f64(const double (&Ein)[W], double (&g)[W]) {
+    constexpr double q[10] = {0x1.0000000000001p-1,  0x1.5555555555556p-3,  0x1.5555555553d68p-5,  0x1.11111111109b5p-7,
+                              0x1.6c16c17889ef1p-10, 0x1.a01a01a7c2efep-13, 0x1.a019b9149a41cp-16, 0x1.71de0db2f6b19p-19,
+                              0x1.28917c89a43a7p-22, 0x1.af389ecfc4b9cp-26};
+    double n[W], t[W], p[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) t[w] = fmax(Ein[w], -2000.0);  // -inf (no equilibrium) gives 0
+#pragma unroll
+    for (int w = 0; w < W; ++w) n[w] = rint(t[w] * 1.4426950408889634074);
+#pragma unroll
+    for (int w = 0; w < W; ++w) t[w] = fma(-n[w], 0.6931471805599453, t[w]);
+#pragma unroll
+    for (int w = 0; w < W; ++w) t[w] = fma(-n[w], 2.3190468138462996e-17, t[w]);
+#pragma unroll
+    for (int w = 0; w < W; ++w) p[w] = q[9];
+#pragma unroll
+    for (int k = 8; k >= 0; --k)
+#pragma unroll
+        for (int w = 0; w < W; ++w) p[w] = fma3s(p[w], t[w], q[k]);
+#pragma unroll
+    for (int w = 0; w < W; ++w) p[w] = fma(p[w], t[w], 1.0);
+#pragma unroll
+    for (int w = 0; w < W; ++w) p[w] = fma(p[w], t[w], 1.0);
+#pragma unroll
+    for (int w = 0; w < W; ++w) g[w] = ldexp(p[w], (int)n[w]);
+}
 __device__ __forceinline__ double exp_f64(double E) {
-    E = fmax(E, -2000.0);  // -inf (no equilibrium) gives 0
-    const double n = rint(E * 1.4426950408889634074);
-    double t = fma(-n, 0.6931471805599453, E);
-    t = fma(-n, 2.3190468138462996e-17, t);
-    double p = 1.0 / 479001600.0;  // 1/12!
-    p = fma3s(p, t, 1.0 / 39916800.0);
-    p = fma3s(p, t, 1.0 / 3628800.0);
-    p = fma3s(p, t, 1.0 / 362880.0);
-    p = fma3s(p, t, 1.0 / 40320.0);
-    p = fma3s(p, t, 1.0 / 5040.0);
-    p = fma3s(p, t, 1.0 / 720.0);
-    p = fma3s(p, t, 1.0 / 120.0);
-    p = fma3s(p, t, 1.0 / 24.0);
-    p = fma3s(p, t, 1.0 / 6.0);
-    p = fma(p, t, 0.5);
-    p = fma(p, t, 1.0);
-    p = fma(p, t, 1.0);
-    return ldexp(p, (int)n);
+    const double e[1] = {E};
+    double g[1];
+    exp_f64<1>(e, g);
+    return g[0];
 }
 
 // The exponent polynomial of an element reference (FP32 deviation storage):

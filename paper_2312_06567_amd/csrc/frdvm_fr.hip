@@ -100,15 +100,13 @@ __device__ __forceinline__ const OpsR<double> &ops_of<double>(const FrArgs &A) {
 
 // exp of an exponent held in FP64, returned in the working precision (FP32:
 // evaluated in FP64 and rounded once, see exp_to_f32).
-template <typename Real>
-__device__ __forceinline__ Real exp_r(double E);
-template <>
-__device__ __forceinline__ float exp_r<float>(double E) {
-    return exp_to_f32(E);
+template <int W>
+__device__ __forceinline__ void exp_r(const double (&E)[W], float (&g)[W]) {
+    exp_to_f32<W>(E, g);
 }
-template <>
-__device__ __forceinline__ double exp_r<double>(double E) {
-    return exp_f64(E);
+template <int W>
+__device__ __forceinline__ void exp_r(const double (&E)[W], double (&g)[W]) {
+    exp_f64<W>(E, g);
 }
 
 // Coefficient c (in the order of ref_exponent) of the exponent of an
@@ -222,6 +220,10 @@ struct Vel {
     double u[3];
 };
 
+template <int V>
+struct IntC {
+    static constexpr int value = V;
+};
 template <bool B>
 struct BoolC {
     static constexpr bool value = B;
@@ -706,6 +708,12 @@ k_fr_layer(const FrArgs A) {
             }
             // collision source and the Runge-Kutta combination, point by point
             const Real dt = (Real)A.sa.dt;
+            // Values whose collision and combination run side by side: one is a
+            // chain of some 45 dependent operations, the last 35 of them FP64.
+            // Stage kernels, 1 / 2 at a time: FP32 deviations 16^3 elements
+            // p = 3, 20^3 velocities 9.45 / 9.22 ms, FP64 BGK 16^3, 16^3
+            // 6.20 / 6.05 ms; 4 at a time spill (FP32 pair 0.52 / 0.73 ms).
+            constexpr int W = 2;
             // random bits of the stochastic rounding: one hash per lane and
             // chunk, a xorshift step per value
             uint32_t rs = sizeof(Real) == 4 ? round_bits(A.sa.seed, (uint32_t)(e * NS + l * NL), (uint32_t)(comp * nu + v.k)) | 1u
@@ -718,46 +726,69 @@ k_fr_layer(const FrArgs A) {
             auto points = [&](auto coll_c, auto lsrk_c, auto keep_c) {
                 constexpr bool COLL = decltype(coll_c)::value, LSRK = decltype(lsrk_c)::value;
                 constexpr bool KEEP = decltype(keep_c)::value;
+                auto group = [&](auto width, int q0) {
+                    constexpr int G = decltype(width)::value;
+                    Real fq[G], dg[G], it[G];  // dg: the equilibrium less the value
 #pragma unroll
-                for (int q = 0; q < NL; ++q) {
-                    const Real fq = tS[tix<Real>(l * NL + q, vt)];
-                    Real L = -r[q];
+                    for (int i = 0; i < G; ++i) fq[i] = tS[tix<Real>(l * NL + q0 + i, vt)];
                     if constexpr (COLL) {
-                        const int s = l * NL + q;
-                        const double *b = &s_eb[s * kEb];
-                        const double c0 = (NCOMP == 2 && comp) ? b[0] + b[kRefCoef] : b[0];
-                        // the equilibrium's exponent at this point and velocity
-                        const double Eq = eq_exponent(b, c0, v.u);
-                        if constexpr (ER)
-                            L += ((Real)(exp_f64(Eq) - (double)rp) - fq) * s_it[s];  // g - rp rounded once
-                        else
-                            L += (exp_r<Real>(Eq) - fq) * s_it[s];
+                        double Eq[G];
+#pragma unroll
+                        for (int i = 0; i < G; ++i) {
+                            const int s = l * NL + q0 + i;
+                            const double *b = &s_eb[s * kEb];
+                            const double c0 = (NCOMP == 2 && comp) ? b[0] + b[kRefCoef] : b[0];
+                            // the equilibrium's exponent at this point and velocity
+                            Eq[i] = eq_exponent(b, c0, v.u);
+                            it[i] = s_it[s];
+                        }
+                        if constexpr (ER) {
+                            double g[G];
+                            exp_f64<G>(Eq, g);
+#pragma unroll
+                            for (int i = 0; i < G; ++i) dg[i] = (Real)(g[i] - (double)rp) - fq[i];  // g - rp rounded once
+                        } else {
+                            Real g[G];
+                            exp_r<G>(Eq, g);
+#pragma unroll
+                            for (int i = 0; i < G; ++i) dg[i] = g[i] - fq[i];
+                        }
                     }
-                    // the result, in FP64 for the stochastic rounding of the FP32 state
-                    double fod;
-                    if constexpr (!LSRK) {
-                        fod = A.sa.beta * ((double)fq + (double)(dt * L));
-                        fod = fma(A.sa.alpha, (double)x2[q], fod);  // (0 when not read)
-                    } else {
-                        Real dd = dt * L;
-                        dd += (Real)A.sa.lsA * (Real)x2[q];
-                        if constexpr (KEEP) stn(dFE, o + q * QB, (SReal)dd);
-                        fod = fma(A.sa.lsB, (double)dd, (double)fq);
+#pragma unroll
+                    for (int i = 0; i < G; ++i) {
+                        const int q = q0 + i;
+                        Real L = -r[q];
+                        if constexpr (COLL) L += dg[i] * it[i];
+                        // the result, in FP64 for the stochastic rounding of the FP32 state
+                        double fod;
+                        if constexpr (!LSRK) {
+                            fod = A.sa.beta * ((double)fq[i] + (double)(dt * L));
+                            fod = fma(A.sa.alpha, (double)x2[q], fod);  // (0 when not read)
+                        } else {
+                            Real dd = dt * L;
+                            dd += (Real)A.sa.lsA * (Real)x2[q];
+                            if constexpr (KEEP) stn(dFE, o + q * QB, (SReal)dd);
+                            fod = fma(A.sa.lsB, (double)dd, (double)fq[i]);
+                        }
+                        if constexpr (ER) fod += LSRK ? (double)sh : shd;
+                        Real fo;
+                        if constexpr (sizeof(Real) == 4) {
+                            rs = xorshift32(rs);
+                            fo = round_stochastic(fod, rs);
+                        } else {
+                            fo = (Real)fod;
+                        }
+                        f[q] = fo;
+                        stn(outE, o + q * QB, (SReal)fo);
                     }
-                    if constexpr (ER) fod += LSRK ? (double)sh : shd;
-                    Real fo;
-                    if constexpr (sizeof(Real) == 4) {
-                        rs = xorshift32(rs);
-                        fo = round_stochastic(fod, rs);
-                    } else {
-                        fo = (Real)fod;
-                    }
-                    f[q] = fo;
-                    stn(outE, o + q * QB, (SReal)fo);
-                    // (a fence every two points in FP32, four in FP64: the
-                    // chains in flight at once, against register pressure)
-                    if (q % (sizeof(Real) == 4 ? 2 : 4) == (sizeof(Real) == 4 ? 1 : 3)) phase_fence();
-                }
+                    // (the fences bound the chains in flight at once, against
+                    // register pressure)
+                    phase_fence();
+                };
+#pragma unroll
+                for (int q0 = 0; q0 + W <= NL; q0 += W) group(IntC<W>{}, q0);
+#pragma unroll
+                for (int q0 = NL / W * W; q0 < NL; ++q0) group(IntC<1>{}, q0);
             };
             if constexpr (STAGE) {
                 if (A.sa.scheme == 0) {
