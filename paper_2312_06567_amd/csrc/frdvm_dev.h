@@ -5,6 +5,16 @@
 
 namespace frdvm {
 
+// compile-time arguments of generic lambdas
+template <int V>
+struct IntC {
+    static constexpr int value = V;
+};
+template <bool B>
+struct BoolC {
+    static constexpr bool value = B;
+};
+
 // exp of an exponent held in FP64, rounded once to FP32.  E = (n + r) ln 2
 // with n integer and |r| <= 1/2, reduced in FP64; 2^r = e^t, t = r ln 2
 // (|t| <= 0.347), by its Taylor series to degree 8 in FP64 (error below

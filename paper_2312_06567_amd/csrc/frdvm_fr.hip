@@ -220,15 +220,6 @@ struct Vel {
     double u[3];
 };
 
-template <int V>
-struct IntC {
-    static constexpr int value = V;
-};
-template <bool B>
-struct BoolC {
-    static constexpr bool value = B;
-};
-
 __device__ __forceinline__ Vel velocity(const FrArgs &A, int k, bool lane_ok) {
     const VGrid &vg = A.vg;
     Vel v;

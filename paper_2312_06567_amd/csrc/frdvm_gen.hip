@@ -100,6 +100,15 @@ __device__ __forceinline__ float gexp<float>(double E) { return exp_to_f32(E); }
 template <>
 __device__ __forceinline__ double gexp<double>(double E) { return exp(E); }
 
+// W of them side by side
+template <int W>
+__device__ __forceinline__ void gexp(const double (&E)[W], float (&g)[W]) { exp_to_f32<W>(E, g); }
+template <int W>
+__device__ __forceinline__ void gexp(const double (&E)[W], double (&g)[W]) {
+#pragma unroll
+    for (int w = 0; w < W; ++w) g[w] = exp(E[w]);
+}
+
 // Uniform base + the lane's byte offset (a run of consecutive velocities).
 template <typename T>
 __device__ __forceinline__ T ldo(const T *base, uint32_t boff) {
@@ -385,18 +394,22 @@ __device__ __forceinline__ void load_ext(const ExtArgs<Real> &X, int d, int km0,
 // unrolled, so every value has a fixed register) and its N^3 residual
 // accumulators in its own LDS column (lane-private: no barrier between the
 // phases; in registers too, p = 2 would need 175 in FP32).  The register
-// targets are what LDS admits: 3 (FP32) / 2 (FP64) waves per SIMD at p <= 2,
-// 2 / 1 at p = 3.  (With the values of p = 3 in a second LDS column, loops
-// rolled, LDS held 4 / 2 waves per CU: 3.07 / 6.60 ms per stage at 256
-// elements, 20^3 velocities, against 1.33 / 2.62.)  What bounds it: half
-// VALU issue, half HBM (3.3-4.0 TB/s); p = 2 FP32, 2304 elements, 24^3,
-// limiter on: 5.99 -> 5.39 ms per stage with the exterior values requested a
-// direction ahead, the connectivity and the metrics of whole lines through
-// the scalar cache, one random-number hash per lane instead of per value, and
-// the traces of waves that only enter left out.
+// targets are what LDS admits, 3 (FP32) / 2 (FP64) waves per SIMD at p = 2,
+// 2 / 1 at p = 3, and at p = 1 what measured best (FP32 6: 596 us, 5: 647;
+// p = 2 FP32 at 4 spills: 5.39 for 5.22 ms).  (With the values of p = 3 in a
+// second LDS column, loops rolled, LDS held 4 / 2 waves per CU: 3.07 / 6.60 ms
+// per stage at 256 elements, 20^3 velocities, against 1.14 / 2.53.)  What
+// bounds it: half VALU issue, half HBM (3.4-4.2 TB/s); p = 2 FP32, 2304
+// elements, 24^3, limiter on: 5.99 -> 5.34 ms per stage with the exterior
+// values requested a direction ahead, the connectivity and the metrics of
+// whole lines through the scalar cache, one random-number hash per lane
+// instead of per value, and the traces of waves that only enter left out;
+// 5.22 with the points of the collision in pairs (p = 3 FP32 1.32 -> 1.14, and
+// 63 registers fewer).
 template <typename Real, int P>
 constexpr int gen_waves() {
-    return P == 3 ? (sizeof(Real) == 4 ? 2 : 1) : (sizeof(Real) == 4 ? 3 : 2);
+    if (sizeof(Real) == 8) return P == 3 ? 1 : 2;
+    return P == 3 ? 2 : (P == 2 ? 3 : 6);
 }
 // Whether the next direction's exterior values are requested ahead: where
 // that costs no wave per SIMD (at p = 2 it does in FP64 and for the residual
@@ -557,59 +570,90 @@ k_gen_stage(const GenArgs A) {
     // random bits of the stochastic rounding: one hash per lane, a xorshift
     // step per value
     uint32_t rs = sizeof(Real) == 4 ? round_bits(A.sa.seed, (uint32_t)(e * NS), (uint32_t)k) | 1u : 0u;
+    // One loop per combination of the launch-uniform switches (the collision,
+    // the RK scheme, whether dF is kept): no branch splits the points, and two
+    // chains run side by side.
+    auto points = [&](auto coll_c, auto lsrk_c, auto keep_c) __attribute__((always_inline)) {
+        constexpr bool COLL = decltype(coll_c)::value, LSRK = decltype(lsrk_c)::value;
+        constexpr bool KEEP = decltype(keep_c)::value;
+        auto group = [&](auto width, int s0, const Real *x) __attribute__((always_inline)) {
+            constexpr int W = decltype(width)::value;
+            Real g[W];
+            if constexpr (COLL) {
+                double E[W];
 #pragma unroll
-    for (int s0 = 0; s0 < NS; s0 += NFP) {
-        // a layer's second-register values requested together
-        if constexpr (AHEAD) {
-            if (s0 + NFP < NS) load_x(s0 + NFP, xv[(s0 / NFP + 1) & 1]);
-        } else {
-            load_x(s0, xv[(s0 / NFP) & 1]);
+                for (int i = 0; i < W; ++i) {
+                    const int s = s0 + i;
+                    const double *bq = &sEb[s * 8];
+                    const double c0 = ud[0] - sEv[s * 3], c1 = ud[1] - sEv[s * 3 + 1], c2 = ud[2] - sEv[s * 3 + 2];
+                    double t0 = bq[0] * c0;
+                    t0 = fma(bq[3], c1, t0);
+                    t0 = fma(bq[4], c2, t0);
+                    double t1 = bq[1] * c1;
+                    t1 = fma(bq[5], c2, t1);
+                    const double t2 = bq[2] * c2;
+                    E[i] = fma(c0, t0, comp ? bq[6] + sLg[s] : bq[6]);
+                    E[i] = fma(c1, t1, E[i]);
+                    E[i] = fma(c2, t2, E[i]);
+                }
+                gexp<W>(E, g);
+            }
+#pragma unroll
+            for (int i = 0; i < W; ++i) {
+                const int s = s0 + i;
+                const Real fq = fv[s];
+                Real L = -sa[s][lane] * gJ[s];
+                if constexpr (COLL) L += (g[i] - fq) * (Real)sEb[s * 8 + 7];
+                // the result, in FP64 for the stochastic rounding of the FP32 state
+                double fod;
+                if constexpr (!LSRK) {
+                    fod = A.sa.beta * ((double)fq + (double)(dt * L));
+                    fod = fma(A.sa.alpha, (double)x[i], fod);  // (0 when not read)
+                } else {
+                    Real dd = dt * L;
+                    dd += (Real)A.sa.lsA * x[i];
+                    if constexpr (KEEP) sto(dFE + s * nu, ko, dd);
+                    fod = fma(A.sa.lsB, (double)dd, (double)fq);
+                }
+                Real fo;
+                if constexpr (sizeof(Real) == 4) {
+                    rs = xorshift32(rs);
+                    fo = round_stochastic(fod, rs);
+                } else {
+                    fo = (Real)fod;
+                }
+                fv[s] = fo;
+                lim_min = s == 0 ? fo : (fo < lim_min ? fo : lim_min);
+                sto(outE + s * nu, ko, fo);
+            }
+            // (the fences bound the chains in flight at once)
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+        };
+#pragma unroll
+        for (int s0 = 0; s0 < NS; s0 += NFP) {
+            // a layer's second-register values requested together
+            if constexpr (AHEAD) {
+                if (s0 + NFP < NS) load_x(s0 + NFP, xv[(s0 / NFP + 1) & 1]);
+            } else {
+                load_x(s0, xv[(s0 / NFP) & 1]);
+            }
+            const Real *x = xv[(s0 / NFP) & 1];
+#pragma unroll
+            for (int r = 0; r + 2 <= NFP; r += 2) group(IntC<2>{}, s0 + r, x + r);
+            if constexpr (NFP % 2) group(IntC<1>{}, s0 + NFP - 1, x + NFP - 1);
         }
-#pragma unroll
-        for (int r = 0; r < NFP; ++r) {
-            const int s = s0 + r;
-            const Real fq = fv[s];
-            Real L = -sa[s][lane] * gJ[s];
-            if (collide) {
-                const double *bq = &sEb[s * 8];
-                const double c0 = ud[0] - sEv[s * 3], c1 = ud[1] - sEv[s * 3 + 1], c2 = ud[2] - sEv[s * 3 + 2];
-                double t0 = bq[0] * c0;
-                t0 = fma(bq[3], c1, t0);
-                t0 = fma(bq[4], c2, t0);
-                double t1 = bq[1] * c1;
-                t1 = fma(bq[5], c2, t1);
-                const double t2 = bq[2] * c2;
-                double E = fma(c0, t0, comp ? bq[6] + sLg[s] : bq[6]);
-                E = fma(c1, t1, E);
-                E = fma(c2, t2, E);
-                L += (gexp<Real>(E) - fq) * (Real)bq[7];
-            }
-            // the result, in FP64 for the stochastic rounding of the FP32 state
-            double fod;
-            if (A.sa.scheme == 0) {
-                fod = A.sa.beta * ((double)fq + (double)(dt * L));
-                if (useX) fod = fma(A.sa.alpha, (double)xv[(s0 / NFP) & 1][r], fod);
-            } else {
-                Real dd = dt * L;
-                if (useX) dd += (Real)A.sa.lsA * xv[(s0 / NFP) & 1][r];
-                if (A.sa.keep_dF) sto(dFE + s * nu, ko, dd);
-                fod = fma(A.sa.lsB, (double)dd, (double)fq);
-            }
-            Real fo;
-            if constexpr (sizeof(Real) == 4) {
-                rs = xorshift32(rs);
-                fo = round_stochastic(fod, rs);
-            } else {
-                fo = (Real)fod;
-            }
-            fv[s] = fo;
-            lim_min = s == 0 ? fo : (fo < lim_min ? fo : lim_min);
-            sto(outE + s * nu, ko, fo);
-            // two points' chains in flight at a time
-            if (r % 2 == 1) {
-                asm volatile("" ::: "memory");
-                __builtin_amdgcn_sched_barrier(0);
-            }
+    };
+    if constexpr (STAGE) {
+        if (A.sa.scheme == 0) {
+            if (collide) points(BoolC<true>{}, BoolC<false>{}, BoolC<false>{});
+            else points(BoolC<false>{}, BoolC<false>{}, BoolC<false>{});
+        } else if (A.sa.keep_dF) {
+            if (collide) points(BoolC<true>{}, BoolC<true>{}, BoolC<true>{});
+            else points(BoolC<false>{}, BoolC<true>{}, BoolC<true>{});
+        } else {
+            if (collide) points(BoolC<true>{}, BoolC<true>{}, BoolC<false>{});
+            else points(BoolC<false>{}, BoolC<true>{}, BoolC<false>{});
         }
     }
     // Traces of the result where the velocity leaves; with the positivity limiter
