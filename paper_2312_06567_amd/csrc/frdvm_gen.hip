@@ -93,14 +93,7 @@ __device__ __forceinline__ Metrics<double> metrics(const GenArgs &A, double) {
     return {(cptr<double>)A.S, (cptr<double>)A.ijac, (cptr<double>)A.nf};
 }
 
-template <typename Real>
-__device__ __forceinline__ Real gexp(double E);
-template <>
-__device__ __forceinline__ float gexp<float>(double E) { return exp_to_f32(E); }
-template <>
-__device__ __forceinline__ double gexp<double>(double E) { return exp(E); }
-
-// W of them side by side
+// exp of W exponents, side by side
 template <int W>
 __device__ __forceinline__ void gexp(const double (&E)[W], float (&g)[W]) { exp_to_f32<W>(E, g); }
 template <int W>
@@ -795,13 +788,12 @@ __device__ __forceinline__ MixOps<double> mix_ops(const MixArgs &A, double) {
 }
 
 // The wave's element, its lane's velocity and the velocity's contravariant
-// components; an idle lane (past the last node) works on node 0 and stores
-// nothing.
+// components; a lane past the last node does and stores exactly what the lane
+// of the last node (of the same wave) does.
 template <typename Real>
 struct MixLane {
     int64_t e, p0, t0, nu;
     int k;
-    bool act;
     uint32_t ko;
     double ud[3];
     Real u0, u1, u2, c[3];
@@ -809,15 +801,14 @@ struct MixLane {
     __device__ __forceinline__ MixLane(const MixArgs &A, const MixOps<Real> &op) {
         e = A.elems[blockIdx.x / A.nvw];
         k = (int)(blockIdx.x % A.nvw) * kGWave + threadIdx.x;
-        act = k < A.nu;
-        const int kk = act ? k : 0;
+        k = k < A.nu ? k : A.nu - 1;
         nu = A.nu;
-        ko = (uint32_t)kk * (uint32_t)sizeof(Real);
+        ko = (uint32_t)k * (uint32_t)sizeof(Real);
         p0 = A.poff[e];
         t0 = A.toff[e];
         g = op.geo + e * kMixGeo;
         int iv[3];
-        split_k(A.vg, kk, iv);
+        split_k(A.vg, k, iv);
 #pragma unroll
         for (int d = 0; d < 3; ++d) ud[d] = node_u(A.vg, d, iv[d]);
         u0 = (Real)ud[0];
@@ -829,47 +820,94 @@ struct MixLane {
     __device__ __forceinline__ Real un(int f) const { return u0 * g[9 + 3 * f] + u1 * g[10 + 3 * f] + u2 * g[11 + 3 * f]; }
 };
 
-// Collision source and Runge-Kutta combination of point i with value fq,
-// advective residual L and second-register value xv; stores the result.
-// rs: the lane's stream of random bits (one xorshift step per value).
-template <typename Real>
-__device__ __forceinline__ Real mix_point(const MixArgs &A, const MixLane<Real> &v, int i, Real fq, Real L, Real xv,
-                                          bool useX, uint32_t &rs) {
-    if (A.sa.collide) {
-        const cptr<double> q = (cptr<double>)A.sa.eq + (v.p0 + i) * kEqW;
-        const double c0 = v.ud[0] - q[EQ_V], c1 = v.ud[1] - q[EQ_V + 1], c2 = v.ud[2] - q[EQ_V + 2];
-        double t0 = -0.5 * q[EQ_B] * c0;
-        t0 = fma(-q[EQ_B + 3], c1, t0);
-        t0 = fma(-q[EQ_B + 4], c2, t0);
-        double t1 = -0.5 * q[EQ_B + 1] * c1;
-        t1 = fma(-q[EQ_B + 5], c2, t1);
-        const double t2 = -0.5 * q[EQ_B + 2] * c2;
-        double E = fma(c0, t0, q[EQ_C0]);
-        E = fma(c1, t1, E);
-        E = fma(c2, t2, E);
-        L += (gexp<Real>(E) - fq) * (Real)q[EQ_INVTAU];
-    }
+// Collision source and Runge-Kutta combination of an element's points with
+// values val(i) and advective residuals res(i); stores the results.  One loop
+// per combination of the launch-uniform switches (the collision, the RK
+// scheme, whether dF is kept), XB second-register values requested together
+// and two points' chains side by side.
+template <typename Real, int NS, int XB, typename Val, typename Res>
+__device__ __forceinline__ void mix_points(const MixArgs &A, const MixLane<Real> &v, Val val, Res res) {
+    const bool useX = A.sa.scheme == 0 ? A.sa.alpha != 0.0 : A.sa.lsA != 0.0;
+    const Real *XE = reinterpret_cast<const Real *>(A.sa.scheme == 0 ? A.sa.fn : A.sa.dF) + v.p0 * v.nu;
+    Real *dFE = reinterpret_cast<Real *>(A.sa.dF) + v.p0 * v.nu;
+    Real *outE = reinterpret_cast<Real *>(A.sa.fout) + v.p0 * v.nu;
     const Real dt = (Real)A.sa.dt;
-    const int64_t row = (v.p0 + i) * v.nu;
-    double fod;
+    // the lane's stream of random bits, one xorshift step per value
+    uint32_t rs = sizeof(Real) == 4 ? round_bits(A.sa.seed, (uint32_t)v.p0, (uint32_t)v.k) | 1u : 0u;
+    auto points = [&](auto coll_c, auto lsrk_c, auto keep_c) __attribute__((always_inline)) {
+        constexpr bool COLL = decltype(coll_c)::value, LSRK = decltype(lsrk_c)::value;
+        constexpr bool KEEP = decltype(keep_c)::value;
+        auto group = [&](auto width, int i0, const Real *x) __attribute__((always_inline)) {
+            constexpr int W = decltype(width)::value;
+            Real g[W], it[W];
+            if constexpr (COLL) {
+                double E[W];
+#pragma unroll
+                for (int w = 0; w < W; ++w) {
+                    const cptr<double> q = (cptr<double>)A.sa.eq + (v.p0 + i0 + w) * kEqW;
+                    const double c0 = v.ud[0] - q[EQ_V], c1 = v.ud[1] - q[EQ_V + 1], c2 = v.ud[2] - q[EQ_V + 2];
+                    double t0 = -0.5 * q[EQ_B] * c0;
+                    t0 = fma(-q[EQ_B + 3], c1, t0);
+                    t0 = fma(-q[EQ_B + 4], c2, t0);
+                    double t1 = -0.5 * q[EQ_B + 1] * c1;
+                    t1 = fma(-q[EQ_B + 5], c2, t1);
+                    const double t2 = -0.5 * q[EQ_B + 2] * c2;
+                    E[w] = fma(c0, t0, q[EQ_C0]);
+                    E[w] = fma(c1, t1, E[w]);
+                    E[w] = fma(c2, t2, E[w]);
+                    it[w] = (Real)q[EQ_INVTAU];
+                }
+                gexp<W>(E, g);
+            }
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                const int i = i0 + w;
+                const Real fq = val(i);
+                Real L = res(i);
+                if constexpr (COLL) L += (g[w] - fq) * it[w];
+                double fod;
+                if constexpr (!LSRK) {
+                    fod = A.sa.beta * ((double)fq + (double)(dt * L));
+                    fod = fma(A.sa.alpha, (double)x[w], fod);  // (0 when not read)
+                } else {
+                    Real dd = dt * L;
+                    dd += (Real)A.sa.lsA * x[w];
+                    if constexpr (KEEP) sto(dFE + i * v.nu, v.ko, dd);
+                    fod = fma(A.sa.lsB, (double)dd, (double)fq);
+                }
+                Real fo;
+                if constexpr (sizeof(Real) == 4) {
+                    rs = xorshift32(rs);
+                    fo = round_stochastic(fod, rs);
+                } else {
+                    fo = (Real)fod;
+                }
+                sto(outE + i * v.nu, v.ko, fo);
+            }
+        };
+#pragma unroll
+        for (int i0 = 0; i0 < NS; i0 += XB) {
+            Real xv[XB];
+#pragma unroll
+            for (int x = 0; x < XB; ++x)
+                if (i0 + x < NS) xv[x] = useX ? ldo(XE + (i0 + x) * v.nu, v.ko) : Real(0);
+#pragma unroll
+            for (int x = 0; x < XB; x += 2) {
+                if (x + 2 <= XB && i0 + x + 2 <= NS) group(IntC<2>{}, i0 + x, &xv[x]);
+                else if (i0 + x < NS) group(IntC<1>{}, i0 + x, &xv[x]);
+            }
+        }
+    };
     if (A.sa.scheme == 0) {
-        fod = A.sa.beta * ((double)fq + (double)(dt * L));
-        if (useX) fod = fma(A.sa.alpha, (double)xv, fod);
+        if (A.sa.collide) points(BoolC<true>{}, BoolC<false>{}, BoolC<false>{});
+        else points(BoolC<false>{}, BoolC<false>{}, BoolC<false>{});
+    } else if (A.sa.keep_dF) {
+        if (A.sa.collide) points(BoolC<true>{}, BoolC<true>{}, BoolC<true>{});
+        else points(BoolC<false>{}, BoolC<true>{}, BoolC<true>{});
     } else {
-        Real dd = dt * L;
-        if (useX) dd += (Real)A.sa.lsA * xv;
-        if (v.act && A.sa.keep_dF) sto(reinterpret_cast<Real *>(A.sa.dF) + row, v.ko, dd);
-        fod = fma(A.sa.lsB, (double)dd, (double)fq);
+        if (A.sa.collide) points(BoolC<true>{}, BoolC<true>{}, BoolC<false>{});
+        else points(BoolC<false>{}, BoolC<true>{}, BoolC<false>{});
     }
-    Real fo;
-    if constexpr (sizeof(Real) == 4) {
-        rs = xorshift32(rs);
-        fo = round_stochastic(fod, rs);
-    } else {
-        fo = (Real)fod;
-    }
-    if (v.act) sto(reinterpret_cast<Real *>(A.sa.fout) + row, v.ko, fo);
-    return fo;
 }
 
 // Hexahedra: dense operators; up to 27 points the values and residuals in
@@ -949,17 +987,11 @@ __global__ __launch_bounds__(kGWave) void k_mix_hex(const MixArgs A) {
     };
     if (MODE == GMODE_RESID) {
         Real *R = reinterpret_cast<Real *>(A.sa.fout) + v.p0 * nu;
-        if (v.act)
 #pragma unroll
-            for (int i = 0; i < NS; ++i) sto(R + i * nu, v.ko, res(i));
+        for (int i = 0; i < NS; ++i) sto(R + i * nu, v.ko, res(i));
         return;
     }
-    const bool useX = A.sa.scheme == 0 ? A.sa.alpha != 0.0 : A.sa.lsA != 0.0;
-    const Real *XE = reinterpret_cast<const Real *>(A.sa.scheme == 0 ? A.sa.fn : A.sa.dF) + v.p0 * nu;
-    uint32_t rs = sizeof(Real) == 4 ? round_bits(A.sa.seed, (uint32_t)v.p0, (uint32_t)v.k) | 1u : 0u;
-#pragma unroll
-    for (int i = 0; i < NS; ++i)
-        mix_point(A, v, i, val(i), res(i), useX ? ldo(XE + i * nu, v.ko) : Real(0), useX, rs);
+    if constexpr (MODE == GMODE_STAGE) mix_points<Real, NS, 2>(A, v, val, res);
 }
 
 // Prisms (DIM 2: the triangle's points on the PL = p + 1 Gauss-Lobatto layers
@@ -970,13 +1002,28 @@ __global__ __launch_bounds__(kGWave) void k_mix_hex(const MixArgs A) {
 // enters is decided once per face: a wave none of whose velocities enter
 // skips the face, and the neighbour's values of a face are requested
 // together.  What bounds it: HBM (f, the neighbours' face values, the result,
-// the second register).  A stage of 51,200 points at p = 3, 24^3 velocities,
-// FP32 low-storage: tetrahedra 3.44 -> 1.64 ms (4.5 TB/s of those bytes),
-// prisms 2.70 -> 1.23 ms (3.9 TB/s); before, with dense tetrahedral
-// products, the face points one after the other through LDS and their
-// traces stored and read back, VALU issue and load latency bound it.
+// the second register) and, for tetrahedra, VALU issue.  A stage of 51,200
+// points at p = 3, 24^3 velocities, FP32 low-storage: tetrahedra 3.44 -> 1.64 ms
+// (4.2 TB/s), prisms 2.70 -> 1.22 ms (3.7 TB/s); before, with dense
+// tetrahedral products, the face points one after the other through LDS and
+// their traces stored and read back, VALU issue and load latency bound it.
+// Points in pairs without branches (mix_points; before, each point waited
+// for its record and branched on the collision, the scheme, the register and
+// the idle lanes): tetrahedra 1.64 -> 1.53 ms, prisms 1.22 -> 1.13 ms, FP64
+// tetrahedra 0.63 -> 0.59 ms, prisms 0.55 -> 0.50 ms at 21,600 points, 20^3.
+// Waves per SIMD the registers are held to: what the kernel needs by itself,
+// and where a few registers stand in the way of one more wave (p = 3: prisms
+// FP32, tetrahedra FP64) that wave: 1.25 / 1.05 ms and 0.69 / 0.59 ms per
+// stage without / with it.  (6 waves for FP32 tetrahedra leave arrays in
+// scratch memory: 34 ms.)
+template <typename Real, int DIM, int P>
+constexpr int mix_waves() {
+    if (DIM == 2) return P == 1 ? 8 : (P == 2 ? (sizeof(Real) == 4 ? 5 : 4) : (sizeof(Real) == 4 ? 4 : 2));
+    return P == 1 ? 8 : (P == 2 ? (sizeof(Real) == 4 ? 6 : 5) : (sizeof(Real) == 4 ? 5 : 4));
+}
 template <typename Real, int DIM, int P, int MODE>
-__global__ __launch_bounds__(kGWave) void k_mix_simplex(const MixArgs A) {
+__global__ __launch_bounds__(kGWave) __attribute__((amdgpu_waves_per_eu(mix_waves<Real, DIM, P>()))) void
+k_mix_simplex(const MixArgs A) {
     using S = Simplex<DIM, P>;
     constexpr auto tb = S::table();
     constexpr auto rest = S::rest();
@@ -1115,25 +1162,15 @@ __global__ __launch_bounds__(kGWave) void k_mix_simplex(const MixArgs A) {
     }
     if (MODE == GMODE_RESID) {
         Real *R = reinterpret_cast<Real *>(A.sa.fout) + v.p0 * nu;
-        if (v.act)
 #pragma unroll
-            for (int i = 0; i < NS; ++i) sto(R + i * nu, v.ko, r[i]);
+        for (int i = 0; i < NS; ++i) sto(R + i * nu, v.ko, r[i]);
         return;
     }
-    // collision source and the Runge-Kutta combination, a layer's (the
-    // tetrahedron: ten points') second-register values requested together
-    constexpr int XB = DIM == 2 ? NT : (NS < 10 ? NS : 10);
-    const bool useX = A.sa.scheme == 0 ? A.sa.alpha != 0.0 : A.sa.lsA != 0.0;
-    const Real *XE = reinterpret_cast<const Real *>(A.sa.scheme == 0 ? A.sa.fn : A.sa.dF) + v.p0 * nu;
-    uint32_t rs = sizeof(Real) == 4 ? round_bits(A.sa.seed, (uint32_t)v.p0, (uint32_t)v.k) | 1u : 0u;
-#pragma unroll
-    for (int i0 = 0; i0 < NS; i0 += XB) {
-        Real xv[XB];
-#pragma unroll
-        for (int x = 0; x < XB; ++x) xv[x] = useX ? ldo(XE + (i0 + x) * nu, v.ko) : Real(0);
-#pragma unroll
-        for (int x = 0; x < XB; ++x) mix_point(A, v, i0 + x, fv[i0 + x], r[i0 + x], xv[x], useX, rs);
-    }
+    // a layer's (the tetrahedron: ten points') second-register values together
+    if constexpr (MODE == GMODE_STAGE)
+        mix_points<Real, NS, DIM == 2 ? NT : (NS < 10 ? NS : 10)>(
+            A, v, [&](int i) __attribute__((always_inline)) { return fv[i]; },
+            [&](int i) __attribute__((always_inline)) { return r[i]; });
 }
 
 template <typename Real, int NS, int NFT>
