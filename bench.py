@@ -325,25 +325,26 @@ def mixed_flops_per_dof(mesh, p: int) -> float:
 
 
 def mixed_roofline(r, p, mesh):
-    """The mixed-mesh stage (dense element operators, VALU) against the
-    vector ALU peak of its precision: algorithmic flops of the stage launches
-    over their summed HIP-event durations."""
+    """The mixed-mesh stage against the vector ALU peak of its precision: flops
+    of the nodal operators (the kernels execute fewer: they skip zeros and
+    differentiate at the points of degree p - 1) over the summed HIP-event
+    durations of its launches; and its HBM bytes."""
     ms, n = r["prof"]["stage"]
     fpd = mixed_flops_per_dof(mesh, p)
     ach = fpd * r["dof"] * 3 * r["steps"] / (ms / 1e3) / 1e12
     peak = VALU_PEAK_TFLOPS[0 if r["precision"] == 0 else 1]
     # HBM: read f, write the result, the low-storage register (read in 2 of 3
-    # stages, written in 2 of 3), read the neighbour traces where the velocity
-    # enters (half the face points), write the result's traces, read the
-    # result again for its moments
+    # stages, written in 2 of 3), read the neighbours' face values where the
+    # velocity enters (half the face points), read the result again for its
+    # moments
     import numpy as np
     counts = np.bincount(np.asarray(mesh["elem_type"]), minlength=3)
     pts = sum(int(counts[t]) * MIXED_SIZES[p][t][0] for t in range(3))
     fpts = sum(int(counts[t]) * MIXED_SIZES[p][t][1] for t in range(3))
-    vals = 3.0 + (4.0 / 3.0 if r["rk"] == 1 else 2.0 / 3.0) + 1.5 * fpts / pts
+    vals = 3.0 + (4.0 / 3.0 if r["rk"] == 1 else 2.0 / 3.0) + 0.5 * fpts / pts
     bpd = vals * (8 if r["precision"] == 0 else 4)
     gbs = bpd * r["dof"] * 3 * r["steps"] / (ms / 1e3) / 1e9
-    return {"kernel": "k_mix_stage (+ k_gen_moments), element operators (prisms: layer/column structure)", "bound": "alu", "achieved": ach,
+    return {"kernel": "k_mix_simplex / k_mix_hex (+ k_gen_moments), operator flops of the nodal form (prisms: layer/column structure)", "bound": "alu", "achieved": ach,
             "peak": peak, "unit": "TFLOP/s", "frac": ach / peak, "traffic": None,
             "flops_per_dof": fpd, "avg_launch_ms": ms / max(n, 1),
             "hbm_bytes_per_dof": bpd, "hbm_GBps": gbs, "frac_hbm": gbs / HBM_PEAK_GBS}
