@@ -435,17 +435,25 @@ int setup_general(fr_dvm *h, const fr_dvm_mesh *mesh, std::vector<double> &wq3J)
         return rc;
     if ((rc = dev_alloc(h, &h->d_ijac, ijac.size())) || (rc = upload(h, h->d_ijac, ijac.data(), ijac.size() * sizeof(double))))
         return rc;
-    // normals with a margin in the fourth place: |n|_1 times a bound on how far
+    // normals with a margin in the fourth place; a trace is stored for every
+    // velocity u with u.n + margin |u|_1 > 0.  |n|_1 times a bound on how far
     // (relative to |n|_1 |u|_1) the rounded u.n of the two sides of a face may
     // differ, the rounding of three products and the gap of the two normals
-    // allowed above; a trace is stored for every velocity that leaves within it
+    // allowed above.  A specular face reads its own trace at the mirrored
+    // velocity u' where u enters: its plane may be tilted a little off the
+    // coordinate plane (the check above), and with the normal's tangential
+    // part n_t, u'.n = -u.n + 2 u.n_t > -2 |n_t|_1 |u|_1, which the margin has
+    // to cover too.
     std::vector<double> nf4(nf.size() / 3 * 4);
     std::vector<float> nff4(nf4.size());
     for (size_t i = 0; i < nf.size() / 3; ++i) {
-        const double l1 = std::fabs(nf[3 * i]) + std::fabs(nf[3 * i + 1]) + std::fabs(nf[3 * i + 2]);
-        for (int c = 0; c < 4; ++c) {
-            nf4[4 * i + c] = c < 3 ? nf[3 * i + c] : 1e-8 * l1;
-            nff4[4 * i + c] = (float)(c < 3 ? nf[3 * i + c] : 1e-5 * l1);
+        const double *v = &nf[3 * i];
+        const double l1 = std::fabs(v[0]) + std::fabs(v[1]) + std::fabs(v[2]);
+        const int32_t *c = &conn[i / nfp * 4];
+        const double tangential = c[0] < 0 && c[3] == 3 ? 2.0 * (l1 - std::fabs(v[c[2]])) : 0.0;
+        for (int k = 0; k < 4; ++k) {
+            nf4[4 * i + k] = k < 3 ? v[k] : tangential + 1e-8 * l1;
+            nff4[4 * i + k] = (float)(k < 3 ? v[k] : tangential + 1e-5 * l1);
         }
     }
     if ((rc = dev_alloc(h, &h->d_nf, nf4.size())) || (rc = upload(h, h->d_nf, nf4.data(), nf4.size() * sizeof(double))))
