@@ -261,7 +261,9 @@ typedef struct {
 int fr_dvm_create_mixed(const fr_dvm_mixed_mesh *mesh, int order, const fr_dvm_vgrid *grid, fr_dvm_t *out);
 
 /* Set physics / precision / solver parameters; allocates the work buffers
- * of the chosen precision.  Must be called before any compute call. */
+ * of the chosen precision.  Must be called before any compute call.  After a
+ * call that failed to allocate or upload, compute calls return FR_DVM_EINVAL
+ * until a call succeeds; parameters refused as invalid change nothing. */
 int fr_dvm_set_params(fr_dvm_t h, const fr_dvm_params *p);
 
 /* Run subsequent calls on this hipStream_t (passed as void*). */

@@ -14,7 +14,7 @@ namespace {
 
 int ready(fr_dvm *h) {
     if (!h) return FR_DVM_EINVAL;
-    if (!h->have_params) return h->fail(FR_DVM_EINVAL, "fr_dvm_set_params has not been called");
+    if (!h->have_params) return h->fail(FR_DVM_EINVAL, "fr_dvm_set_params has not been called, or its last call failed");
     return FR_DVM_OK;
 }
 

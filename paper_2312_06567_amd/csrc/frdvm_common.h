@@ -150,6 +150,7 @@ struct fr_dvm {
 
     // work buffers
     void *d_reg = nullptr;       // second RK register [ne*ns*nu]
+    size_t reg_bytes = 0;
     void *d_tr[2] = {nullptr, nullptr};
     size_t tr_bytes[2] = {0, 0};
     int keep_traces = 0;   // no room for stage values in place of traces, see no_traces()

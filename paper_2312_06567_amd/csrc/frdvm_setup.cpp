@@ -165,6 +165,7 @@ int dev_alloc(fr_dvm *h, T **p, size_t count) {
     if (count == 0) return FR_DVM_OK;
     if (hipMalloc(reinterpret_cast<void **>(p), count * sizeof(T)) != hipSuccess) {
         *p = nullptr;
+        hipGetLastError();  // (this allocation's: not the next launch's)
         return h->fail(FR_DVM_ENOMEM, "hipMalloc of " + std::to_string(count * sizeof(T)) + " bytes failed");
     }
     h->owned_bytes += count * sizeof(T);
@@ -472,7 +473,7 @@ int setup_general(fr_dvm *h, const fr_dvm_mesh *mesh, std::vector<double> &wq3J)
         return rc;
     if ((rc = dev_alloc(h, &h->d_rw, (size_t)ne * 6 * nfp))) return rc;
     if ((rc = dev_alloc(h, &h->d_mw, (size_t)h->vg.nu))) return rc;
-    if (h->ncomp == 2 && (rc = dev_alloc(h, &h->d_gfp, (size_t)ne * ns))) return rc;
+    if (h->ncomp == 2 && !h->d_gfp && (rc = dev_alloc(h, &h->d_gfp, (size_t)ne * ns))) return rc;
     return dev_alloc(h, &h->d_finf, (size_t)h->vg.nu * h->ncomp);
 }
 
@@ -662,11 +663,8 @@ int alloc_traces(fr_dvm *h) {
         }
         if (b == n) return FR_DVM_OK;
         h->d_tr[b] = nullptr;
-        if (!values || h->mx) {
-            h->have_params = false;  // (not ready for a step)
-            return h->fail(FR_DVM_ENOMEM, "trace allocation failed");
-        }
         hipGetLastError();  // (the failed allocation's: not the next launch's)
+        if (!values || h->mx) return h->fail(FR_DVM_ENOMEM, "trace allocation failed");
         free_traces(h);
         h->keep_traces = 1;
     }
@@ -675,9 +673,13 @@ int alloc_traces(fr_dvm *h) {
 // A box handle moves to the general-mesh path (the positivity limiter runs
 // in the general stage kernel): pointwise metrics, full traces, its own
 // boundary tables.  The box path's trace buffers are released here (their
-// size depends on the path) and reallocated by the caller.
+// size depends on the path) and reallocated by the caller.  If it fails the
+// handle is a box again.
 int move_to_general(fr_dvm *h) {
     free_traces(h);
+    const TraceLayout box_tl = h->tl;
+    const std::vector<double> box_detJ = h->h_detJ;
+    const double box_hmin = h->hmin;
     const fr_dvm::MeshCopy &mc = h->mesh_copy;
     fr_dvm_mesh m;
     m.n_elem = mc.n_elem;
@@ -692,6 +694,12 @@ int move_to_general(fr_dvm *h) {
     std::vector<double> wq3J(h->ne * h->ns);
     int rc = setup_general(h, &m, wq3J);
     if (!rc) rc = upload(h, h->d_wq3J, wq3J.data(), wq3J.size() * sizeof(double));
+    if (rc) {
+        h->axis_mode = true;
+        h->tl = box_tl;
+        h->h_detJ = box_detJ;
+        h->hmin = box_hmin;
+    }
     return rc;
 }
 
@@ -713,7 +721,11 @@ extern "C" int fr_dvm_set_params(fr_dvm_t h, const fr_dvm_params *p) {
     if (p->overlap != 0 && p->overlap != 1) return h->fail(FR_DVM_EINVAL, "overlap must be 0 or 1");
     if (p->positivity != 0 && p->positivity != 1) return h->fail(FR_DVM_EINVAL, "positivity must be 0 or 1");
     if (h->mx && p->positivity) return h->fail(FR_DVM_EUNSUPPORTED, "no positivity limiter on mixed meshes");
-    bool realloc_all = !h->have_params || p->precision != h->prm.precision;
+    // From here on a failure (of a device allocation, say) may leave any of
+    // the buffers missing: the handle has no parameters until all is done.
+    const bool had_params = h->have_params;
+    h->have_params = false;
+    bool realloc_all = !had_params || p->precision != h->prm.precision;
     if (p->positivity && h->axis_mode) {
         int rc0 = move_to_general(h);
         if (rc0) return rc0;
@@ -722,9 +734,7 @@ extern "C" int fr_dvm_set_params(fr_dvm_t h, const fr_dvm_params *p) {
     // moment record: rho, rho U, then E (BGK) or the raw second moments (ES),
     // plus the integral of G for the reduced pair
     int nmom = ((p->model == FR_DVM_ESBGK) ? 10 : 5) + (h->ncomp == 2 ? 1 : 0);
-    bool realloc_mom = !h->have_params || nmom != h->nmom;
-    // element size of the buffers allocated under the previous parameters
-    const size_t es_old = h->have_params && h->prm.precision != FR_DVM_FP64 ? sizeof(float) : sizeof(double);
+    bool realloc_mom = !had_params || nmom != h->nmom;
     h->prm = *p;
     h->nmom = nmom;
     h->stage_count = 0;
@@ -733,10 +743,15 @@ extern "C" int fr_dvm_set_params(fr_dvm_t h, const fr_dvm_params *p) {
     int64_t nu = h->vg.nu * h->ncomp;  // state values per point
     int rc;
     if (realloc_all) {
-        if (h->d_reg) { hipFree(h->d_reg); h->owned_bytes -= npts * nu * es_old; h->d_reg = nullptr; }
+        if (h->d_reg) { hipFree(h->d_reg); h->owned_bytes -= h->reg_bytes; h->d_reg = nullptr; }
         free_traces(h);
-        if (hipMalloc(&h->d_reg, npts * nu * es) != hipSuccess) { h->d_reg = nullptr; return h->fail(FR_DVM_ENOMEM, "register allocation failed"); }
-        h->owned_bytes += npts * nu * es;
+        if (hipMalloc(&h->d_reg, npts * nu * es) != hipSuccess) {
+            h->d_reg = nullptr;
+            hipGetLastError();  // (this allocation's: not the next launch's)
+            return h->fail(FR_DVM_ENOMEM, "register allocation failed");
+        }
+        h->reg_bytes = npts * nu * es;
+        h->owned_bytes += h->reg_bytes;
         if ((rc = alloc_traces(h))) return rc;
         if ((rc = dev_alloc(h, &h->d_eq, npts * kEqW))) return rc;
         for (int b = 0; b < 3; ++b)
