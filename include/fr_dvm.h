@@ -61,7 +61,7 @@ extern "C" {
 #define FR_DVM_FP32 1
 /* FP32 deviation storage: f buffers are float, the FR/RK arithmetic of a
  * stage is FP32, moments and Newton FP64.  Inside one fr_dvm_rk_step(s)
- * call every stage leaves its result in the caller's buffer as the FP32
+ * call every stage but the last leaves its result as the FP32
  * deviation d = f - r_e from an element reference r_e, and its outflow
  * traces likewise: r_e(u) = exp of a quadratic exponent in u whose
  * coefficients are the means over the element's solution points of those

@@ -133,18 +133,27 @@ StageArgs stage_args(fr_dvm *h, void *f, double dt, int st, int collide) {
         a.keep_dF = st < 2;
         a.f = f;
         a.fout = f;
-        a.dF = h->d_reg;
+        a.fn = a.dF = h->d_reg;
     }
     if (no_traces(h)) {
         // a stage reads its neighbours' traces from the stage value and never
         // writes over it: the step goes from the caller's buffer through two
-        // of the handle's and back
-        void *v[2];
-        v[0] = a.scheme == 0 ? h->d_reg : h->d_tr[0];
-        v[1] = a.scheme == 0 ? h->d_tr[0] : h->d_tr[1];
-        a.f = st == 0 ? f : v[st - 1];
-        a.fout = st == 2 ? f : v[st];
+        // of the handle's and back.  The second register is read and written
+        // point by point, so a stage's result may go over the register it
+        // reads.  SSP:  f -> reg -> v -> f, with f^n in f.  Low storage:
+        // f -> v, dF to reg; v -> reg (over dF), dF to f, which nobody
+        // reads any more; reg -> f (over dF).
+        void *v = h->d_tr[0];
         a.tr_in = a.tr_out = nullptr;
+        if (a.scheme == 0) {
+            a.f = st == 0 ? f : (st == 1 ? h->d_reg : v);
+            a.fout = st == 0 ? h->d_reg : (st == 1 ? v : f);
+        } else {
+            a.f = st == 0 ? f : (st == 1 ? v : h->d_reg);
+            a.fout = st == 0 ? v : (st == 1 ? h->d_reg : f);
+            a.fn = st == 2 ? f : h->d_reg;
+            a.dF = st == 1 ? f : h->d_reg;
+        }
     }
     return a;
 }

@@ -153,7 +153,6 @@ struct fr_dvm {
     size_t reg_bytes = 0;
     void *d_tr[2] = {nullptr, nullptr};
     size_t tr_bytes[2] = {0, 0};
-    int keep_traces = 0;   // no room for stage values in place of traces, see no_traces()
     int cur_tr = 0;
     double *d_Q = nullptr;       // [ne*ns][nmom]
     int nsplit[2] = {1, 1};      // workgroups per element of the box kernel: stage and residual, prime pass
@@ -199,10 +198,13 @@ namespace frdvm {
 // Meshes whose flux points are solution points: mixed ones, and boxes with
 // Gauss-Lobatto points.  A stage reads its neighbours' traces from the stage
 // value itself, so it must not write over that value, and no traces are kept:
-// d_tr holds stage values.  A box for which the device has no room for these
-// keeps traces (shorter than a stage value from p = 3 on).
+// d_tr[0] holds a stage value, and there is no second buffer.  That is never
+// more memory than two buffers of traces (p = 3: 1 state against 1.5), except
+// on box grids where most nodes have zero velocity in some direction and so
+// no trace there (one node in each of two directions); these keep traces.
 inline bool no_traces(const fr_dvm *h) {
-    return h->mx || (h->axis_mode && h->nodes == FR_DVM_NODES_LOBATTO && !h->keep_traces);
+    return h->mx || (h->axis_mode && h->nodes == FR_DVM_NODES_LOBATTO &&
+                     (int64_t)h->ns * h->vg.nu * h->ncomp <= 2 * h->tl.elem);
 }
 
 // Brackets a launch with events when profiling is on.
@@ -232,9 +234,9 @@ namespace frdvm {
 // fout, traces + moments of the result), 2 = residual only (R into fout).
 struct StageArgs {
     const void *f;      // current stage value
-    const void *fn;     // f^n (SSP) or dF (LSRK), may be null at stage 1
+    const void *fn;     // second register read: f^n (SSP, alpha != 0) or dF (LSRK, lsA != 0); may be fout
     void *fout;         // output register
-    void *dF;           // LSRK dF register (in/out)
+    void *dF;           // LSRK: where dF goes (keep_dF); may be fn
     const void *tr_in;  // neighbour traces of f
     void *tr_out;       // own outflow traces of the result
     double *Q;          // moments of the result [ne*ns][nmom]

@@ -461,9 +461,7 @@ k_fr_layer(const FrArgs A) {
     SReal *__restrict__ dFE = reinterpret_cast<SReal *>(A.sa.dF) + ebase;
     // second register read by the stage: f^n (SSP, alpha != 0) or dF (LSRK, A != 0)
     const bool useX = STAGE && (A.sa.scheme == 0 ? A.sa.alpha != 0.0 : A.sa.lsA != 0.0);
-    const SReal *__restrict__ XE = STAGE ? (A.sa.scheme == 0 ? reinterpret_cast<const SReal *>(A.sa.fn) + ebase
-                                                              : reinterpret_cast<const SReal *>(A.sa.dF) + ebase)
-                                         : nullptr;
+    const SReal *__restrict__ XE = STAGE ? reinterpret_cast<const SReal *>(A.sa.fn) + ebase : nullptr;
     const int nchunk = (nu + kChunk - 1) / kChunk;
     const int ntot = NCOMP * nchunk;  // chunks of all components, F first
     // this workgroup's chunks [cc0, cc1)

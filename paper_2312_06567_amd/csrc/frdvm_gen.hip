@@ -465,7 +465,7 @@ k_gen_stage(const GenArgs A) {
     for (int s = 0; s < NS; ++s) fv[s] = ldo(fe + s * nu, ko);
     // the second RK register of the stage
     const bool useX = STAGE && (A.sa.scheme == 0 ? A.sa.alpha != 0.0 : A.sa.lsA != 0.0);
-    const Real *XE = (A.sa.scheme == 0 ? reinterpret_cast<const Real *>(A.sa.fn) : reinterpret_cast<const Real *>(A.sa.dF)) + eoff;
+    const Real *XE = reinterpret_cast<const Real *>(A.sa.fn) + eoff;
     // Divergence and interface corrections, direction by direction: along
     // each line of direction d the transformed flux F_d = (a^d . u) f, its
     // derivative, and the corrections of the line's two flux points on the
@@ -828,7 +828,7 @@ struct MixLane {
 template <typename Real, int NS, int XB, typename Val, typename Res>
 __device__ __forceinline__ void mix_points(const MixArgs &A, const MixLane<Real> &v, Val val, Res res) {
     const bool useX = A.sa.scheme == 0 ? A.sa.alpha != 0.0 : A.sa.lsA != 0.0;
-    const Real *XE = reinterpret_cast<const Real *>(A.sa.scheme == 0 ? A.sa.fn : A.sa.dF) + v.p0 * v.nu;
+    const Real *XE = reinterpret_cast<const Real *>(A.sa.fn) + v.p0 * v.nu;
     Real *dFE = reinterpret_cast<Real *>(A.sa.dF) + v.p0 * v.nu;
     Real *outE = reinterpret_cast<Real *>(A.sa.fout) + v.p0 * v.nu;
     const Real dt = (Real)A.sa.dt;

@@ -641,33 +641,23 @@ void free_traces(fr_dvm *h) {
             h->d_tr[b] = nullptr;
             h->tr_bytes[b] = 0;
         }
-    h->keep_traces = 0;
 }
 
-// Buffers of stage values a step needs beside the register (see stage_args).
-int stage_buffers(const fr_dvm *h) { return h->prm.rk == FR_DVM_LSRK3_2N ? 2 : 1; }
-
-// Allocates what is not there yet.
+// Two buffers of traces, or one stage value in their place (no_traces).
 int alloc_traces(fr_dvm *h) {
     const size_t es = h->prm.precision != FR_DVM_FP64 ? sizeof(float) : sizeof(double);  // of the stage arithmetic
-    for (;;) {
-        const bool values = no_traces(h);
-        const int n = values ? stage_buffers(h) : 2;
-        const size_t bytes = es * (values ? h->ne * h->ns * h->vg.nu * h->ncomp : h->ne * h->tl.elem);
-        int b = 0;
-        for (; b < n; ++b) {
-            if (h->d_tr[b]) continue;
-            if (hipMalloc(&h->d_tr[b], bytes) != hipSuccess) break;
-            h->tr_bytes[b] = bytes;
-            h->owned_bytes += bytes;
+    const bool values = no_traces(h);
+    const size_t bytes = es * (values ? h->ne * h->ns * h->vg.nu * h->ncomp : h->ne * h->tl.elem);
+    for (int b = 0; b < (values ? 1 : 2); ++b) {
+        if (hipMalloc(&h->d_tr[b], bytes) != hipSuccess) {
+            h->d_tr[b] = nullptr;
+            hipGetLastError();  // (this allocation's: not the next launch's)
+            return h->fail(FR_DVM_ENOMEM, "trace allocation failed");
         }
-        if (b == n) return FR_DVM_OK;
-        h->d_tr[b] = nullptr;
-        hipGetLastError();  // (the failed allocation's: not the next launch's)
-        if (!values || h->mx) return h->fail(FR_DVM_ENOMEM, "trace allocation failed");
-        free_traces(h);
-        h->keep_traces = 1;
+        h->tr_bytes[b] = bytes;
+        h->owned_bytes += bytes;
     }
+    return FR_DVM_OK;
 }
 
 // A box handle moves to the general-mesh path (the positivity limiter runs
@@ -764,8 +754,6 @@ extern "C" int fr_dvm_set_params(fr_dvm_t h, const fr_dvm_params *p) {
         if ((rc = dev_alloc(h, &h->d_pt_status, npts))) return rc;
         if ((rc = dev_alloc(h, &h->d_pt_resid, npts))) return rc;
         h->zvalid = 0;
-    } else if (no_traces(h) && stage_buffers(h) == 2 && !h->d_tr[1]) {
-        if ((rc = alloc_traces(h))) return rc;
     }
     if (realloc_mom) {
         if ((rc = dev_alloc(h, &h->d_Q, npts * nmom))) return rc;

@@ -31,6 +31,7 @@ CASES = {
     "box fp64 -> dev": (box, 3, {}, es, dict(es, precision=2)),
     "box -> limiter": (box, 2, {}, es, dict(es, positivity=1)),
     "box pair -> limiter": (box, 2, dict(delta=2.0), es, dict(es, positivity=1)),
+    "gll fp64 -> fp32 low storage": (box, 3, dict(nodes=1), bgk, dict(es, precision=1, rk=1)),
     "mixed": (W.prism_tet_box_mesh(3), 2, {}, bgk, dict(es, precision=1, rk=1)),
     "general": (W.cylinder_mesh(4, 2, 1), 2, {}, bgk, dict(es, precision=1)),
 }
@@ -70,7 +71,7 @@ print(json.dumps([n, bad]))
 
 
 @pytest.mark.parametrize("case", ["box bgk -> es", "box fp64 -> dev", "box -> limiter", "box pair -> limiter",
-                                  "mixed", "general"])
+                                  "gll fp64 -> fp32 low storage", "mixed", "general"])
 def test_a_failed_allocation_leaves_a_handle_that_refuses(tmp_path, case):
     n, bad = json.loads(run(tmp_path, f"CASE = {case!r}\n" + CODE).splitlines()[-1])
     print(case, n, "allocations")
