@@ -479,8 +479,11 @@ __device__ __forceinline__ void sums_es_fact(const NewtonArgs &A, int lane, doub
 
 // Whether the factors of an evaluation stay well inside the FP64 range: the
 // largest |exponents| of the cross factors over the grid (their sum bounds
-// the lanes' start values, twice it the range of a geometric factor) and the
-// peaks of the one-axis factors.
+// the lanes' start values, twice it the range of a geometric factor), the
+// peaks of the one-axis factors, and the largest value W of a row can take in
+// the padded y nodes: it goes on growing there, and only a finite W times
+// their zero weight is zero (8 x 9 nodes have 7 padded ones, 2.75 times as far
+// from the mean as the last node).
 __device__ __forceinline__ bool factors_in_range(const NewtonArgs &A, const EsPoint &p) {
     const VGrid &vg = A.vg;
     double cm[3];
@@ -489,10 +492,12 @@ __device__ __forceinline__ bool factors_in_range(const NewtonArgs &A, const EsPo
         cm[d] = fmax(fabs(gridu(vg, d, 0) - p.U[d]), fabs(gridu(vg, d, vg.nv[d] - 1) - p.U[d])) * p.ist;
     const double z4 = p.z[4];
     const double cross = z4 * (fabs(p.A[3]) * cm[0] * cm[1] + fabs(p.A[4]) * cm[0] * cm[2] + fabs(p.A[5]) * cm[1] * cm[2]);
+    const double c1p = fmax(cm[1], fabs(gridu(vg, 1, es_rows(vg, A.nph) - 1) - p.U[1]) * p.ist);
+    const double row = z4 * cm[0] * (fabs(p.A[3]) * c1p + fabs(p.A[4]) * cm[2]);
     double peak = fabs(p.z[0]);
 #pragma unroll
     for (int d = 0; d < 3; ++d) peak = fmax(peak, p.z[1 + d] * p.z[1 + d] / (2.0 * z4 * p.A[d]));
-    return cross <= 300.0 && peak <= 25.0;  // (false for NaN)
+    return cross <= 300.0 && row <= 650.0 && peak <= 25.0;  // (false for NaN)
 }
 
 // Smallest eigenvalue of a symmetric 3x3 matrix (closed form, trigonometric).
