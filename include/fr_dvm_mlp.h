@@ -79,7 +79,8 @@ int fr_mlp_adam(int H, float *w, const float *grad, float *m, float *v, int step
  * c = (u-U)/sqrt(theta), iters[n] linear solves, evals[n] residual/Jacobian
  * evaluations (sum passes over the grid), status[n] (FR_DVM_NEWTON_*),
  * resid[n] final scaled residual.  Uses the handle's tolerance and
- * iteration cap.  Synchronises the handle's stream. */
+ * iteration cap.  Synchronises the handle's stream.
+ * A vector's results have the same bits whatever batch it is in. */
 int fr_dvm_equilibrium(fr_dvm_t h, const double *Q, int64_t n, int guess, double *z, int32_t *iters,
                        int32_t *evals, int32_t *status, double *resid);
 

@@ -177,30 +177,49 @@ __device__ __forceinline__ void assemble(const Sums &s, double r[5], double J[5]
 }
 
 // BGK sums by axis factorisation: e = exp(z0) prod_d exp(z_d c_d - z4 c_d^2 / 2).
-// LPP lanes of a point take every LPP-th node of each axis and add their
-// sums in a butterfly (every lane gets the same bits).
+// LPP lanes share a point.  Whatever LPP is, the nodes of an axis are summed in
+// eight classes (i mod 8), and the classes p0 .. p7 added as ((p0 + p1) +
+// (p2 + p3)) + ((p4 + p5) + (p6 + p7)): a lane adds those of its own classes,
+// 8 / LPP consecutive ones, a butterfly over the lanes the rest (every lane
+// gets the same bits).  So a point's result does not depend on the batch it is
+// solved in.  Up to four classes are walked side by side: an exponential is a
+// chain of its own.
 template <int LPP>
 __device__ void sums_bgk(const NewtonArgs &A, int lane, const double U[3], double ist, const double z[5], Sums &s) {
+    constexpr int NC = 8 / LPP, W = NC < 4 ? NC : 4;  // classes of a lane, and those it walks side by side
     double m[3][5];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        double a0 = 0, a1 = 0, a2 = 0, a3 = 0, a4 = 0;
         const int nv = A.vg.nv[d];
         const double zd = z[1 + d], hz = 0.5 * z[4];
-        for (int i = lane; i < nv; i += LPP) {
-            const double c = (gridu(A.vg, d, i) - U[d]) * ist;
-            const double ev = A.wax[64 * d + i] * ist * exp(c * (zd - hz * c));
-            double t = ev;
-            a0 += t; t *= c;
-            a1 += t; t *= c;
-            a2 += t; t *= c;
-            a3 += t; t *= c;
-            a4 += t;
+        // (a node past the end has weight zero and the last node's velocity)
+#pragma unroll 1
+        for (int pass = 0; pass < NC / W; ++pass) {
+            double a[W][5] = {};
+            for (int i0 = NC * lane + W * pass; i0 < nv; i0 += 8)
+#pragma unroll
+                for (int w = 0; w < W; ++w) {
+                    const int i = i0 + w;
+                    const double c = (gridu(A.vg, d, W == 1 || i < nv ? i : nv - 1) - U[d]) * ist;
+                    double t = A.wax[64 * d + i] * ist * exp(c * (zd - hz * c));
+#pragma unroll
+                    for (int e = 0; e < 5; ++e) {
+                        a[w][e] += t;
+                        t *= c;
+                    }
+                }
+#pragma unroll
+            for (int o = 1; o < W; o *= 2)
+#pragma unroll
+                for (int w = 0; w < W; w += 2 * o)
+#pragma unroll
+                    for (int e = 0; e < 5; ++e) a[w][e] += a[w + o][e];
+#pragma unroll
+            for (int e = 0; e < 5; ++e) m[d][e] = pass ? m[d][e] + a[0][e] : a[0][e];
         }
-        m[d][0] = a0; m[d][1] = a1; m[d][2] = a2; m[d][3] = a3; m[d][4] = a4;
     }
 #pragma unroll
-    for (int o = LPP / 2; o >= 1; o >>= 1)
+    for (int o = 1; o < LPP; o *= 2)
 #pragma unroll
         for (int d = 0; d < 3; ++d)
 #pragma unroll
@@ -1485,18 +1504,17 @@ void launch_bgk_lanes(const NewtonArgs &A, hipStream_t s) {
 }
 // Lanes per point: one where the points alone fill the chip (the sums are a
 // part of the work, the 5 x 5 solves are repeated by every lane: at 262,144
-// points of a 32^3 grid 1, 2, 4, 8 lanes take 356, 370, 439, 596 us), more
+// points of a 32^3 grid 1, 2, 4, 8 lanes take 269, 282, 369, 571 us), more
 // on small batches, where one lane's chain over the nodes is the time (4096
-// points: 99, 71, 52, 47 us; 512 points of an 8^3 grid 57, 51, 46, 44 us, of
+// points: 90, 59, 47, 45 us; 512 points of an 8^3 grid 54, 45, 42, 41 us, of
 // which 30 are the call).  The lines lie where the measured times cross:
-// with the axis length, since the shared part grows with it.  `all` counts
-// the points of the whole solve, of which A may be a part: the order of a
-// point's sums does not depend on the part it is solved in.
-void launch_bgk(const NewtonArgs &A, int64_t all, hipStream_t s) {
+// with the axis length, since the shared part grows with it.  A point's sums
+// have one order for every number of lanes.
+void launch_bgk(const NewtonArgs &A, hipStream_t s) {
     const int64_t nv = std::max(A.vg.nv[0], std::max(A.vg.nv[1], A.vg.nv[2]));
-    if (all <= 128 * nv) launch_bgk_lanes<8>(A, s);
-    else if (all <= 512 * nv) launch_bgk_lanes<4>(A, s);
-    else if (all <= 2048 * nv) launch_bgk_lanes<2>(A, s);
+    if (A.npts <= 128 * nv) launch_bgk_lanes<8>(A, s);
+    else if (A.npts <= 512 * nv) launch_bgk_lanes<4>(A, s);
+    else if (A.npts <= 2048 * nv) launch_bgk_lanes<2>(A, s);
     else launch_bgk_lanes<1>(A, s);
 }
 
@@ -1531,7 +1549,7 @@ int newton_run(fr_dvm *h, NewtonArgs A, int64_t p0, int64_t np, hipStream_t s) {
     if (h->prm.model == FR_DVM_ESBGK) {
         launch_es(h, A, s);
     } else {
-        launch_bgk(A, h->ne * h->ns, s);
+        launch_bgk(A, s);
     }
     int64_t nb = (A.npts + 256 * kStatPts - 1) / (256 * kStatPts);
     if (nb > 1024) nb = 1024;
@@ -1601,7 +1619,7 @@ int launch_newton_points(fr_dvm *h, const double *Q, int64_t n, int guess, doubl
         A.delta = 0.0;  // monatomic moment vectors
         A.gfp = nullptr;
         if (!(A.mu_ref > 0)) A.mu_ref = 1.0;  // tau is not an output here
-        launch_bgk(A, n, h->stream);
+        launch_bgk(A, h->stream);
         rc = check(h, "newton kernel");
     }
     (void)hipStreamSynchronize(h->stream);
