@@ -6,6 +6,7 @@
 
 #include <cstdint>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/fr_dvm.h"
@@ -67,6 +68,7 @@ struct MixType {
     std::vector<double> lift;    // [nft][ns] correction of a unit jump at each face point
     std::vector<double> W;       // [ns] integral of each Lagrange function (reference)
     std::vector<double> stream;  // prisms, tetrahedra: the operators in the kernel's order (frdvm_simplex.h)
+    std::vector<std::pair<int, int>> drow;  // its derivative rows: first entry, entries
     std::vector<int32_t> elems;  // elements of this type
     double *d_D = nullptr, *d_lift = nullptr, *d_stream = nullptr;  // (hexahedra: D, lift; others: stream)
     float *d_Df = nullptr, *d_liftf = nullptr, *d_streamf = nullptr;

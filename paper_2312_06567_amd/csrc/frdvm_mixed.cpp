@@ -361,14 +361,19 @@ int fill_stream(fr_dvm *h, MixType &T, const std::vector<V3> &x) {
     }
     std::vector<double> &st = T.stream;
     st.clear();
+    T.drow.clear();
+    auto row_from = [&](size_t first) { T.drow.push_back({(int)first, (int)(st.size() - first)}); };
     for (int m = 0; m < NM; ++m)
-        for (int a = 0; a < DIM; ++a)
+        for (int a = 0; a < DIM; ++a) {
+            const size_t first = st.size();
             for (int j = 0; j < NP; ++j) {
                 if ((tb.d[a][m] >> j) & 1) st.push_back(D(a, tb.sub[m], j));
                 else if (std::fabs(D(a, tb.sub[m], j)) > dtol) return bad("derivative pattern");
                 for (int k = 1; k < PL; ++k)
                     if (std::fabs(D(a, tb.sub[m] + NP * k, j + NP * k) - D(a, tb.sub[m], j)) > dtol) return bad("layers");
             }
+            row_from(first);
+        }
     for (int q = 0; q < NP - NM; ++q) {
         for (int m = 0; m < NM; ++m) {
             if ((tb.e[q] >> m) & 1) st.push_back(E[q * NM + m]);
@@ -391,12 +396,15 @@ int fill_stream(fr_dvm *h, MixType &T, const std::vector<V3> &x) {
             }
         return (int)st.size() == tet_stream<P>() ? FR_DVM_OK : bad("stream length");
     } else {
-        for (int i = 0; i < PL; ++i)
+        for (int i = 0; i < PL; ++i) {
+            const size_t first = st.size();
             for (int k = 0; k < PL; ++k) {
                 st.push_back(D(2, NP * i, NP * k));
                 for (int m = 1; m < NP; ++m)
                     if (std::fabs(D(2, m + NP * i, m + NP * k) - D(2, NP * i, NP * k)) > dtol) return bad("columns");
             }
+            row_from(first);
+        }
         // (the order of the face points is checked by prism_structure, the edges' points here)
         for (int f = 0; f < 2; ++f)
             for (int k = 0; k < PL; ++k) {
@@ -539,6 +547,38 @@ int dput(fr_dvm *h, T **p, const std::vector<T> &v) {
     return FR_DVM_OK;
 }
 std::vector<float> to_f32(const std::vector<double> &v) { return std::vector<float>(v.begin(), v.end()); }
+
+// The operator stream in FP32.  Rounded entry by entry a derivative row does
+// not sum to zero, and a constant leaves its sum times the value: at p = 3 the
+// larger part of the residual's rounding error on a smooth state, which the
+// interpolation of the derivatives amplifies.  So entries of a row are moved by
+// units in their last place as long as that brings the row's sum nearer to
+// zero (p <= 2: the entries are exact and nothing moves).
+std::vector<float> stream_f32(const MixType &T) {
+    std::vector<float> s = to_f32(T.stream);
+    for (const auto &[first, n] : T.drow) {
+        float *r = &s[first];
+        for (int it = 0; it < 4 * n; ++it) {
+            double sum = 0.0;
+            for (int j = 0; j < n; ++j) sum += (double)r[j];
+            double best = std::fabs(sum);
+            int at = -1;
+            float to = 0.f;
+            for (int j = 0; j < n; ++j) {
+                const float v = std::nextafter(r[j], sum > 0 ? -INFINITY : INFINITY);
+                const double left = std::fabs(sum + ((double)v - (double)r[j]));
+                if (left < best) {
+                    best = left;
+                    at = j;
+                    to = v;
+                }
+            }
+            if (at < 0) break;
+            r[at] = to;
+        }
+    }
+    return s;
+}
 
 }  // namespace
 
@@ -724,7 +764,7 @@ extern "C" int fr_dvm_create_mixed(const fr_dvm_mixed_mesh *mesh, int order, con
                 (rc = dput(h, &T.d_liftf, to_f32(T.lift))) || (rc = dput(h, &T.d_fnode, T.fnode)) ||
                 (rc = dput(h, &T.d_ffac, T.ffac)))
                 return bail(rc);
-        } else if ((rc = dput(h, &T.d_stream, T.stream)) || (rc = dput(h, &T.d_streamf, to_f32(T.stream)))) {
+        } else if ((rc = dput(h, &T.d_stream, T.stream)) || (rc = dput(h, &T.d_streamf, stream_f32(T)))) {
             return bail(rc);
         }
     }
