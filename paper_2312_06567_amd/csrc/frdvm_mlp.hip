@@ -304,8 +304,10 @@ __global__ __launch_bounds__(64 * HT) void k_mlp_rows(const float *__restrict__ 
             float *dst = sA[GRAD ? l : (l & 1)];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
+                // (a neuron past the width stays 0 also where a real one is
+                // infinite: 0 x inf would make the row NaN)
                 const float x = z[i] + bias[l];
-                a[l][i] = silu(x);
+                a[l][i] = n < H ? silu(x) : 0.f;
                 if (GRAD) ds[l][i] = dsilu(x);
                 dst[(4 * q + i) * S + n] = a[l][i];
             }
@@ -349,7 +351,7 @@ __global__ __launch_bounds__(64 * HT) void k_mlp_rows(const float *__restrict__ 
             for (int l = 2; l >= 0; --l) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    d[i] *= ds[l][i];
+                    d[i] = n < H ? d[i] * ds[l][i] : 0.f;
                     db[l] += d[i];
                     if (l > 0) sD[l - 1][(4 * q + i) * S + n] = d[i];
                 }
