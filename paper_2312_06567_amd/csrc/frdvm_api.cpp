@@ -43,10 +43,16 @@ int guess_mode(fr_dvm *h) {
 }
 
 // How the moments a Newton solve is about to read are wanted: on small boxes
-// as the workgroups' parts, added by the solve itself (the learned start's
-// features read the sums).
+// as the workgroups' parts, added by the solve itself, which saves a launch
+// (the learned start's features read the sums).  What it costs is the parts'
+// loads, one after the other, in the solve's first instructions: BGK spreads
+// them over a point's lanes, ES holds up a workgroup of points.  Steps with
+// the sums / with the parts, BGK: 512 points 90.2 / 84.2 us, 1620 260 / 253,
+// 13,824 793 / 777 and 904 / 879, above 32,000 within 1 %; ES: 512 points
+// 128.7 / 123.2 us, 1620 317 / 311, 5832 504 / 507, 13,824 1064 / 1122.
 int solve_moments(fr_dvm *h, int guess) {
-    return h->axis_mode && h->ne * h->ns <= 16384 && newton_part_ok(h, guess) ? kMomentParts : 1;
+    const int64_t most = h->prm.model == FR_DVM_ESBGK ? 4096 : 16384;
+    return h->axis_mode && h->ne * h->ns <= most && newton_part_ok(h, guess) ? kMomentParts : 1;
 }
 
 }  // namespace

@@ -61,7 +61,7 @@ struct NewtonArgs {
     int guess;
     const float *dz_guess;  // [npts][5] learned correction (guess == MLP)
     int use_fact;           // ES: factorised sums
-    int nph, es_pts;        // ES: lanes that share an x node, points per workgroup
+    int nph, nrow, es_pts;  // ES: lanes that share an x node, y nodes padded to them, points per workgroup
     double delta;           // internal degrees of freedom (the reduced pair)
     double *gfp;            // [npts] delta theta / 2 per point (pair only, else null)
 };
@@ -361,8 +361,7 @@ __device__ void sums_es(const NewtonArgs &A, int lane, const EsPoint &p, double 
 
 // Doubles of one wave's tables: per y node factor with weight, Rb, c1 (padded
 // with zero weights to the same number of nodes for every lane); Z c2^e.
-__host__ __device__ inline int es_rows(const VGrid &vg, int nph) { return (vg.nv[1] + nph - 1) / nph * nph; }
-__host__ __device__ inline int es_table_doubles(const VGrid &vg, int nph) { return 3 * es_rows(vg, nph) + 5 * vg.nv[2]; }
+__host__ __device__ inline int es_table_doubles(const NewtonArgs &A) { return 3 * A.nrow + 5 * A.vg.nv[2]; }
 
 __device__ __forceinline__ void lds_wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -481,7 +480,7 @@ __device__ __forceinline__ void sums_es_fact(const NewtonArgs &A, int lane, doub
     lds_wave_sync();  // previous evaluation's readers are done with the tables
     // the y and z tables: one exponential per entry, the entries of all three
     // tables dealt to the lanes together
-    const int np = es_rows(vg, nph);
+    const int np = A.nrow;
     for (int t = lane; t < np - n1; t += 64) {
         tb[n1 + t] = tb[2 * np + n1 + t] = 0.0;
         tb[np + n1 + t] = WIDE ? 1.0 : 0.0;  // (the wide form divides by it)
@@ -594,7 +593,7 @@ __device__ __forceinline__ int sums_form(const NewtonArgs &A, const EsPoint &p) 
     for (int d = 0; d < 3; ++d) peak = fmax(peak, p.z[1 + d] * p.z[1 + d] / (2.0 * z4 * p.A[d]));
     const double a01 = z4 * fabs(p.A[3]), a02 = z4 * fabs(p.A[4]), a12 = z4 * fabs(p.A[5]);
     const double cross = a01 * cm[0] * cm[1] + a02 * cm[0] * cm[2] + a12 * cm[1] * cm[2];
-    const double c1p = fmax(cm[1], fabs(gridu(vg, 1, es_rows(vg, A.nph) - 1) - p.U[1]) * p.ist);
+    const double c1p = fmax(cm[1], fabs(gridu(vg, 1, A.nrow - 1) - p.U[1]) * p.ist);
     const double row = cm[0] * (a01 * c1p + a02 * cm[2]);
     if (cross <= 300.0 && row <= 650.0 && peak <= 25.0) return 0;  // (false for NaN)
     // the largest exponent of the c0 c1 factor, that of a ratio over its reach,
@@ -1119,7 +1118,7 @@ __global__ __launch_bounds__(kEsBlock) __attribute__((amdgpu_waves_per_eu(FRDVM_
     EsPoint *const P = reinterpret_cast<EsPoint *>(es_lds);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    double *const tb = es_lds + npw * kEsPointD + wave * es_table_doubles(A.vg, A.nph);
+    double *const tb = es_lds + npw * kEsPointD + wave * es_table_doubles(A);
     const int64_t p0 = (int64_t)blockIdx.x * npw;
     const bool owner = (int)threadIdx.x < npw && p0 + threadIdx.x < A.npts;
     const int64_t pt = p0 + threadIdx.x;
@@ -1523,10 +1522,11 @@ void launch_bgk(const NewtonArgs &A, hipStream_t s) {
 void launch_es(const fr_dvm *h, NewtonArgs &A, hipStream_t s) {
     A.use_fact = !h->es_direct;
     A.nph = std::max(1, std::min(64 / A.vg.nv[0], A.vg.nv[1]));
+    A.nrow = (A.vg.nv[1] + A.nph - 1) / A.nph * A.nph;
     int pts = kEsMaxPts;
     while (pts > 4 && A.npts < (int64_t)pts * 1024) pts /= 2;
     A.es_pts = pts;
-    const size_t shm = sizeof(double) * (size_t)(pts * kEsPointD + (kEsBlock / 64) * es_table_doubles(A.vg, A.nph));
+    const size_t shm = sizeof(double) * (size_t)(pts * kEsPointD + (kEsBlock / 64) * es_table_doubles(A));
     hipLaunchKernelGGL(k_newton_es, dim3((unsigned)((A.npts + pts - 1) / pts)), dim3(kEsBlock), shm, s, A);
 }
 
