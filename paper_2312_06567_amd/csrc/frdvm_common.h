@@ -129,8 +129,9 @@ struct fr_dvm {
     // general (curved / re-oriented / bounded) meshes, axis_mode == false
     double *d_S = nullptr;       // [ne][3][nfp][n][3] a^d = |J| grad xi_d at the points of each line of direction d
     double *d_ijac = nullptr;    // [ne][ns] 1/|J|
-    double *d_nf = nullptr;      // [ne][6][nfp][4] outward area-scaled normal at the flux points, margin of u.n
-    float *d_Sf = nullptr, *d_ijacf = nullptr, *d_nff = nullptr;  // FP32 copies
+    double *d_nf = nullptr;      // [ne][6]: outward area-scaled normals at the flux points [nfp][3], margins of u.n [nfp]
+    double *d_nm = nullptr;      // [ne][6][nfp][4] the same, each normal with its margin
+    float *d_Sf = nullptr, *d_ijacf = nullptr, *d_nff = nullptr, *d_nmf = nullptr;  // FP32 copies
     int32_t *d_conn = nullptr;   // [ne][6][4] neighbour, its face, orientation code, bc tag
     int32_t *d_wall = nullptr;   // [nwall] e*6+face of every diffuse-wall face
     int64_t nwall = 0;

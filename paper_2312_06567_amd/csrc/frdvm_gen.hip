@@ -60,8 +60,9 @@ struct GenArgs {
     const double *wJ;    // [ne][ns] Gauss weight x |J| (positivity limiter)
     const double *S;     // [ne][3][nfp][n][3] a^d at the points of each line of direction d
     const double *ijac;  // [ne][ns]
-    const double *nf;    // [ne][6][nfp][4] normal, margin of u.n
-    const float *Sf, *ijacf, *nff;  // the same in FP32
+    const double *nf;    // [ne][6]: normals [nfp][3], margins of u.n [nfp]
+    const double *nm;    // [ne][6][nfp][4]: each normal with its margin
+    const float *Sf, *ijacf, *nff, *nmf;  // the same in FP32
     const int32_t *conn; // [ne][6][4]
     const int32_t *wall; // [nwall]
     double *rw;          // [ne*6][nfp]
@@ -84,13 +85,13 @@ template <typename Real>
 using cptr = const __attribute__((address_space(4))) Real *;
 template <typename Real>
 struct Metrics {
-    cptr<Real> S, ijac, nf;
+    cptr<Real> S, ijac, nf, nm;
 };
 __device__ __forceinline__ Metrics<float> metrics(const GenArgs &A, float) {
-    return {(cptr<float>)A.Sf, (cptr<float>)A.ijacf, (cptr<float>)A.nff};
+    return {(cptr<float>)A.Sf, (cptr<float>)A.ijacf, (cptr<float>)A.nff, (cptr<float>)A.nmf};
 }
 __device__ __forceinline__ Metrics<double> metrics(const GenArgs &A, double) {
-    return {(cptr<double>)A.S, (cptr<double>)A.ijac, (cptr<double>)A.nf};
+    return {(cptr<double>)A.S, (cptr<double>)A.ijac, (cptr<double>)A.nf, (cptr<double>)A.nm};
 }
 
 // exp of W exponents, side by side
@@ -167,7 +168,13 @@ __device__ __forceinline__ Real face_value(const Real *lam, const Real (&line)[N
 // wave's, since a row stored in part costs more than a whole one: with every
 // value stored the prime pass of the Mach-8 O-grid (p = 2, FP32) takes 1.82
 // ms, with each lane storing for itself 2.66, so 1.57.
-template <typename Real, int P>
+// ALL: every row, for states of up to kGenAllBytes, where the decisions' loads
+// and ballots take longer than the rows: residual in FP64, decided / all, of 216
+// elements p = 2, 120 velocities (6 MB) 32.3 / 28.8 us, 24 elements p = 3, 12^3
+// (21 MB) 68.7 / 60.9, 216 elements p = 1, 12^3 (24 MB) 37.0 / 39.1, p = 2 (81 MB)
+// 112 / 128.
+constexpr int64_t kGenAllBytes = 22 << 20;
+template <typename Real, int P, bool ALL>
 __global__ __launch_bounds__(kGBlock) void k_gen_traces(const GenArgs A, const Real *__restrict__ f,
                                                          Real *__restrict__ tr) {
     constexpr int N = P + 1, NS = N * N * N, NFP = N * N;
@@ -196,8 +203,9 @@ __global__ __launch_bounds__(kGBlock) void k_gen_traces(const GenArgs A, const R
         Real t[NFP];
 #pragma unroll
         for (int q = 0; q < NFP; ++q) {
-            const cptr<Real> n4 = gN + 4 * (face * NFP + q);
-            kept |= __ballot(n4[0] * u0 + n4[1] * u1 + n4[2] * u2 + n4[3] * ul1 > Real(0)) ? 1u << q : 0u;
+            const cptr<Real> nf = gN + 4 * face * NFP, n = nf + 3 * q;
+            if constexpr (ALL) kept |= 1u << q;
+            else kept |= __ballot(n[0] * u0 + n[1] * u1 + n[2] * u2 + nf[3 * NFP + q] * ul1 > Real(0)) ? 1u << q : 0u;
             Real line[N];
 #pragma unroll
             for (int m = 0; m < N; ++m) line[m] = v[line_pt<N>(d, q % N, q / N, m)];
@@ -292,7 +300,7 @@ __global__ __launch_bounds__(kGBlock) void k_gen_wall(const GenArgs A, const Rea
     __shared__ double red[kGBlock / 64][2];
     const int64_t fid = A.wall[blockIdx.x / NFP];
     const int fp = blockIdx.x % NFP;
-    const double *nv = A.nf + (fid * NFP + fp) * 4;
+    const double *nv = A.nf + fid * NFP * 4 + fp * 3;
     const double n0 = nv[0], n1 = nv[1], n2 = nv[2];
     const Real *t = tr + (fid * NFP + fp) * (int64_t)A.nut;  // F part of the trace
     double out = 0.0, in = 0.0;
@@ -332,6 +340,7 @@ __global__ __launch_bounds__(kGBlock) void k_gen_wall(const GenArgs A, const Rea
 template <typename Real>
 struct ExtArgs {
     cptr<int32_t> conn;   // the element's [6][4]
+    int32_t cn[24];       // the same, read
     cptr<double> rwall;   // wall densities of its faces [6][nfp]
     cptr<Real> gN;        // its normals
     const double *finf, *mwall;
@@ -348,24 +357,26 @@ struct ExtArgs {
 // in each axis (passed by value: a choice between members of X would keep X in
 // scratch memory).  KEEP: kept gets the (wave-uniform) bits of the flux points
 // whose traces the wave has to store.
-template <typename Real, int N, bool KEEP>
+template <typename Real, int N, bool KEEP, bool CONN, bool PAIRS>
 __device__ __forceinline__ void load_ext(const ExtArgs<Real> &X, int d, int km0, int km1, int km2,
                                          Real (&un)[2][N * N], Real (&ext)[2][N * N], uint64_t (&kept)[2]) {
-    constexpr int NFP = N * N;
+    constexpr int NFP = N * N, NW = PAIRS ? 4 : 3;
 #pragma unroll
     for (int side = 0; side < 2; ++side) {
         const int face = 2 * d + side;
-        const cptr<int32_t> c = X.conn + face * 4;
+        int32_t c[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c[i] = CONN ? X.cn[4 * face + i] : X.conn[4 * face + i];
         const int32_t nb = c[0], nface = c[1], orient = c[2], bc = c[3];
         const cptr<Real> nv = X.gN + face * NFP * 4;
 #pragma unroll
         for (int q = 0; q < NFP; ++q)
-            un[side][q] = nv[4 * q] * X.u0 + nv[4 * q + 1] * X.u1 + nv[4 * q + 2] * X.u2;
+            un[side][q] = nv[NW * q] * X.u0 + nv[NW * q + 1] * X.u1 + nv[NW * q + 2] * X.u2;
         if constexpr (KEEP) {
 #pragma unroll
             for (int q = 0; q < NFP; ++q) {
                 const int b = face * NFP + q;
-                const uint64_t bit = __ballot(un[side][q] + nv[4 * q + 3] * X.ul1 > Real(0)) ? 1ull << (b & 63) : 0ull;
+                const uint64_t bit = __ballot(un[side][q] + nv[PAIRS ? 4 * q + 3 : 3 * NFP + q] * X.ul1 > Real(0)) ? 1ull << (b & 63) : 0ull;
                 if (b < 64) kept[0] |= bit;
                 else kept[1] |= bit;
             }
@@ -425,11 +436,21 @@ template <typename Real, int P, int MODE>
 constexpr bool gen_ahead() {
     return P == 1 || (P == 2 && sizeof(Real) == 4 && MODE == GMODE_STAGE);
 }
+// Whether a stage reads each margin with its normal.  The residual reads no
+// margins: consecutive normals are fewer scalar loads (384 elements, 20^3, FP64,
+// pairs / apart: p = 1 344 / 328 us, p = 2 912 / 850, p = 3 2998 / 2603).  The stage
+// reads both; which is better is a matter of its registers: low-storage steps
+// at that size p = 1 no difference, p = 2 FP64 2909 / 3055, FP32 1564 / 1561, p = 3
+// FP64 9522 / 8713, FP32 4144 / 4258 us.
+template <typename Real, int P, int MODE>
+constexpr bool gen_pairs() {
+    return MODE == GMODE_STAGE && P == (sizeof(Real) == 8 ? 2 : 3);
+}
 template <typename Real, int P, int MODE>
 __global__ __launch_bounds__(kGWave) __attribute__((amdgpu_waves_per_eu(gen_waves<Real, P>()))) void
 k_gen_stage(const GenArgs A) {
     constexpr int N = P + 1, NS = N * N * N, NFP = N * N;
-    constexpr bool STAGE = MODE == GMODE_STAGE;
+    constexpr bool STAGE = MODE == GMODE_STAGE, PAIRS = gen_pairs<Real, P, MODE>();
     Real fv[NS];  // the lane's stage value
     __shared__ Real sa[NS][kGWave];
     __shared__ double sEb[STAGE ? NS * 8 : 1];
@@ -465,7 +486,7 @@ k_gen_stage(const GenArgs A) {
 
     const GOps<Real> &op = gops<Real>(A);
     const Metrics<Real> G = metrics(A, Real(0));
-    const cptr<Real> gS = G.S + e * NS * 9, gJ = G.ijac + e * NS, gN = G.nf + e * 6 * NFP * 4;
+    const cptr<Real> gS = G.S + e * NS * 9, gJ = G.ijac + e * NS, gN = (PAIRS ? G.nm : G.nf) + e * 6 * NFP * 4;
     const int64_t nu = A.nut;  // stride of a solution point
     const int comp = k >= A.nu, kv = k - comp * A.nu;  // component, velocity node
     int iv[3];
@@ -489,8 +510,15 @@ k_gen_stage(const GenArgs A) {
     const Real *tin = reinterpret_cast<const Real *>(A.sa.tr_in);
     const Real ul1 = (u0 < 0 ? -u0 : u0) + (u1 < 0 ? -u1 : u1) + (u2 < 0 ? -u2 : u2);
     uint64_t kept[2] = {0, 0};  // flux points (face * NFP + q) whose traces the wave stores
-    const ExtArgs<Real> X = {(cptr<int32_t>)A.conn + e * 24, (cptr<double>)A.rw + e * 6 * NFP, gN, A.finf, A.mw, tin,
-                             comp ? A.gwall : 1.0, e, nu, ko, k8, kv8, u0, u1, u2, ul1};
+    ExtArgs<Real> X = {(cptr<int32_t>)A.conn + e * 24, {}, (cptr<double>)A.rw + e * 6 * NFP, gN, A.finf, A.mw, tin,
+                       comp ? A.gwall : 1.0, e, nu, ko, k8, kv8, u0, u1, u2, ul1};
+    // the connectivity of all faces now: face by face, each direction's
+    // requests would wait for it (at p = 1 the registers cost more than that)
+    constexpr bool CONN = P > 1;
+    if constexpr (CONN) {
+#pragma unroll
+        for (int i = 0; i < 24; ++i) X.cn[i] = X.conn[i];
+    }
     const int km0 = k + A.vg.nv[0] - 1 - 2 * iv[0], km1 = k + (A.vg.nv[1] - 1 - 2 * iv[1]) * A.vg.nv[0],
               km2 = k + (A.vg.nv[2] - 1 - 2 * iv[2]) * (A.vg.nv[0] * A.vg.nv[1]);
     // the next direction's exterior values, and before the last direction the
@@ -498,7 +526,7 @@ k_gen_stage(const GenArgs A) {
     // is computed
     constexpr bool AHEAD = gen_ahead<Real, P, MODE>();
     Real unx[2][2][NFP], exx[2][2][NFP];
-    if constexpr (AHEAD) load_ext<Real, N, STAGE>(X, 0, km0, km1, km2, unx[0], exx[0], kept);
+    if constexpr (AHEAD) load_ext<Real, N, STAGE, CONN, PAIRS>(X, 0, km0, km1, km2, unx[0], exx[0], kept);
     Real xv[2][NFP];
     auto load_x = [&](int s0, Real(&x)[NFP]) __attribute__((always_inline)) {
 #pragma unroll
@@ -511,7 +539,7 @@ k_gen_stage(const GenArgs A) {
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (AHEAD) {
-            if (d < 2) load_ext<Real, N, STAGE>(X, d + 1, km0, km1, km2, unx[(d + 1) & 1], exx[(d + 1) & 1], kept);
+            if (d < 2) load_ext<Real, N, STAGE, CONN, PAIRS>(X, d + 1, km0, km1, km2, unx[(d + 1) & 1], exx[(d + 1) & 1], kept);
             else if (STAGE) load_x(0, xv[0]);
 #pragma unroll
             for (int side = 0; side < 2; ++side)
@@ -521,7 +549,7 @@ k_gen_stage(const GenArgs A) {
                     ext[side][q] = exx[d & 1][side][q];
                 }
         } else {
-            load_ext<Real, N, STAGE>(X, d, km0, km1, km2, un, ext, kept);
+            load_ext<Real, N, STAGE, CONN, PAIRS>(X, d, km0, km1, km2, un, ext, kept);
         }
 #pragma unroll
         for (int q = 0; q < NFP; ++q) {
@@ -731,8 +759,12 @@ int gen_run(fr_dvm *h, int mode, const GenArgs &A, int do_moments) {
     int rc;
     if (mode == 0) {
         if (A.do_traces) {
-            hipLaunchKernelGGL((k_gen_traces<Real, P>), dim3(blocks), dim3(kGBlock), 0, h->stream, A,
-                               reinterpret_cast<const Real *>(A.sa.f), reinterpret_cast<Real *>(A.sa.tr_out));
+            const Real *f = reinterpret_cast<const Real *>(A.sa.f);
+            Real *tr = reinterpret_cast<Real *>(A.sa.tr_out);
+            if (npts * A.nut * (int64_t)sizeof(Real) <= kGenAllBytes)
+                hipLaunchKernelGGL((k_gen_traces<Real, P, true>), dim3(blocks), dim3(kGBlock), 0, h->stream, A, f, tr);
+            else
+                hipLaunchKernelGGL((k_gen_traces<Real, P, false>), dim3(blocks), dim3(kGBlock), 0, h->stream, A, f, tr);
             if ((rc = gcheck(h, "trace kernel"))) return rc;
         }
         return do_moments ? moments(A.sa.f) : FR_DVM_OK;
@@ -1312,6 +1344,8 @@ int launch_fr_gen(fr_dvm *h, int mode, const StageArgs &sa, int do_traces, int d
     A.Sf = h->d_Sf;
     A.ijacf = h->d_ijacf;
     A.nff = h->d_nff;
+    A.nm = h->d_nm;
+    A.nmf = h->d_nmf;
     A.conn = h->d_conn;
     A.wall = h->d_wall;
     A.rw = h->d_rw;

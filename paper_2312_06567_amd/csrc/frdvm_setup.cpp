@@ -436,8 +436,10 @@ int setup_general(fr_dvm *h, const fr_dvm_mesh *mesh, std::vector<double> &wq3J)
         return rc;
     if ((rc = dev_alloc(h, &h->d_ijac, ijac.size())) || (rc = upload(h, h->d_ijac, ijac.data(), ijac.size() * sizeof(double))))
         return rc;
-    // normals with a margin in the fourth place; a trace is stored for every
-    // velocity u with u.n + margin |u|_1 > 0.  |n|_1 times a bound on how far
+    // normals and margins, in two layouts (behind a face's normals their
+    // margins, and each margin with its normal; gen_pairs() says who reads
+    // which).  A trace is stored for every velocity u with u.n + margin |u|_1 > 0.  The
+    // margin: |n|_1 times a bound on how far
     // (relative to |n|_1 |u|_1) the rounded u.n of the two sides of a face may
     // differ, the rounding of three products and the gap of the two normals
     // allowed above.  A specular face reads its own trace at the mirrored
@@ -445,25 +447,29 @@ int setup_general(fr_dvm *h, const fr_dvm_mesh *mesh, std::vector<double> &wq3J)
     // coordinate plane (the check above), and with the normal's tangential
     // part n_t, u'.n = -u.n + 2 u.n_t > -2 |n_t|_1 |u|_1, which the margin has
     // to cover too.
-    std::vector<double> nf4(nf.size() / 3 * 4);
-    std::vector<float> nff4(nf4.size());
+    std::vector<double> nf4(nf.size() / 3 * 4), nm(nf4.size());
+    std::vector<float> nff4(nf4.size()), nmf(nf4.size());
     for (size_t i = 0; i < nf.size() / 3; ++i) {
         const double *v = &nf[3 * i];
         const double l1 = std::fabs(v[0]) + std::fabs(v[1]) + std::fabs(v[2]);
         const int32_t *c = &conn[i / nfp * 4];
         const double tangential = c[0] < 0 && c[3] == 3 ? 2.0 * (l1 - std::fabs(v[c[2]])) : 0.0;
+        const size_t face = i / nfp * nfp * 4, q = i % nfp;
         for (int k = 0; k < 4; ++k) {
-            nf4[4 * i + k] = k < 3 ? v[k] : tangential + 1e-8 * l1;
-            nff4[4 * i + k] = (float)(k < 3 ? v[k] : tangential + 1e-5 * l1);
+            const size_t to = k < 3 ? face + 3 * q + k : face + 3 * nfp + q;
+            nf4[to] = nm[4 * i + k] = k < 3 ? v[k] : tangential + 1e-8 * l1;
+            nff4[to] = nmf[4 * i + k] = (float)(k < 3 ? v[k] : tangential + 1e-5 * l1);
         }
     }
-    if ((rc = dev_alloc(h, &h->d_nf, nf4.size())) || (rc = upload(h, h->d_nf, nf4.data(), nf4.size() * sizeof(double))))
+    if ((rc = dev_alloc(h, &h->d_nf, nf4.size())) || (rc = upload(h, h->d_nf, nf4.data(), nf4.size() * sizeof(double))) ||
+        (rc = dev_alloc(h, &h->d_nm, nm.size())) || (rc = upload(h, h->d_nm, nm.data(), nm.size() * sizeof(double))))
         return rc;
     {
         std::vector<float> Sf(S.begin(), S.end()), jf(ijac.begin(), ijac.end());
         if ((rc = dev_alloc(h, &h->d_Sf, Sf.size())) || (rc = upload(h, h->d_Sf, Sf.data(), Sf.size() * sizeof(float))) ||
             (rc = dev_alloc(h, &h->d_ijacf, jf.size())) || (rc = upload(h, h->d_ijacf, jf.data(), jf.size() * sizeof(float))) ||
-            (rc = dev_alloc(h, &h->d_nff, nff4.size())) || (rc = upload(h, h->d_nff, nff4.data(), nff4.size() * sizeof(float))))
+            (rc = dev_alloc(h, &h->d_nff, nff4.size())) || (rc = upload(h, h->d_nff, nff4.data(), nff4.size() * sizeof(float))) ||
+            (rc = dev_alloc(h, &h->d_nmf, nmf.size())) || (rc = upload(h, h->d_nmf, nmf.data(), nmf.size() * sizeof(float))))
             return rc;
     }
     if ((rc = dev_alloc(h, &h->d_conn, conn.size())) || (rc = upload(h, h->d_conn, conn.data(), conn.size() * sizeof(int32_t))))
@@ -877,7 +883,7 @@ extern "C" void fr_dvm_destroy(fr_dvm_t h) {
                     h->d_Q, h->d_Qpart, h->d_eq, h->d_ref[0], h->d_ref[1], h->d_ref[2], h->d_z, h->d_prim, h->d_stats, h->d_maxres, h->d_tot, h->d_mlp,
                     h->d_mlp_x, h->d_mlp_dz, h->d_pt_iters, h->d_pt_evals, h->d_pt_status,
                     h->d_pt_resid, h->d_S, h->d_ijac, h->d_nf, h->d_conn, h->d_wall, h->d_rw, h->d_mw,
-                    h->d_finf, h->d_Sf, h->d_ijacf, h->d_nff, h->d_gfp};
+                    h->d_finf, h->d_Sf, h->d_ijacf, h->d_nff, h->d_nm, h->d_nmf, h->d_gfp};
     for (void *p : ptrs)
         if (p) hipFree(p);
     for (auto &r : h->prof_recs) {

@@ -14,7 +14,7 @@ from hipstub import run
 CODE = """
 import json
 def unstored(n4, grid, ax, real):
-    # n4: normals and margins [points][4] of one face; rows per 64 velocities
+    # n4: normals and margins [points][4] of one face; a row is stored per 64 velocities
     a = [np.linspace(grid["umin"][d], grid["umax"][d], grid["n"][d]) for d in range(3)]
     n = grid["n"]
     iv = np.stack(np.meshgrid(*[np.arange(m) for m in n], indexing="ij"), -1).transpose(2, 1, 0, 3).reshape(-1, 3)
@@ -46,9 +46,13 @@ for ax in range(3):
                 pts = 2 * 6 * 9
                 for real, size in ((np.float64, 8), (np.float32, 4)):
                     tab = (C.c_double if size == 8 else C.c_float) * (pts * 4)
-                    p = hip.stub_find(pts * 4 * size, 0)
-                    assert p and not hip.stub_find(pts * 4 * size, 1)
-                    n4 = np.array(tab.from_address(p)).reshape(2, 6, 9, 4)
+                    # the table with the margins behind a face's normals, and the one with each at its normal
+                    p, q = hip.stub_find(pts * 4 * size, 0), hip.stub_find(pts * 4 * size, 1)
+                    assert p and q and not hip.stub_find(pts * 4 * size, 2)
+                    a, b = (np.array(tab.from_address(x)).reshape(2, 6, 36) for x in (p, q))
+                    if not np.array_equal(a[..., 27:], b.reshape(2, 6, 9, 4)[..., 3]): a, b = b, a
+                    n4 = b.reshape(2, 6, 9, 4)
+                    assert np.array_equal(a[..., 27:], n4[..., 3]) and np.array_equal(a[..., :27].reshape(2, 6, 9, 3), n4[..., :3])
                     for e in range(2):
                         for f in (2 * ax, 2 * ax + 1):
                             if mesh["bc"][e, f] != 3: continue
