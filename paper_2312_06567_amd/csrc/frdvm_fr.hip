@@ -1119,10 +1119,14 @@ void fill_args(fr_dvm *h, const StageArgs &sa, int do_traces, int do_moments, Fr
 // one another, and a launch of few rounds of resident workgroups ends in a
 // long, half-empty last round; such meshes have an element's chunks dealt to
 // several workgroups, whose moments k_moment_parts adds in order.
-//  * Where every workgroup still gets kSplitChunks chunks (its start-up,
-//    records and tables into LDS and the first chunk's loads exposed, is
-//    about one and a half): as many as make 16 rounds (the prime pass, which
-//    streams f at the copy rate by itself, 4).  Steps, one workgroup per
+//  * Where every workgroup still gets 8 chunks (its start-up, records and
+//    tables into LDS and the first chunk's loads exposed, is about one and a
+//    half): as many as make 16 rounds.  The prime pass streams f at the copy
+//    rate with few workgroups and has the moments' sums over the lanes at its
+//    end: 16 chunks, 4 rounds (FP64 at p = 3, the most bytes a workgroup, 2).
+//    Moments of 8^3 elements p = 3, 20^3 velocities, FP64: 1 workgroup per
+//    element 334 us, 4 342, 7 377; 10^3 p = 3, 9 x 33 x 6, FP32 1 113, 3 129;
+//    10^3 p = 2, 20^3, FP32 1 259, 6 188.  Steps, one workgroup per
 //    element -> the rule's: 6^3 elements p = 3 pair 5.0 -> 2.3 ms, 12^3 FP64
 //    ES 26.0 -> 24.9, 16^3 deviation storage 43.5 -> 43.0, 16^3 FP64 BGK
 //    24.2 -> 23.7; at 24^3 (18 rounds) nothing is split.
@@ -1133,12 +1137,13 @@ void fill_args(fr_dvm *h, const StageArgs &sa, int do_traces, int do_moments, Fr
 // It depends on the whole mesh only, so a launch over a part of the elements
 // sums in the same order.
 int box_split(const fr_dvm *h, bool prime) {
-    constexpr int kSplitChunks = 8;
     constexpr double kSplitSetup = 1.5;
     const int n = h->n, per_simd = prime ? 4 : (h->prm.precision == FR_DVM_FP64 ? FRDVM_WAVES_F64 : FRDVM_WAVES_F32);
-    const int64_t slots = 256 * (4 * per_simd / n), rounds = prime ? 4 : 16;  // (n <= 4)
+    const int64_t slots = 256 * (4 * per_simd / n);  // (n <= 4)
+    const int64_t rounds = prime ? (n == 4 && h->prm.precision == FR_DVM_FP64 ? 2 : 4) : 16;
+    const int chunks = prime ? 16 : 8;
     const int ntot = h->ncomp * ((h->vg.nu + kChunk - 1) / kChunk);
-    const int64_t most = ntot / kSplitChunks > 1 ? ntot / kSplitChunks : 1, want = (rounds * slots + h->ne - 1) / h->ne;
+    const int64_t most = ntot / chunks > 1 ? ntot / chunks : 1, want = (rounds * slots + h->ne - 1) / h->ne;
     if (h->ne * most >= 2 * slots) return (int)(want < most ? want : most);
     int s = 1;
     auto cost = [&](int q) { return (double)((h->ne * q + slots - 1) / slots) * ((ntot + q - 1) / q + kSplitSetup); };
