@@ -21,9 +21,10 @@
 // the face terms are formed line by line, direction by direction.  Every access to f, the
 // RK registers and the traces is a run of consecutive velocities.  Traces
 // have a place for every velocity at every flux point, [e][face][point][k]; a
-// lane stores one only where its velocity leaves the element there (within a
-// margin for rounding), which is where the neighbour, the wall and the mirror
-// image read it.
+// wave stores its row of a point where one of its velocities leaves the element
+// there (within a margin for rounding, on specular faces for the mirror image
+// too), which is where the neighbour, the wall and the mirror image read it;
+// small states store every row (kGenAllBytes).
 // The per-point moments are a separate reduction over the velocity axis.
 #include <hip/hip_runtime.h>
 
@@ -594,8 +595,8 @@ k_gen_stage(const GenArgs A) {
     const Real dt = (Real)A.sa.dt;
     Real *outE = reinterpret_cast<Real *>(A.sa.fout) + eoff;
     Real *dFE = reinterpret_cast<Real *>(A.sa.dF) + eoff;
-    // positivity limiter: the result is held in the lane's column until its
-    // element mean and smallest value are known
+    // positivity limiter: the result is held in the value registers (fv)
+    // until its element mean and smallest value are known
     const bool limit = A.sa.positivity != 0;
     const cptr<double> gW = (cptr<double>)A.wJ + e * NS;
     Real lim_min = Real(0);

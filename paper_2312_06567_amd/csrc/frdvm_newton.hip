@@ -15,11 +15,13 @@
 // (1, 0, 0, 0, 3/2), q = |c|^2 (BGK) or c^T A c with A = theta T^-1 (ES-BGK),
 // and g' = rho wt exp(...).
 //
-// BGK kernel: one thread per point.  On a tensor velocity grid the BGK
-// exponential factorises per axis, so each Newton iteration costs 3 n_v
-// exponentials and 1-D power sums instead of n_v^3 terms.
+// BGK kernel: one to eight lanes per point (by the number of points; the
+// result is the same for all).  On a tensor velocity grid the BGK exponential
+// factorises per axis, so each Newton iteration costs 3 n_v exponentials and
+// 1-D power sums instead of n_v^3 terms.
 // ES kernel: a wave per point for the sums, one thread per point for the
-// iteration around them; the state the two share lives in LDS.
+// iteration around them; the state the two share lives in LDS.  The sums come
+// in three forms, chosen per evaluation by the range of its exponents.
 // Starting points: cold (continuous equilibrium of the moments), warm (the
 // previous solution at the point) or learned (cold + a correction predicted
 // by the MLP kernels; the start with the smaller residual is kept, so the
@@ -260,7 +262,6 @@ __device__ void sums_bgk(const NewtonArgs &A, int lane, const double U[3], doubl
 // The state of a point's iteration that its wave and its owner thread share
 // (see k_newton_es): the frame (U, theta^-1/2, A = theta T^-1 as xx yy zz xy
 // xz yz), the point z under evaluation, and two sets of sums.
-constexpr int kSumsD = (int)(sizeof(Sums) / sizeof(double));
 struct EsPoint {
     double U[3], ist, A[6], z[5];
     Sums s[2];
@@ -1096,8 +1097,9 @@ __global__ __launch_bounds__(kBgkBlock) void k_newton_bgk(const NewtonArgs A) {
 // that the points request, one point per wave after the other, and then one
 // thread per point (the first es_pts threads) advances the point's iteration
 // and makes its next request, until no point has one.  Every wave reaches
-// every barrier, and a point makes at most max_iter + kRejectBudget + 3
-// requests after its first (an accepted step, its refresh, a rejected trial).
+// every barrier, and a point makes at most 2 max_iter + kRejectBudget + 1
+// requests after its first (an accepted trial and its refresh per iteration,
+// the rejected trials, the cold start).
 // Warm solves (two evaluations a point), 32 lanes per point running the whole
 // iteration and two-axis tables -> this form: 262,144 points of a 20^3 grid
 // 2.89 -> 1.66 ms, 62,208 of 24^3 1.19 -> 0.75, 51,200 of 24^3 0.97 -> 0.58;
