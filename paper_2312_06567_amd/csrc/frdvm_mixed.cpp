@@ -280,8 +280,9 @@ std::vector<V3> ref_verts(int t) {
 // lifts onto its column, a side face point (edge point e on layer k, face
 // index e + (p + 1) k) onto its layer.  The inverted matrices leave
 // rounding in the other entries; they are set to their exact value, zero
-// (the kernel reads the operators as streams, which have no such entries).  The face order (bottom, top, three
-// sides) and a structure that does not hold are reported as errors.
+// (the kernel reads the operators as streams, which have no such entries).
+// The face order (bottom, top, three sides) and a structure that does not
+// hold are reported as errors.
 int prism_structure(fr_dvm *h, MixType &T, int p) {
     const int ns = T.ns, nl = p + 1, nt = ns / nl, nft = T.nft;
     if (nt * nl != ns || nft != 2 * nt + 3 * nl * nl)
