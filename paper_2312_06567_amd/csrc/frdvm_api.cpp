@@ -45,13 +45,16 @@ int guess_mode(fr_dvm *h) {
 // How the moments a Newton solve is about to read are wanted: on small boxes
 // as the workgroups' parts, added by the solve itself, which saves a launch
 // (the learned start's features read the sums).  What it costs is the parts'
-// loads, one after the other, in the solve's first instructions: BGK spreads
-// them over a point's lanes, ES holds up a workgroup of points.  Steps with
-// the sums / with the parts, BGK: 512 points 90.2 / 84.2 us, 1620 260 / 253,
-// 13,824 793 / 777 and 904 / 879, above 32,000 within 1 %; ES: 512 points
-// 128.7 / 123.2 us, 1620 317 / 311, 5832 504 / 507, 13,824 1064 / 1122.
+// loads in the solve's first instructions: BGK spreads them over a point's
+// lanes, ES holds up a workgroup of points.  Steps with the sums / with the
+// parts, each from the same state (2 to 27 parts), BGK: 512 points 87.5 /
+// 82.2 us, 1620 259 / 253, 13,824 788 / 783 and 873 / 870, above that within
+// 0.6 % either way; ES: 512 points 129 / 125 us, 1620 312 / 307, 9600 1024 /
+// 1017, 13,824 1040 / 1033 and 1127 / 1121, above that within 0.6 %; pairs
+// (up to 54 parts): 512 points 137 / 132 us, 1728 804 / 797, 8000 2297 /
+// 2305, 13,824 1912 / 1911, 2138 / 2143 and 6774 / 6801.
 int solve_moments(fr_dvm *h, int guess) {
-    const int64_t most = h->prm.model == FR_DVM_ESBGK ? 4096 : 16384;
+    const int64_t most = 16384;
     return h->axis_mode && h->ne * h->ns <= most && newton_part_ok(h, guess) ? kMomentParts : 1;
 }
 
