@@ -24,7 +24,7 @@
 // wave stores its row of a point where one of its velocities leaves the element
 // there (within a margin for rounding, on specular faces for the mirror image
 // too), which is where the neighbour, the wall and the mirror image read it;
-// small states store every row (kGenAllBytes).
+// the first pass over a small state stores every row (kGenAllBytes).
 // The per-point moments are a separate reduction over the velocity axis.
 #include <hip/hip_runtime.h>
 
@@ -417,14 +417,14 @@ __device__ __forceinline__ void load_ext(const ExtArgs<Real> &X, int d, int km0,
 // 2 / 1 at p = 3, and at p = 1 what measured best (FP32 6: 596 us, 5: 647;
 // p = 2 FP32 at 4 spills: 5.39 for 5.22 ms).  (With the values of p = 3 in a
 // second LDS column, loops rolled, LDS held 4 / 2 waves per CU: 3.07 / 6.60 ms
-// per stage at 256 elements, 20^3 velocities, against 1.14 / 2.53.)  What
+// per stage at 256 elements, 20^3 velocities, against 1.15 / 2.30.)  What
 // bounds it: half VALU issue, half HBM (3.4-4.2 TB/s); p = 2 FP32, 2304
 // elements, 24^3, limiter on: 5.99 -> 5.34 ms per stage with the exterior
 // values requested a direction ahead, the connectivity and the metrics of
 // whole lines through the scalar cache, one random-number hash per lane
 // instead of per value, and the traces of waves that only enter left out;
 // 5.22 with the points of the collision in pairs (p = 3 FP32 1.32 -> 1.14, and
-// 63 registers fewer).
+// 63 registers fewer); 5.08 with the normals and margins as laid out below.
 template <typename Real, int P>
 constexpr int gen_waves() {
     if (sizeof(Real) == 8) return P == 3 ? 1 : 2;

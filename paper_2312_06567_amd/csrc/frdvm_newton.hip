@@ -1102,7 +1102,7 @@ __global__ __launch_bounds__(kBgkBlock) void k_newton_bgk(const NewtonArgs A) {
 // the rejected trials, the cold start).
 // Warm solves (two evaluations a point), 32 lanes per point running the whole
 // iteration and two-axis tables -> this form: 262,144 points of a 20^3 grid
-// 2.89 -> 1.66 ms, 62,208 of 24^3 1.19 -> 0.75, 51,200 of 24^3 0.97 -> 0.58;
+// 2.89 -> 1.73 ms, 62,208 of 24^3 1.19 -> 0.78, 51,200 of 24^3 0.97 -> 0.66;
 // the multiply-adds of the sums alone are 0.5 ms of the first.  Register
 // targets of 2 and 4 waves per SIMD: 1.97 and 1.71 ms.
 #ifndef FRDVM_WAVES_ES
